@@ -131,6 +131,18 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * DROT_FLAG_NO_GRAPH has no effect on it.  Setting any tile field keeps a
  * small problem on the sweep + aux path.  drot_result.path reports which
  * path ran. */
+/* Larger problems up to what the compute units' registers hold (float32 up to
+ * 4096 x 4096, float64 up to 2048 x 4096, any cost kind) take the resident
+ * path: one cooperative launch runs many iterations with the plan and the cost
+ * on the chip, tile by tile, and the tiles exchange their row and column sums.
+ * It needs all sweep-schedule fields 0, cache_mode AUTO, no flags (float64
+ * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32 and calls of
+ * drot_iterate for at least 8 iterations; anything else, and a stream that is
+ * being captured or has fewer compute units, runs sweep + aux launches from
+ * the same state.  Steps, state and stopping test are the same; sums are
+ * formed in another order, so results agree with sweep + aux to rounding.  A
+ * run that stops inside a launch repeats the iterations of that launch up to
+ * the stopping one (the test trails by two).  path reports 0. */
 typedef struct {
   double rho;          /* penalty parameter rho > 0 (the paper uses rho0/(m+n)) */
   double tol;          /* stopping tolerance >= 0; 0 runs exactly max_iter iterations */
@@ -138,7 +150,7 @@ typedef struct {
   int32_t tol_mode;    /* drot_tol_mode */
   int32_t x0_mode;     /* drot_x0_mode */
   int32_t check_every; /* iterations between host polls of the stop flag; 0 = 32
-                          (1024 on the one-workgroup path) */
+                          (1024 on the one-workgroup and resident paths) */
   int32_t flags;       /* DROT_FLAG_* */
   /* Sweep schedule (all 0 = automatic).  A workgroup owns a strip of
    * 64 * tile_chunks * (16 / element size) columns and the row blocks
@@ -155,9 +167,10 @@ typedef struct {
 typedef struct {
   int64_t iters;          /* iterations executed (K; X holds X_K) */
   int32_t status;         /* DROT_OK or DROT_MAXITER (or the error code) */
-  int32_t path;           /* how the iterations ran: 0 = sweep and aux launches
-                             (always in drot_solve_batched), 1 = the one-workgroup
-                             path (drot_params) */
+  int32_t path;           /* how the iterations ran: 0 = many workgroups (sweep and
+                             aux launches, or resident; always in
+                             drot_solve_batched), 1 = the one-workgroup path
+                             (drot_params) */
   double objective;       /* <C, X_K>, accumulated in FP64 over the returned X */
   double dual_objective;  /* p.mu + q.nu at the returned duals */
   double r_primal, r_dual, gap;          /* exact, at the returned (X, mu, nu) */
@@ -284,8 +297,8 @@ int drot_iterate(drot_ctx *ctx, int64_t iters, void *stream);
  * with the caller's other parameters, ready for drot_iterate from iteration
  * 0, and returned in *best (host; tile_rows, tile_chunks and tile_groups set).
  * *us_per_iter (host, may be NULL) receives its time per iteration.  A
- * problem on the one-workgroup path (drot_params) has no tile variants: it is
- * timed as bound (`iters` iterations, 0 = 256), bound again, and *best is the
+ * problem on the one-workgroup or the resident path (drot_params) has no tile
+ * variants: it is timed as bound (`iters` iterations, 0 = 256), bound again, and *best is the
  * caller's parameters.  X is overwritten by the trials, so the problem must have been bound with
  * x0_mode = DROT_X0_PQ (else DROT_EUNSUPPORTED); DROT_ESTATE without a bound
  * problem.  Blocks until done. */

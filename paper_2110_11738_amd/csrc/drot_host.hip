@@ -18,6 +18,7 @@
 
 #include "../../include/drot.h"
 #include "drot_internal.h"
+#include "drot_resident.h"
 
 using namespace drot;
 
@@ -82,6 +83,13 @@ struct drot_ctx {
   SweepArgs sa{};
   bool finished = false;
 
+  // Middle problems iterate with the plan on the chip (drot_resident.h): the
+  // team's record and messages (res_ws), on the device, allocated once.
+  bool res = false;
+  int res_rpw = 0, cus = 0;
+  void* res_ws = nullptr;
+  ResTeam* team_host = nullptr;  // pinned
+
   // Small problems iterate in one workgroup (small_kernel) instead of
   // sweep + aux launches.
   bool small = false;
@@ -120,6 +128,32 @@ void drop_graph(drot_ctx* c) {
   if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
   c->gexec = nullptr;
   c->g_iters = 0;
+}
+
+// Device memory of the resident iteration: the step counter, the team record,
+// then the messages of the largest team.
+constexpr size_t kResTeamOff = 256, kResMsgOff = 4096;
+constexpr int kResMaxTiles = 256, kResMaxSide = 128;
+static_assert(kResTeamOff + sizeof(ResTeam) <= kResMsgOff, "team record");
+size_t res_msg_bytes(int dtype, int rpw, int tiles) {
+  return sizeof(unsigned long long) * kResPhases * (size_t)tiles * res_msg_words(dtype, rpw);
+}
+
+// Rows per wave of the resident iteration for an m x n problem on `cus`
+// compute units, and its tiles; 0 if it does not fit.
+int choose_resident(int dtype, int64_t m, int64_t n, int cus, int* R, int* S) {
+  const int tiles = std::min(cus, kResMaxTiles);
+  const int64_t s = (n + res_cols(dtype) - 1) / res_cols(dtype);
+  int fit = 0;
+  for (int rpw : {4, 8, 16, 24, 32}) {
+    const int64_t r = (m + kResWaves * rpw - 1) / (kResWaves * rpw);
+    if (s > kResMaxSide || r > kResMaxSide || r * s > tiles) continue;
+    fit = rpw;
+    *R = (int)r;
+    *S = (int)s;
+    if (r <= 32) break;  // more tiles down: the column exchange outweighs the sweep
+  }
+  return fit;
 }
 
 int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, const void* X,
@@ -362,7 +396,7 @@ int launch_iteration(drot_ctx* c, hipStream_t s, hipEvent_t e0, hipEvent_t e1, i
 // Iterations per graph / per host poll (even under the skip-C schedule, so
 // that every graph starts with a C-reading iteration).
 int group_size(const drot_ctx* c) {
-  int g = c->prm.check_every > 0 ? c->prm.check_every : (c->small ? 1024 : 32);
+  int g = c->prm.check_every > 0 ? c->prm.check_every : (c->small || c->res ? 1024 : 32);
   if (c->skipc && (g & 1)) ++g;
   return g;
 }
@@ -603,12 +637,18 @@ int drot_ctx_create(drot_ctx** out, int device) {
   if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
     c->wall_rate = (double)khz * 1000.0;
   if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess ||
-      hipHostMalloc((void**)&c->st_host, sizeof(DevState), hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc((void**)&c->st_host, sizeof(DevState), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&c->team_host, sizeof(ResTeam), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     drot_ctx_destroy(c);
     return fail(DROT_EDEVICE, "stream or pinned allocation failed");
   }
   memset(c->st_host, 0, sizeof(DevState));
+  int coop = 0, cus = 0;
+  if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) == hipSuccess && coop &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess)
+    c->cus = cus;
+  (void)hipGetLastError();
   *out = c;
   return DROT_OK;
 }
@@ -620,7 +660,9 @@ int drot_ctx_destroy(drot_ctx* c) {
   drop_graph(c);
   for (auto e : c->ev) (void)hipEventDestroy(e);
   if (c->ws) (void)hipFree(c->ws);
+  if (c->res_ws) (void)hipFree(c->res_ws);
   if (c->st_host) (void)hipHostFree(c->st_host);
+  if (c->team_host) (void)hipHostFree(c->team_host);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   delete c;
   return DROT_OK;
@@ -662,6 +704,27 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
              prm->tile_groups == 0 && prm->cache_mode == DROT_CACHE_AUTO &&
              small_fits(dtype, m, n);
   c->pend = !c->small && aux_workgroups(m, n) < kAuxSplitMin;
+  // The resident iteration: default schedule, graphs allowed, plain sums, and
+  // launches long enough to carry their fixed cost (loading and writing back
+  // the plan and one closing exchange, about as much as ten iterations), so
+  // callers that poll more often than every 32 iterations stay on graphs.
+  int res_R = 0, res_S = 0;
+  const int plain = DROT_FLAG_NO_GRAPH | DROT_FLAG_TIME_SWEEP | DROT_FLAG_SKIP_C |
+                    (dtype == DROT_F32 ? DROT_FLAG_COMPENSATED : 0);
+  c->res = !c->small && !c->fixed_ws && c->team_host && !(prm->flags & plain) &&
+           (prm->check_every == 0 || prm->check_every >= 32) && prm->tile_rows == 0 &&
+           prm->tile_chunks == 0 && prm->tile_unroll == 0 && prm->tile_groups == 0 &&
+           prm->cache_mode == DROT_CACHE_AUTO &&
+           (c->res_rpw = choose_resident(dtype, m, n, c->cus, &res_R, &res_S)) > 0;
+  if (c->res && !c->res_ws) {
+    const size_t most = std::max(res_msg_bytes(DROT_F32, 32, kResMaxTiles),
+                                 res_msg_bytes(DROT_F64, 32, kResMaxTiles));
+    if (hipMalloc(&c->res_ws, kResMsgOff + most) != hipSuccess) {
+      (void)hipGetLastError();
+      c->res_ws = nullptr;
+      c->res = false;
+    }
+  }
   c->enq = 0;
   c->sweep_ms = 0.0;
   c->sweep_n = 0;
@@ -698,6 +761,23 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
   sa.trace_cap = kTraceCap;
   sa.wall_rate = c->wall_rate;
   sa.g = g.g;
+
+  if (c->res) {
+    const int V = dtype == DROT_F32 ? 4 : 2;
+    char* rws = static_cast<char*>(c->res_ws);
+    ResTeam* t = c->team_host;
+    t->a = sa;
+    t->R = res_R;
+    t->S = res_S;
+    t->vec_c = cost->kind == DROT_COST_DENSE && (uintptr_t)cost->data % 16 == 0 && cost->ld % V == 0;
+    t->vec_x = (uintptr_t)X % 16 == 0 && ldx % V == 0;
+    t->xch = reinterpret_cast<unsigned long long*>(rws + kResMsgOff);
+    t->seq = reinterpret_cast<uint32_t*>(rws);
+    HIP_TRY(hipMemsetAsync(rws, 0, kResTeamOff, s));
+    HIP_TRY(hipMemcpyAsync(rws + kResTeamOff, t, sizeof(ResTeam), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemsetAsync(rws + kResMsgOff, 0xff,
+                           res_msg_bytes(dtype, c->res_rpw, res_R * res_S), s));
+  }
 
   // Problem block of the device state.
   DevState* h = c->st_host;
@@ -774,6 +854,27 @@ int run_eager(drot_ctx* c, hipStream_t s, int64_t count) {
   return DROT_OK;
 }
 
+// Whether a cooperative launch of the bound team can go to `s` now: not into
+// a capture, and not onto a stream restricted to fewer compute units.
+bool resident_stream(const drot_ctx* c, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (s) {
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
+      int bits = 0;
+      for (uint32_t w : mask) bits += __builtin_popcount(w);
+      if (bits > 0 && bits < c->team_host->R * c->team_host->S) return false;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  return true;
+}
+
 }  // namespace
 
 extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
@@ -795,7 +896,27 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     }
     return DROT_OK;
   }
-  if (c->prm.flags & DROT_FLAG_NO_GRAPH) return run_eager(c, s, iters);
+  if (c->res && iters == 0) return DROT_OK;
+  if (c->res && iters >= kResMinIters && resident_stream(c, s)) {
+    // Bounded launches, as above; a rest too short for one, and everything
+    // where a launch is refused, goes to sweep + aux, from the same state.
+    constexpr int64_t kChunk = 4096;
+    while (c->res && iters >= kResMinIters) {
+      const int64_t k = std::min(iters, kChunk);
+      const char* rws = static_cast<const char*>(c->res_ws);
+      if (launch_resident(c->dtype, c->res_rpw, reinterpret_cast<const ResTeam*>(rws + kResTeamOff),
+                          nullptr, c->team_host->R * c->team_host->S, k, s) != hipSuccess) {
+        (void)hipGetLastError();
+        c->res = false;
+        break;
+      }
+      c->enq += k;
+      iters -= k;
+    }
+    if (c->res) return run_eager(c, s, iters);
+  }
+  if ((c->prm.flags & DROT_FLAG_NO_GRAPH) || (c->res && iters < group_size(c)))
+    return run_eager(c, s, iters);
   if ((rc = ensure_graph(c))) return rc;
   const int G = group_size(c);
   int64_t done = 0;
@@ -831,9 +952,9 @@ extern "C" int drot_tune(drot_ctx* c, int64_t iters, drot_params* best, double* 
   hipStream_t s = (hipStream_t)stream;
   const auto A = c->args;
   const drot_params user = c->prm;
-  if (c->small) {
-    // The one-workgroup path has no tile variants: time it, bind again, and
-    // return the caller's parameters.
+  if (c->small || c->res) {
+    // The one-workgroup and the resident path have no tile variants: time
+    // them, bind again, and return the caller's parameters.
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY(hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -851,7 +972,7 @@ extern "C" int drot_tune(drot_ctx* c, int64_t iters, drot_params* best, double* 
     if (!rc && (hipEventRecord(e0, s) != hipSuccess || drot_iterate(c, k, stream) != DROT_OK ||
                 hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
-      rc = fail(DROT_EDEVICE, "timing the one-workgroup path failed");
+      rc = fail(DROT_EDEVICE, "timing the bound path failed");
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
@@ -970,6 +1091,8 @@ int drot_finish(drot_ctx* c, double* mu, double* nu, drot_result* out, void* str
   out->sweep_timed = c->sweep_n;
   out->cost_scale = c->sa.cost_kind == kCostCoords ? h->cscale : 0.0;
   c->finished = true;
+  if (out->status == DROT_EDEVICE)
+    return fail(DROT_EDEVICE, "a workgroup of the resident iteration waited in vain for another");
   if (out->status == -3)
     return fail(DROT_ENONFINITE, "the iteration produced a non-finite value at iteration %lld",
                 (long long)h->stop_iter);

@@ -159,6 +159,24 @@ struct SweepArgs {
   SweepGeom g;
 };
 
+// The resident iteration (drot_resident.h): eight waves per workgroup, one
+// tile of 8 rpw rows and 64 * 16 / (element size) columns each.
+constexpr int kResWaves = 8;
+constexpr int kResBlock = kResWaves * kWave;
+constexpr int kResPhases = 4;  // message buffers per workgroup
+constexpr int kResMinIters = 8;  // shorter runs go to sweep + aux
+struct ResTeam {
+  SweepArgs a;
+  int R, S;              // tiles down and across
+  int vec_c, vec_x;      // C, X readable as 16-byte chunks
+  unsigned long long* xch;  // [kResPhases][R S] messages of res_msg_words words
+  uint32_t* seq;         // steps taken since the buffers were cleared
+};
+constexpr int res_cols(int dtype) { return kWave * (dtype == 0 ? 4 : 2); }
+constexpr int res_msg_words(int dtype, int rpw) {
+  return kResWaves * rpw / (dtype == 0 ? 2 : 1) + 128 + 16;
+}
+
 // Tile variant of the sweep: `vec` is 4 (float) / 2 (double) for 16-byte
 // loads or 1 for the scalar fallback; `chunks` the chunks per lane (1/2, or
 // 1/4 on the scalar path); `unroll` the rows kept in flight (4 or 8);

@@ -1,0 +1,863 @@
+// The resident iteration: whole iterations of Algorithm 1 with the plan and
+// the cost held on the chip.
+//
+// A problem is cut into R x S tiles, one workgroup (one compute unit) each.
+// A workgroup of eight waves loads its tile of X and of rho C once, keeps
+// both in registers (the largest tiles keep half of rho C in LDS) for up to
+// thousands of iterations, and writes X back at the end.  What crosses
+// workgroups in an iteration is O(rows + columns) per tile: the tile's row
+// and column partials and a few scalars, exchanged through memory.  256
+// compute units hold 128 MB of registers, so float32 problems up to
+// 4096 x 4096 (float64: up to 2048 x 4096) fit.
+//
+// The exchange.  Every workgroup owns one message per phase: its row
+// partials, its column partials and its scalars as 8-byte words, written with
+// device-scope stores (which bypass the per-XCD L2 caches) and polled with
+// device-scope loads by the workgroups of the same tile row and tile column
+// (everybody reads the scalar words).  A word that has not been written holds
+// the sentinel, so data and readiness travel together: one memory trip, no
+// flags, no fences, no atomic counters.  Message s lives in phase s mod 4.
+// Having published s, a workgroup puts the sentinel back into its words of
+// phase (s + 2) mod 4, i.e. of message s - 2, which every reader has consumed:
+// it published s - 1 after reading s - 2.  That reset is complete (vmcnt 0 and
+// a barrier) before s + 1 is published, so whoever has seen s + 1 and polls
+// for s + 2 cannot see message s - 2 any more.  A poll that runs dry ends the
+// kernel with an error state instead of spinning on.  All workgroups have to
+// be on the chip together: the launch is cooperative.
+//
+// Every workgroup of a tile row adds the same row partials in the same order
+// (columns likewise), so the row's duals are computed redundantly and
+// identically; the total of X, which gives beta, comes from the scalar words.
+//
+// The stopping test needs sums over all rows and columns of quantities that
+// follow from this exchange, so it trails: workgroup 0 tests iteration k
+// while it waits for the words of iteration k + 2, and announces a stop in
+// its next message.
+// By then X has moved on; the workgroups load the plan as it was when the
+// launch began and repeat the iterations up to the stopping one (everything
+// is deterministic), so the result is exactly X at the stopping iteration.
+//
+// What bounds it: latency up to about 2000 x 2000 -- publishing, one memory
+// trip to the peers and the reductions on both sides take 4.5 to 5 us (a probe
+// with the exchange alone: 2.7 us for 4 x 4 tiles, 3.5 us for 16 x 16) -- and
+// beyond that the vector units: nine operations per entry, 64 lanes per clock
+// and compute unit, 3.9 us for the 65536 entries per unit of 4096 x 4096.
+// Measured per iteration, float32, against sweep + aux launches: 5.1 us (10.6)
+// at 517 x 483, 5.4 (13.5) at 1000^2, 6.1 (17) at 2000^2, 12.4 (36.5) at
+// 4096^2; float64: 4.8 (14) at 700 x 901, 6.8 at 2000^2.
+#pragma once
+
+#include "drot_device.h"
+#include "drot_internal.h"
+
+namespace drot {
+namespace {
+
+typedef unsigned long long u64;
+constexpr u64 kSent = ~0ull;
+constexpr int kResSpins = 1 << 22;  // polls of one word before giving up (seconds)
+constexpr int kResScal = 16;        // scalar words of a message
+// Scalar words: total of the tile, <rho C, X>, sum [t]_+^2, stop iteration
+// (workgroup 0), and of the previous iteration sum r^2, sum p phi~ (tile
+// column 0), sum s^2, sum q psi~ (tile row 0).
+enum ResWord : int { kRwTot = 0, kRwS0, kRwS1, kRwCtl, kRwR2, kRwPphi, kRwS2, kRwQpsi, kRwCount };
+
+// Messages are global memory (the address space is spelled out because the
+// pointers come out of a record in memory).
+typedef __attribute__((address_space(1))) u64* Msg;
+__device__ __forceinline__ u64 ld_word(Msg p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_word(Msg p, u64 v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A message word of T: two floats or one double.  The sentinel is a NaN
+// pattern per value; a value that has it (a NaN) is replaced by another NaN.
+template <typename T>
+struct WordOf;
+template <>
+struct WordOf<float> {
+  static __device__ __forceinline__ bool missing(u64 w) {
+    return (uint32_t)w == 0xffffffffu || (uint32_t)(w >> 32) == 0xffffffffu;
+  }
+  static __device__ __forceinline__ uint32_t half(float v) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    return u == 0xffffffffu ? 0x7fc00000u : u;
+  }
+  static __device__ __forceinline__ u64 pack(float x, float y) {
+    return ((u64)half(y) << 32) | half(x);
+  }
+  static __device__ __forceinline__ void add(u64 w, double (&s)[2]) {
+    s[0] += (double)__builtin_bit_cast(float, (uint32_t)w);
+    s[1] += (double)__builtin_bit_cast(float, (uint32_t)(w >> 32));
+  }
+};
+__device__ __forceinline__ u64 pack_double(double v) {
+  const u64 u = __builtin_bit_cast(u64, v);
+  return u == kSent ? 0x7ff8000000000000ull : u;
+}
+template <>
+struct WordOf<double> {
+  static __device__ __forceinline__ bool missing(u64 w) { return w == kSent; }
+  static __device__ __forceinline__ void add(u64 w, double (&s)[1]) {
+    s[0] += __builtin_bit_cast(double, w);
+  }
+};
+
+// Lanes l < 32 get a's two halves added, lanes l >= 32 b's (v_permlane32_swap),
+// and the same for the even and odd rows of 16 lanes (v_permlane16_swap).
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a),
+                                                  __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]);
+  b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
+                                                  __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]);
+  b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((u64)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
+  b = __builtin_bit_cast(double, ((u64)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((u64)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
+  b = __builtin_bit_cast(double, ((u64)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
+}
+template <typename V>
+__device__ __forceinline__ V fold32(V a, V b) {
+  swap32(a, b);
+  return a + b;
+}
+template <typename V>
+__device__ __forceinline__ V fold16(V a, V b) {
+  swap16(a, b);
+  return a + b;
+}
+
+// Sums over the wave of G values at once (G = 8 or 4): lane l gets the sum of
+// value l / (64 / G).  Each folding step halves the registers, so eight sums
+// cost 18 operations instead of 48.
+template <typename V>
+__device__ __forceinline__ V wave_fold(V (&r)[8], int lane) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = fold32(r[i], r[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) r[i] = fold16(r[i], r[i + 2]);
+  const bool up = lane & 8;
+  const V keep = up ? r[1] : r[0], send = up ? r[0] : r[1];
+  V v = keep + dpp<0x128>(send);  // row_ror:8
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  return v;
+}
+template <typename V>
+__device__ __forceinline__ V wave_fold(V (&r)[4], int) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) r[i] = fold32(r[i], r[i + 2]);
+  V v = fold16(r[0], r[1]);
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  v += dpp<0x140>(v);
+  return v;
+}
+
+__device__ __forceinline__ float relu_of(float v) { return __builtin_fmaxf(v, 0.f); }
+__device__ __forceinline__ double relu_of(double v) { return __builtin_fmax(v, 0.0); }
+
+// Keeps the compiler from carrying `p` (and addresses made from it) in
+// registers from an earlier use: the plan takes most of them.
+template <typename P>
+__device__ __forceinline__ P* fresh(P* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Wave-uniform values, held in scalar registers.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename P>
+__device__ __forceinline__ P* uni(P* p) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<P*>(((uint64_t)(uint32_t)uni((int)(u >> 32)) << 32) | (uint32_t)uni((int)u));
+}
+__device__ __forceinline__ int64_t uni(int64_t v) {
+  return (int64_t)(((uint64_t)(uint32_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v));
+}
+
+// The same for a value whose comparisons are not worth a register.
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+__device__ __forceinline__ int fresh_lane(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Shared state of a workgroup outside the sums.
+struct ResShared {
+  double wsum[3][kResWaves];  // total, <rho C, X>, sum [t]_+^2 per wave
+  double esum[2][kResWaves];  // sum r^2 (or s^2), sum p phi~ (or q psi~) per wave
+  double bc[4][3];            // cphi, cpsi, alpha after iteration k, at k mod 4
+  double mon[2][6][kWave];    // workgroup 0: a step's test sums per lane, by step parity
+  double prev[2];             // workgroup 0: <rho C,X> and sum [t]_+^2 one iteration back
+  double rec[6];              // workgroup 0: the latest tested iteration
+  StateIn sv;
+  double ctl;                 // workgroup 0: stop iteration to announce
+  int rec_k, rec_status, rec_done;
+  int stop_at, dead;
+};
+
+// Poll up to four words until all are written; false when the spins run out.
+__device__ __forceinline__ bool res_poll(u64 (&w)[4], Msg p, int stride, int count) {
+  for (int spin = 0; spin < kResSpins; ++spin) {
+    bool again = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u < count && w[u] == kSent) {
+        w[u] = ld_word(p + u * stride);
+        again = true;
+      }
+    if (!again) return true;
+  }
+  return false;
+}
+
+// The four sums of iteration kt that waves 3 (rows) and 4 (columns) of
+// workgroup 0 read: even lanes hold the first word's, odd lanes the second's.
+__device__ __forceinline__ void res_keep(double (&mon)[6][kWave], int wave, int lane, double v) {
+  mon[2 * wave - 4][lane] = lane & 1 ? 0.0 : v;
+  mon[2 * wave - 3][lane] = lane & 1 ? v : 0.0;
+}
+
+// Workgroup 0, one wave: the test of iteration kt (of this launch; none if
+// kt < 1) with the sums that the step of iteration kt + 1 (or the closing
+// step) brought into sh.mon: <rho C,X> and sum [t]_+^2 of that step's own
+// iteration, kept for the next call, and the other four of iteration kt.
+__device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][kWave],
+                                         const ResTeam* tm, int kt, double rhoT, int lane) {
+  double v[6];
+#pragma unroll
+  for (int q = 0; q < 6; ++q) v[q] = mon[q][lane];
+  wave_sum_n(v);
+  if (lane != 0) return;
+  if (kt >= 1 && sh.ctl == 0.0) {
+    ScalarStep f;
+    f.cphi = sh.bc[kt & 3][0];
+    f.cpsi = sh.bc[kt & 3][1];
+    f.alpha = sh.bc[kt & 3][2];
+    f.k = sh.sv.iter + kt;
+    const double w[8] = {0.0, v[2], v[3], 0.0, v[4], v[5], sh.prev[0] / rhoT, sh.prev[1]};
+    scalar_tests(f, sh.sv, w, false);
+    commit_trace(tm->a, f, sh.sv.t_start, wall_clock64());
+    sh.rec[0] = f.pobj;
+    sh.rec[1] = f.dobj;
+    sh.rec[2] = f.rp;
+    sh.rec[3] = f.rd;
+    sh.rec[4] = f.gap;
+    sh.rec[5] = f.test;
+    sh.rec_k = kt;
+    sh.rec_done = f.done;
+    sh.rec_status = f.status;
+    if (f.done) sh.ctl = (double)kt;
+  }
+  sh.prev[0] = v[0];
+  sh.prev[1] = v[1];
+}
+
+// RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep rho C in
+// LDS.  `map`: the (team, workgroup) of each block, or null for the one team
+// teams[0].
+template <typename T, int RPW, int CL>
+__global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* teams,
+                                                                const uint2* map, int64_t iters) {
+  constexpr int VEC = 16 / sizeof(T);
+  constexpr int W = kWave * VEC;             // tile columns
+  constexpr int TR = kResWaves * RPW;        // tile rows
+  constexpr int PW = 8 / sizeof(T);          // values per message word
+  constexpr int WR = TR / PW, WC = W / PW;   // row and column words
+  constexpr int MSG = WR + WC + kResScal;
+  constexpr int GC = kResBlock / WC;         // peers read side by side, columns
+  constexpr int GR = kResBlock / WR;         // and rows
+  constexpr int G = RPW < 8 ? RPW : 8;       // rows whose sums are folded together
+  constexpr int kHeld = RPW - CL;            // rows with rho C in registers
+  constexpr int kBuf = kResWaves * W > GC * W + GR * TR ? kResWaves * W : GC * W + GR * TR;
+  // Words in flight per thread and batch: all of them for the usual team
+  // shapes, within the registers that a tile leaves.
+  constexpr int NBC = RPW >= 24 ? 4 : 8;
+  constexpr int NBR = sizeof(T) == 8 && RPW >= 16 ? 8 : 4;
+  static_assert(RPW % G == 0 && TR <= 256 && W <= 256 && MSG <= kResBlock, "thread roles");
+  static_assert(WC == 128, "message layout");
+  using Wd = WordOf<T>;
+
+  __shared__ double buf[kBuf];  // column sums of the waves, then the peers' sums
+  // rho C of the last CL rows; before that (and where CL = 0) the staging area
+  // of rows on their way between memory and registers, SR rows per wave.
+  constexpr int SR = CL > 0 ? CL : RPW < 8 ? RPW : 8;
+  static_assert(RPW % SR == 0 && (CL == 0 || SR == CL), "staging");
+  __shared__ __align__(16) T cl[kResWaves * SR * W];
+  __shared__ __align__(16) T rowsh[TR];
+  __shared__ __align__(16) T colsh[W];
+  __shared__ __align__(16) T rowp[TR];
+  __shared__ ResShared sh;
+
+  const uint2 who = map ? map[blockIdx.x] : uint2{0u, blockIdx.x};
+  const ResTeam* const tm = teams + uni((int)who.x);
+  const int b = uni((int)who.y);
+  DevState* const st = uni(tm->a.st);
+  if (uni(st->done)) return;
+  const int64_t left = uni(st->max_iter - st->iter);
+  int limit = (int)(iters < left ? iters : left);
+  if (limit <= 0) return;
+
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int R = uni(tm->R), S = uni(tm->S);
+  const int ti = uni(b / S), tj = b - ti * S;
+  const int m = uni((int)tm->a.g.m), n = uni((int)tm->a.g.n);
+  int seq = uni((int)*tm->seq);
+  const Msg xch = (Msg)uni(tm->xch);
+  const int phase = R * S * MSG;
+
+  // Roles: thread t < TR finishes row t of the tile, thread 256 + c column c.
+  const int row0 = ti * TR, col0 = tj * W;
+  const int cc0 = tid - 256;
+  const bool is_row = tid < TR, is_col = cc0 >= 0 && cc0 < W;
+  const int gid = is_row ? row0 + tid : col0 + cc0;  // row or column index
+  const bool own_r = is_row && gid < m, own_c = is_col && gid < n;
+  // The tile's entries of this lane: rows wr0 + r, columns jl .. jl + VEC - 1.
+  const int wr0 = row0 + wave * RPW;
+  const int jl = col0 + lane * VEC;
+  const int nv = n - jl >= VEC ? VEC : n > jl ? n - jl : 0;
+
+  // Words of the peers' messages that this thread reads: column word cw of
+  // the tile column's workgroups csub, csub + GC, ... (nc0 of them, from
+  // offset ocol on) and row word rw of the tile row's.
+  const int cw = tid & (WC - 1), csub = tid / WC;
+  const int rw = tid % WR, rsub = tid / WR;
+  const int nc0 = col0 + cw * PW < n && csub < R ? (R - csub + GC - 1) / GC : 0;
+  const int nr0 = rsub < GR && row0 + rw * PW < m && rsub < S ? (S - rsub + GR - 1) / GR : 0;
+  const int ocol = (csub * S + tj) * MSG + WR + cw, orow = (ti * S + rsub) * MSG + rw;
+
+  // Scalar words that a wave reads, up to four per lane, from word ox on with
+  // stride sx.  Every workgroup: wave 7 the totals, wave 2 the stop word.
+  // Workgroup 0: waves 5 and 6 <rho C,X> and the dual sums of all tiles, wave
+  // 3 the row sums (first tile column), wave 4 the column sums (first tile
+  // row), two words of every second workgroup.
+  int nx0 = 0, ox = WR + WC, sx = kWave * MSG;
+  if (wave == 7 || (b == 0 && (wave == 5 || wave == 6))) {
+    nx0 = R * S > lane ? (R * S - lane + kWave - 1) / kWave : 0;
+    ox += lane * MSG + (wave == 7 ? kRwTot : wave == 5 ? kRwS0 : kRwS1);
+  } else if (wave == 2) {
+    nx0 = 1;
+    ox += kRwCtl;
+  } else if (b == 0 && (wave == 3 || wave == 4)) {
+    const int cnt = wave == 3 ? R : S, step = wave == 3 ? S * MSG : MSG;
+    nx0 = cnt > (lane >> 1) ? (cnt - (lane >> 1) + kWave / 2 - 1) / (kWave / 2) : 0;
+    ox += (lane >> 1) * step + (wave == 3 ? kRwR2 : kRwS2) + (lane & 1);
+    sx = (kWave / 2) * step;
+  }
+
+  double marg = 0.0;
+  if (own_r) marg = (double)static_cast<const T*>(tm->a.p)[gid];
+  if (own_c) marg = (double)static_cast<const T*>(tm->a.q)[gid];
+  T xr[RPW][VEC], pc[kHeld][VEC];
+  const T rhoT = (T)st->rho;
+  T* const stage = cl + (wave * SR * kWave + lane) * VEC;  // + u * W: row u of the wave
+  if (tid == 0) {
+    sh.sv = load_state(st);
+    sh.ctl = 0.0;
+    sh.dead = 0;
+    sh.rec_k = sh.rec_done = sh.rec_status = 0;
+  }
+
+  double acc = 0.0, dual = 0.0;
+  bool replay = false;
+  int k = 0;
+  for (;;) {  // the iterations, and after a stop once more up to it
+    const ResTeam* const t2 = fresh(tm);
+    const int wl0 = fresh(wr0), nvl = fresh_lane(nv);
+    {
+      // X, then rho C.  Chunks of 16 bytes straight to registers where the
+      // layout allows (a chunk that straddles column n stays inside the row's
+      // leading dimension); else element by element through the staging area.
+      const T* const X = uni(static_cast<const T*>(t2->a.X));
+      const int64_t ldx = uni(t2->a.g.ldx);
+      if (uni(t2->vec_x)) {
+        const int jc = nvl > 0 ? jl : 0;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+          load_chunk<T, VEC, false>(X + (int64_t)(wl0 + r < m ? wl0 + r : m - 1) * ldx + jc, xr[r]);
+      } else {
+#pragma unroll
+        for (int g = 0; g < RPW / SR; ++g) {
+#pragma unroll 4
+          for (int u = 0; u < SR; ++u) {
+            const int i = wl0 + g * SR + u < m ? wl0 + g * SR + u : m - 1;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+              stage[u * W + e] = X[i * ldx + (e < nvl ? jl + e : 0)];
+          }
+#pragma unroll
+          for (int u = 0; u < SR; ++u) load_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
+        }
+      }
+      if (row0 + TR > m || col0 + W > n) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) xr[r][e] = wl0 + r < m && e < nvl ? xr[r][e] : (T)0;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const T kFar = (T)1e30;  // rho c outside the matrix: such entries stay 0
+      const int64_t ldc = uni(t2->a.g.ldc);
+      const int wc0 = fresh(wr0), nvc = fresh_lane(nv);
+      if (uni(t2->vec_c)) {
+        const T* const C = uni(static_cast<const T*>(t2->a.C));
+        const int jc = nvc > 0 ? jl : 0;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+          T c[VEC];
+          load_chunk<T, VEC, false>(C + (int64_t)(wc0 + r < m ? wc0 + r : m - 1) * ldc + jc, c);
+#pragma unroll
+          for (int e = 0; e < VEC; ++e)
+            c[e] = wc0 + r < m && e < nvc ? mul_rounded<T>(rhoT, c[e]) : kFar;
+          if (r < kHeld) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) pc[r < kHeld ? r : 0][e] = c[e];
+          } else {
+            store_chunk<T, VEC, false>(stage + (r - kHeld) * W, c);
+          }
+        }
+      } else {
+        const int kind = uni(t2->a.cost_kind), dim = uni(t2->a.dim);
+        const float cscale = (float)st->cscale;
+#pragma unroll
+        for (int g = 0; g < RPW / SR; ++g) {
+#pragma unroll 1
+          for (int u0 = 0; u0 < SR; u0 += 4) {
+            T c[4][VEC];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int64_t i = wc0 + g * SR + u0 + u < m ? wc0 + g * SR + u0 + u : m - 1;
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                const int64_t j = e < nvc ? jl + e : 0;
+                if (kind == kCostDense) {
+                  c[u][e] = static_cast<const T*>(t2->a.C)[i * ldc + j];
+                } else if (kind == kCostBF16) {
+                  c[u][e] = (T)__builtin_bit_cast(
+                      float, (uint32_t)static_cast<const uint16_t*>(t2->a.C)[i * ldc + j] << 16);
+                } else {
+                  float s = 0.f;
+                  for (int d = 0; d < dim; ++d) {
+                    const float df = t2->a.xs[i * dim + d] - t2->a.xt[j * dim + d];
+                    s += df * df;
+                  }
+                  c[u][e] = (T)(s * cscale);
+                }
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int e = 0; e < VEC; ++e)
+                stage[(u0 + u) * W + e] = wc0 + g * SR + u0 + u < m && e < nvc
+                                              ? mul_rounded<T>(rhoT, c[u][e]) : kFar;
+          }
+          if (g * SR < kHeld) {
+#pragma unroll
+            for (int u = 0; u < SR; ++u)
+              load_chunk<T, VEC, false>(stage + u * W, pc[g * SR < kHeld ? g * SR + u : 0]);
+          }
+        }
+      }
+    }
+    acc = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
+    if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : (T)0;
+    if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : (T)0;
+    if (tid == 0) {
+      sh.bc[0][0] = st->cphi;
+      sh.bc[0][1] = st->cpsi;
+      sh.bc[0][2] = st->alpha;
+      sh.stop_at = 0;
+    }
+    if (tid < 2 * kResWaves) sh.esum[tid & 1][tid >> 1] = 0.0;
+    __syncthreads();
+
+    for (k = 0; k < limit;) {  // sweep iteration k + 1, exchange, steps 5-8
+      const Msg cur = xch + (seq & 3) * phase;
+      // Step 4 on the held entries, with the row and column sums of step 5
+      // and the stopping-test sums.  A lane's float32 sums run over at most
+      // 8 rows; from there on everything is float64.
+      {
+        const T shift = (T)(sh.bc[k & 3][0] + sh.bc[k & 3][1]);
+        T colv[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) colv[e] = colsh[lane * VEC + e];
+        double cd[VEC], s0d = 0.0, s1d = 0.0, rtot = 0.0;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) cd[e] = 0.0;
+#pragma unroll
+        for (int g = 0; g < RPW / G; ++g) {
+          T ca[VEC], s0 = (T)0, s1 = (T)0, rs[G];
+#pragma unroll
+          for (int u = 0; u < G; ++u) {
+            const int r = g * G + u;
+            const T rowv = rowsh[wave * RPW + r] + shift;
+            T c[VEC];
+            if (r < kHeld) {
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) c[e] = pc[r < kHeld ? r : 0][e];
+            } else {
+              load_chunk<T, VEC, false>(stage + (r - kHeld) * W, c);
+            }
+            T rsum = (T)0;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+              const T t = rowv + colv[e] - c[e];
+              const T tp = relu_of(t);
+              s1 += tp * tp;
+              const T x = relu_of(xr[r][e] + t);
+              xr[r][e] = x;
+              rsum = e == 0 ? x : rsum + x;
+              ca[e] = u == 0 ? x : ca[e] + x;
+              s0 += c[e] * x;
+            }
+            rs[u] = rsum;
+          }
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) cd[e] += (double)ca[e];
+          s0d += (double)s0;
+          s1d += (double)s1;
+          const T v = wave_fold(rs, lane);
+          rowp[wave * RPW + g * G + lane / (kWave / G)] = v;  // its 64 / G lanes agree
+          rtot += (double)v;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) buf[wave * W + lane * VEC + e] = cd[e];
+        // rtot holds G distinct values, each in 64 / G neighbouring lanes
+        if (G == 8) rtot += dpp<0x128>(rtot);
+        rtot += dpp<0x142, 0xA>(rtot);
+        rtot += dpp<0x143, 0xC>(rtot);
+        double sx = fold32(s0d, s1d);  // lanes < 32: s0, others: s1
+        sx += dpp<0xB1>(sx);
+        sx += dpp<0x4E>(sx);
+        sx += dpp<0x141>(sx);
+        sx += dpp<0x140>(sx);
+        sx += dpp<0x142, 0xA>(sx);
+        if (lane == 63) {
+          sh.wsum[0][wave] = rtot;
+          sh.wsum[2][wave] = sx;
+        }
+        if (lane == 31) sh.wsum[1][wave] = sx;
+      }
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+
+      // Publish: thread t writes word t.
+      {
+        const Msg dst = cur + b * MSG + tid;
+        if (tid < WR) {
+          if constexpr (PW == 2) st_word(dst, Wd::pack(rowp[2 * tid], rowp[2 * tid + 1]));
+          else st_word(dst, pack_double((double)rowp[tid]));
+        } else if (tid < WR + WC) {
+          const int w = (tid - WR) * PW;
+          double v[PW];
+#pragma unroll
+          for (int e = 0; e < PW; ++e) v[e] = buf[w + e];
+#pragma unroll
+          for (int q = 1; q < kResWaves; ++q)
+#pragma unroll
+            for (int e = 0; e < PW; ++e) v[e] += buf[q * W + w + e];
+          if constexpr (PW == 2) st_word(dst, Wd::pack((float)v[0], (float)v[PW - 1]));
+          else st_word(dst, pack_double(v[0]));
+        } else if (tid < WR + WC + kRwCount) {
+          const int q = tid - WR - WC;
+          double v = 0.0;
+          if (q <= kRwS1) {
+#pragma unroll
+            for (int w = 0; w < kResWaves; ++w) v += sh.wsum[q][w];
+          } else if (q == kRwCtl) {
+            v = sh.ctl;
+          } else {
+            const int side = q >= kRwS2, which = (q - kRwR2) & 1;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v += sh.esum[which][4 * side + w];
+          }
+          st_word(dst, pack_double(v));
+        }
+        if (tid < MSG) st_word(xch + ((seq + 2) & 3) * phase + b * MSG + tid, kSent);
+      }
+      __syncthreads();  // `buf` changes its use
+
+      // While the peers' words are on their way: the test of iteration k - 1.
+      if (b == 0 && wave == 6 && !replay && k >= 1)
+        res_test(sh, sh.mon[(seq - 1) & 1], fresh(tm), k - 1, (double)rhoT, lane);
+
+      // Read the peers' words.  All loads of a batch are in flight together,
+      // and so are the repeats of those that came too early.
+      bool fine = true;
+      {
+        const int nc = fresh_lane(nc0), nr = fresh_lane(nr0), nx = fresh_lane(nx0);
+        const Msg pcol = cur + ocol, prow = cur + orow, px = cur + ox;
+        const int sc = GC * S * MSG, sr = GR * MSG;
+        double cs[PW], rsu[PW];
+        u64 wx[4];
+#pragma unroll
+        for (int e = 0; e < PW; ++e) cs[e] = rsu[e] = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (u < nx) wx[u] = ld_word(px + u * sx);
+        for (int qc = 0, qr = 0; qc < nc || qr < nr; qc += NBC, qr += NBR) {
+          u64 wc[NBC], wr[NBR];
+#pragma unroll
+          for (int u = 0; u < NBC; ++u)
+            if (qc + u < nc) wc[u] = ld_word(pcol + (qc + u) * sc);
+#pragma unroll
+          for (int u = 0; u < NBR; ++u)
+            if (qr + u < nr) wr[u] = ld_word(prow + (qr + u) * sr);
+          bool again = fine;
+          for (int spin = 0; again; ++spin) {
+            again = false;
+#pragma unroll
+            for (int u = 0; u < NBC; ++u)
+              if (qc + u < nc && Wd::missing(wc[u])) {
+                wc[u] = ld_word(pcol + (qc + u) * sc);
+                again = true;
+              }
+#pragma unroll
+            for (int u = 0; u < NBR; ++u)
+              if (qr + u < nr && Wd::missing(wr[u])) {
+                wr[u] = ld_word(prow + (qr + u) * sr);
+                again = true;
+              }
+            if (again && spin > kResSpins) fine = again = false;
+          }
+#pragma unroll
+          for (int u = 0; u < NBC; ++u)
+            if (qc + u < nc) Wd::add(wc[u], cs);
+#pragma unroll
+          for (int u = 0; u < NBR; ++u)
+            if (qr + u < nr) Wd::add(wr[u], rsu);
+        }
+#pragma unroll
+        for (int e = 0; e < PW; ++e) buf[tid * PW + e] = cs[e];  // [csub][column]
+        if (tid < GR * WR)
+#pragma unroll
+          for (int e = 0; e < PW; ++e) buf[GC * W + tid * PW + e] = rsu[e];  // [rsub][row]
+        if (wave >= 2) {
+          if (fine) fine = res_poll(wx, px, sx, nx);
+          double v = 0.0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (u < nx) v += __builtin_bit_cast(double, wx[u]);
+          if (wave == 7) {
+            // beta from the total of X, and the scalar parts of the shifts
+            v = wave_sum(v);
+            if (lane == 0) {
+              const double beta = (v - sh.sv.sum_p) / ((double)m + (double)n);
+              const double alpha = sh.bc[k & 3][2];
+              const double cc = 2.0 * beta - alpha;
+              sh.bc[(k + 1) & 3][0] = cc / (double)n;
+              sh.bc[(k + 1) & 3][1] = cc / (double)m;
+              sh.bc[(k + 1) & 3][2] = alpha - beta;
+            }
+          } else if (wave == 2) {
+            if (lane == 0 && !replay) sh.stop_at = (int)v;
+          } else if (b == 0 && wave >= 5) {
+            sh.mon[seq & 1][wave - 5][lane] = v;
+          } else if (b == 0) {
+            res_keep(sh.mon[seq & 1], wave, lane, v);
+          }
+        }
+      }
+      if (!fine) sh.dead = 1;
+      __syncthreads();
+      if (uni(sh.dead)) break;
+
+      // Steps 5-8 of this tile's rows and columns.
+      {
+        double tot = 0.0;
+        if (is_row) {
+          const int gr = S < GR ? S : GR;
+          for (int q = 0; q < gr; ++q) tot += buf[GC * W + q * TR + tid];
+        } else if (is_col) {
+          const int gc = R < GC ? R : GC;
+          for (int q = 0; q < gc; ++q) tot += buf[q * W + cc0];
+        }
+        double e[2] = {0.0, 0.0};
+        if (own_r || own_c) {
+          const double res = tot - marg;
+          dual = (acc - 2.0 * res) / (double)(is_row ? n : m);
+          acc -= res;
+          if (is_row) rowsh[tid] = (T)dual;
+          else colsh[cc0] = (T)dual;
+          e[0] = res * res;
+          e[1] = marg * dual;
+        }
+        __syncthreads();
+        // The sums that the test needs, from the first tile column and row
+        // (waves 0-3 hold rows, 4-7 columns).
+        if (!replay && ((wave < 4 && tj == 0) || (wave >= 4 && ti == 0))) {
+          wave_sum_n(e);
+          if (lane == 0) {
+            sh.esum[0][wave] = e[0];
+            sh.esum[1][wave] = e[1];
+          }
+        }
+      }
+      ++seq;
+      ++k;
+      if (uni(sh.stop_at) > 0) break;
+    }
+    if (uni(sh.dead)) break;
+    if (!replay && uni(sh.stop_at) == 0) {
+      // The closing exchange: the scalar words alone, for the last two tests.
+      const Msg cur = xch + (seq & 3) * phase;
+      if (b == 0 && wave == 6)
+        res_test(sh, sh.mon[(seq - 1) & 1], fresh(tm), k - 1, (double)rhoT, lane);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      const int q = tid - WR - WC;
+      if (q >= 0 && q < kRwCount) {
+        double v = q == kRwCtl ? sh.ctl : 0.0;
+        if (q >= kRwR2) {
+          const int side = q >= kRwS2, which = (q - kRwR2) & 1;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) v += sh.esum[which][4 * side + w];
+        }
+        st_word(cur + b * MSG + tid, pack_double(v));
+      }
+      if (tid < MSG) st_word(xch + ((seq + 2) & 3) * phase + b * MSG + tid, kSent);
+      if (wave == 2 || (b == 0 && (wave == 3 || wave == 4))) {
+        const Msg px = cur + ox;
+        u64 wx[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (u < nx0) wx[u] = ld_word(px + u * sx);
+        if (!res_poll(wx, px, sx, nx0)) sh.dead = 1;
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (u < nx0) v += __builtin_bit_cast(double, wx[u]);
+        if (wave != 2) res_keep(sh.mon[seq & 1], wave, lane, v);
+        else if (lane == 0) sh.stop_at = (int)v;
+      }
+      __syncthreads();
+      if (b == 0 && wave == 6)
+        res_test(sh, sh.mon[seq & 1], fresh(tm), k, (double)rhoT, lane);
+      ++seq;
+    }
+    if (uni(sh.dead) || replay || uni(sh.stop_at) == 0) break;
+    limit = uni(sh.stop_at);
+    replay = true;
+    __syncthreads();  // every thread has read stop_at
+  }
+  if (uni(sh.dead)) {  // a peer never published: report instead of hanging
+    if (tid == 0) {
+      st->done = 1;
+      st->status = -5;
+    }
+    return;
+  }
+
+  // Write back X, the vectors and the state.
+  const ResTeam* const t3 = fresh(tm);
+  const int ws0 = fresh(wr0), nvs = fresh_lane(nv);
+  {
+    T* const X = uni(static_cast<T*>(t3->a.X));
+    const int64_t ldx = uni(t3->a.g.ldx);
+    const bool vec = uni(t3->vec_x) != 0;
+    if (vec && nvs == VEC) {
+#pragma unroll
+      for (int r = 0; r < RPW; ++r)
+        if (ws0 + r < m) store_chunk<T, VEC, false>(X + (int64_t)(ws0 + r) * ldx + jl, xr[r]);
+    }
+    if (!vec || n % VEC != 0) {  // the other chunks, element by element
+      const int ne = vec && nvs == VEC ? 0 : nvs;
+#pragma unroll
+      for (int g = 0; g < RPW / SR; ++g) {
+#pragma unroll
+        for (int u = 0; u < SR; ++u) store_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
+#pragma unroll 1
+        for (int u = 0; u < SR; ++u) {
+          const int i = ws0 + g * SR + u;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e)
+            if (i < m && e < ne) X[i * ldx + jl + e] = stage[u * W + e];
+        }
+      }
+    }
+  }
+  if (own_r && tj == 0) {
+    t3->a.a[gid] = acc;
+    t3->a.phi64[gid] = dual;
+    static_cast<T*>(t3->a.phiT)[gid] = (T)dual;
+  }
+  if (own_c && ti == 0) {
+    t3->a.b[gid] = acc;
+    t3->a.psi64[gid] = dual;
+    static_cast<T*>(t3->a.psiT)[gid] = (T)dual;
+  }
+  if (b == 0 && tid == 6 * kWave) {
+    const uint64_t now = wall_clock64();
+    *t3->seq = (uint32_t)seq;
+    st->cphi = sh.bc[k & 3][0];
+    st->cpsi = sh.bc[k & 3][1];
+    st->alpha = sh.bc[k & 3][2];
+    st->iter = sh.sv.iter + k;
+    st->t_last = now;
+    st->pobj = sh.rec[0];
+    st->dobj = sh.rec[1];
+    st->rp = sh.rec[2];
+    st->rd = sh.rec[3];
+    st->gap = sh.rec[4];
+    st->test = sh.rec[5];
+    if (sh.rec_done) {
+      st->done = 1;
+      st->status = sh.rec_status;
+      st->stop_iter = sh.sv.iter + sh.rec_k;
+      st->t_stop = now;
+    }
+  }
+}
+
+template <typename T>
+const void* resident_entry(int rpw) {
+  switch (rpw) {
+    case 4: return reinterpret_cast<const void*>(&resident_kernel<T, 4, 0>);
+    case 8: return reinterpret_cast<const void*>(&resident_kernel<T, 8, 0>);
+    case 16: return reinterpret_cast<const void*>(&resident_kernel<T, 16, 0>);
+    case 24: return reinterpret_cast<const void*>(&resident_kernel<T, 24, 0>);
+    case 32: return reinterpret_cast<const void*>(&resident_kernel<T, 32, 16>);
+  }
+  return nullptr;
+}
+
+// Launch `blocks` workgroups of teams with `rpw` rows per wave.  Cooperative:
+// the workgroups wait for each other, so they have to be on the chip together.
+hipError_t launch_resident(int dtype, int rpw, const ResTeam* teams, const uint2* map, int blocks,
+                           int64_t iters, hipStream_t s) {
+  const void* f = dtype == 0 ? resident_entry<float>(rpw) : resident_entry<double>(rpw);
+  if (!f || blocks < 1) return hipErrorInvalidValue;
+  void* args[] = {(void*)&teams, (void*)&map, (void*)&iters};
+  return hipLaunchCooperativeKernel(f, dim3((unsigned)blocks), dim3(kResBlock), args, 0, s);
+}
+
+}  // namespace
+}  // namespace drot

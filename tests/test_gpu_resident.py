@@ -1,0 +1,115 @@
+"""The resident iteration (plan and cost on the chip, tiles exchanging their
+sums through memory) against the oracle: one shape for each tile height and
+type, at the edges of tiles; stops inside a launch; launches mixed with single
+iterations, which run as sweep + aux.
+
+Tolerances are those of tests/test_gpu_parity.py: in float64 only the order of
+the sums differs; in float32 a lane's sums run over at most 8 entries, a row's
+over 4 entries and 6 levels, and everything after that is float64, so the
+bound derived there for longer chains holds."""
+import numpy as np
+import pytest
+
+from gen import config_mixture_2d, round_to
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"float64": (1e-10, 1e-9), "float32": (2e-5, 2e-5)}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2110_11738_amd import drot
+    c = drot.Context(0)
+    yield c
+    c.close()
+
+
+def _inputs(inst, dtype):
+    import torch
+    t = lambda a: torch.tensor(a, dtype=getattr(torch, dtype), device="cuda")
+    return t(inst.C), t(inst.p), t(inst.q)
+
+
+def _instance(seed, m, n, dtype):
+    inst = config_mixture_2d(seed, m, n)
+    return round_to(inst, np.float32) if dtype == "float32" else inst
+
+
+def _rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+# Tiles are 8 h rows by 256 (float32) or 128 (float64) columns, h = 4 up to 32
+# tile rows, then 8, 16, 24, 32 as far as 256 tiles hold the problem.
+@pytest.mark.parametrize("dtype,m,n", [
+    ("float32", 129, 129), ("float32", 32, 1025), ("float32", 33, 513), ("float32", 1024, 255),
+    ("float32", 1025, 257), ("float32", 2048, 2049), ("float32", 2080, 3840),
+    ("float32", 4095, 4096), ("float32", 16500, 9),
+    ("float64", 65, 257), ("float64", 1024, 127), ("float64", 1100, 1030),
+    ("float64", 2049, 1024), ("float64", 2100, 2561), ("float64", 4000, 2047)])
+def test_trajectory(ctx, dtype, m, n):
+    import torch
+    from paper_2110_11738_amd import drot
+    inst = _instance(31, m, n, dtype)
+    K = 12
+    print(f"[resident] {dtype} {m}x{n}", flush=True)
+    X, res, mu, nu = drot.solve(*_inputs(inst, dtype), inst.rho, tol=0.0, max_iter=K, ctx=ctx)
+    torch.cuda.synchronize()
+    tr = ctx.trace(1, K)
+    R = ref.solve(inst.C, inst.p, inst.q, inst.rho, 0.0, max_iter=K, trace=True)
+    assert res["iters"] == K and res["status"] == 1 and res["path"] == 0
+    assert _rel(X.double().cpu().numpy(), R.X) <= TOL[dtype][0]
+    assert _rel(mu.cpu().numpy(), R.mu) <= TOL[dtype][1]
+    assert _rel(nu.cpu().numpy(), R.nu) <= TOL[dtype][1]
+    np.testing.assert_array_equal(tr[:, 7], np.arange(1, K + 1))
+    for c in range(5):  # pobj, dobj, r_primal, lagged r_dual, gap
+        assert _rel(tr[:, c], R.trace[:, c]) <= (1e-9 if dtype == "float64" else 1e-3)
+
+
+@pytest.mark.parametrize("m,n,at", [(300, 260, 1), (300, 260, 2), (1100, 140, 3), (200, 333, 64),
+                                    (64, 700, 1023), (64, 700, 1025)])
+def test_stops_inside_a_launch(ctx, m, n, at):
+    """A tolerance between the oracle's test values stops the run at exactly
+    that iteration, with X, the duals and the trace of that iteration."""
+    import torch
+    from paper_2110_11738_amd import drot
+    inst = _instance(32, m, n, "float64")
+    R = ref.solve(inst.C, inst.p, inst.q, inst.rho, 0.0, max_iter=at + 5, trace=True)
+    test = R.trace[:, 5]
+    tol = 1.000001 * test[:at].min()
+    at = int(np.argmax(test <= tol)) + 1
+    R = ref.solve(inst.C, inst.p, inst.q, inst.rho, 0.0, max_iter=at, trace=True)
+    X, res, mu, nu = drot.solve(*_inputs(inst, "float64"), inst.rho, tol=tol, max_iter=5000,
+                                ctx=ctx)
+    torch.cuda.synchronize()
+    tr = ctx.trace(1, at)
+    assert res["status"] == 0 and res["iters"] == at
+    assert _rel(X.cpu().numpy(), R.X) <= TOL["float64"][0]
+    assert _rel(mu.cpu().numpy(), R.mu) <= TOL["float64"][1]
+    assert _rel(tr[:, 5], R.trace[:, 5]) <= 1e-9
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_mixed_with_single_iterations_and_repeated(ctx, dtype):
+    import torch
+    from paper_2110_11738_amd import drot
+    inst = _instance(33, 700, 300, dtype)
+    C, p, q = _inputs(inst, dtype)
+    X = torch.empty_like(C)
+    plans = []
+    for _ in range(2):
+        ctx.bind(C, p, q, X, drot.make_params(inst.rho, 0.0, 100))
+        for k in (20, 1, 8, 3, 9):
+            ctx.iterate(k)
+        mu = torch.empty(700, dtype=torch.float64, device="cuda")
+        nu = torch.empty(300, dtype=torch.float64, device="cuda")
+        res = ctx.finish(mu, nu)
+        plans.append((X.clone(), mu.clone(), nu.clone()))
+    R = ref.solve(inst.C, inst.p, inst.q, inst.rho, 0.0, max_iter=41)
+    assert res["iters"] == 41
+    assert _rel(plans[0][0].double().cpu().numpy(), R.X) <= TOL[dtype][0]
+    assert _rel(plans[0][1].cpu().numpy(), R.mu) <= TOL[dtype][1]
+    for a, b in zip(*plans):
+        assert torch.equal(a, b)
