@@ -54,6 +54,13 @@ __device__ __forceinline__ V wave_sum(V v) {
   return lane63(v);
 }
 
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)(bits & 0xffffffffull), l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(bits >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 // wave_sum of N values at once: each DPP step is applied to all N before the
 // next, so that the N dependency chains overlap.  Every lane gets the totals.
 template <int N>
@@ -312,18 +319,16 @@ __device__ __forceinline__ ScalarStep scalar_step(const StateIn& sv, const doubl
   return f;
 }
 
-// The trace record of iteration f.k.  One thread.
-__device__ __forceinline__ void commit_trace(const SweepArgs& a, const ScalarStep& f,
-                                             uint64_t t_start, uint64_t now) {
-  const int64_t slot = f.k - 1 < a.trace_cap ? f.k - 1 : (f.k - 1) % a.trace_cap;
-  double* tr = a.trace + slot * kTraceWidth;
+// The trace record of iteration f.k into `tr`.  One thread.
+__device__ __forceinline__ void trace_record(double* tr, const ScalarStep& f, uint64_t t_start,
+                                             uint64_t now, double wall_rate) {
   tr[0] = f.pobj;
   tr[1] = f.dobj;
   tr[2] = f.rp;
   tr[3] = f.rd;
   tr[4] = f.gap;
   tr[5] = f.test;
-  tr[6] = (double)(now - t_start) / a.wall_rate;
+  tr[6] = (double)(now - t_start) / wall_rate;
   tr[7] = (double)f.k;
 }
 
@@ -346,7 +351,8 @@ __device__ __forceinline__ void commit_step(DevState* dst, const DevState* src,
   dst->rd = f.rd;
   dst->gap = f.gap;
   dst->test = f.test;
-  commit_trace(a, f, t_start, now);
+  const int64_t slot = f.k - 1 < a.trace_cap ? f.k - 1 : (f.k - 1) % a.trace_cap;
+  trace_record(a.trace + slot * kTraceWidth, f, t_start, now, a.wall_rate);
   if (f.done) {
     dst->done = 1;
     dst->status = f.status;

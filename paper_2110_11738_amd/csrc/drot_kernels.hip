@@ -440,13 +440,6 @@ __device__ __forceinline__ double row16_sum(double v) {
   return v;
 }
 
-__device__ __forceinline__ double read_lane(double v, int l) {
-  const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)(bits & 0xffffffffull), l);
-  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(bits >> 32), l);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 template <typename T, int NCOL>
 __global__ __launch_bounds__(kSmallBlock) void small_kernel(SweepArgs a, int64_t iters) {
   constexpr int NW = kSmallWaves;

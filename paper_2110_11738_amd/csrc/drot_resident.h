@@ -37,14 +37,20 @@
 // launch began and repeat the iterations up to the stopping one (everything
 // is deterministic), so the result is exactly X at the stopping iteration.
 //
-// What bounds it: latency up to about 2000 x 2000 -- publishing, one memory
-// trip to the peers and the reductions on both sides take 4.5 to 5 us (a probe
-// with the exchange alone: 2.7 us for 4 x 4 tiles, 3.5 us for 16 x 16) -- and
-// beyond that the vector units: nine operations per entry, 64 lanes per clock
-// and compute unit, 3.9 us for the 65536 entries per unit of 4096 x 4096.
-// Measured per iteration, float32, against sweep + aux launches: 5.1 us (10.6)
-// at 517 x 483, 5.4 (13.5) at 1000^2, 6.1 (17) at 2000^2, 12.4 (36.5) at
-// 4096^2; float64: 4.8 (14) at 700 x 901, 6.8 at 2000^2.
+// What bounds it: up to about 2000 x 2000 latency.  In 10.6 k clocks at
+// 517 x 483, 3.0 go to the sweep and its reductions (two waves share a SIMD),
+// 0.8 to publishing, 2.5 to 3.8 to the words' trip through memory, 1.8 to the
+// total and the scalar step, 1.0 to steps 5-8.  Beyond that the vector units:
+// nine operations per entry, 64 lanes per clock and compute unit, make 13.1 k
+// of the 22.7 k clocks at 4096 x 4096.  So nothing is spilled inside the
+// iteration loop (with spills: 12.4 us instead of 7.7 at 4096 x 4096): values
+// that depend on the thread number are made again in each step instead of
+// being kept, and the words of a poll are loaded without branches, all in
+// flight together (a branch and a wait per word: 5.1 us instead of 4.3 at
+// 517 x 483).
+// Measured per iteration, float32, against sweep + aux launches: 4.3 us (10.6)
+// at 517 x 483, 4.4 (13.5) at 1000^2, 5.1 (17) at 2000^2, 7.7 (36.5) at 4096^2;
+// float64: 4.1 (14) at 700 x 901, 9.0 at 2800^2.
 #pragma once
 
 #include "drot_device.h"
@@ -61,25 +67,40 @@ constexpr int kResScal = 16;        // scalar words of a message
 // (workgroup 0), and of the previous iteration sum r^2, sum p phi~ (tile
 // column 0), sum s^2, sum q psi~ (tile row 0).
 enum ResWord : int { kRwTot = 0, kRwS0, kRwS1, kRwCtl, kRwR2, kRwPphi, kRwS2, kRwQpsi, kRwCount };
+// A message: column words, row words, scalar words.
 
 // Messages are global memory (the address space is spelled out because the
 // pointers come out of a record in memory).
 typedef __attribute__((address_space(1))) u64* Msg;
-__device__ __forceinline__ u64 ld_word(Msg p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+typedef __attribute__((address_space(1))) char* MsgByte;
+// A word by wave-uniform base and 32-bit offset in bytes.
+__device__ __forceinline__ Msg word_at(Msg base, uint32_t off) { return (Msg)((MsgByte)base + off); }
+__device__ __forceinline__ u64 ld_word(Msg base, uint32_t off) {
+  return __hip_atomic_load(word_at(base, off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void st_word(Msg p, u64 v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void st_word(Msg base, uint32_t off, u64 v) {
+  __hip_atomic_store(word_at(base, off), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// x / d with r = 1 / d at hand: one Newton step on the quotient, three
+// operations in a row instead of the fifteen of a division.
+__device__ __forceinline__ double div_by(double x, double d, double r) {
+  const double q = x * r;
+  return __builtin_fma(__builtin_fma(-d, q, x), r, q);
 }
 
 // A message word of T: two floats or one double.  The sentinel is a NaN
 // pattern per value; a value that has it (a NaN) is replaced by another NaN.
+// gap() folds a word into a running maximum, which is all ones if and only if
+// a word was missing.
 template <typename T>
 struct WordOf;
 template <>
 struct WordOf<float> {
-  static __device__ __forceinline__ bool missing(u64 w) {
-    return (uint32_t)w == 0xffffffffu || (uint32_t)(w >> 32) == 0xffffffffu;
+  static __device__ __forceinline__ uint32_t gap(uint32_t g, u64 w) {
+    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+    const uint32_t t = lo > hi ? lo : hi;
+    return g > t ? g : t;
   }
   static __device__ __forceinline__ uint32_t half(float v) {
     const uint32_t u = __builtin_bit_cast(uint32_t, v);
@@ -99,7 +120,10 @@ __device__ __forceinline__ u64 pack_double(double v) {
 }
 template <>
 struct WordOf<double> {
-  static __device__ __forceinline__ bool missing(u64 w) { return w == kSent; }
+  static __device__ __forceinline__ uint32_t gap(uint32_t g, u64 w) {
+    const uint32_t t = (uint32_t)w & (uint32_t)(w >> 32);
+    return g > t ? g : t;
+  }
   static __device__ __forceinline__ void add(u64 w, double (&s)[1]) {
     s[0] += __builtin_bit_cast(double, w);
   }
@@ -200,38 +224,98 @@ __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+s"(v));
   return v;
 }
-__device__ __forceinline__ int fresh_lane(int v) {
+template <typename V>
+__device__ __forceinline__ V fresh_lane(V v) {
   asm volatile("" : "+v"(v));
   return v;
 }
 
 // Shared state of a workgroup outside the sums.
 struct ResShared {
-  double wsum[3][kResWaves];  // total, <rho C, X>, sum [t]_+^2 per wave
+  double wsum[3][kResWaves];  // total, <rho C,X>, sum [t]_+^2 per wave
   double esum[2][kResWaves];  // sum r^2 (or s^2), sum p phi~ (or q psi~) per wave
   double bc[4][3];            // cphi, cpsi, alpha after iteration k, at k mod 4
+  double inv[3];              // 1 / n, 1 / m, 1 / (m + n)
   double mon[2][6][kWave];    // workgroup 0: a step's test sums per lane, by step parity
   double prev[2];             // workgroup 0: <rho C,X> and sum [t]_+^2 one iteration back
   double rec[6];              // workgroup 0: the latest tested iteration
   StateIn sv;
+  double rhoT, wall_rate;
+  double* trace;
   double ctl;                 // workgroup 0: stop iteration to announce
+  int trace_mask;
   int rec_k, rec_status, rec_done;
   int stop_at, dead;
 };
 
-// Poll up to four words until all are written; false when the spins run out.
-__device__ __forceinline__ bool res_poll(u64 (&w)[4], Msg p, int stride, int count) {
-  for (int spin = 0; spin < kResSpins; ++spin) {
-    bool again = false;
+// Four words of a lane, `count` of them wanted (the rest repeats the last
+// one, so that all loads go out together without a branch).
+__device__ __forceinline__ void res_load4(u64 (&w)[4], Msg cur, uint32_t off, int stride, int count) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (u < count && w[u] == kSent) {
-        w[u] = ld_word(p + u * stride);
-        again = true;
-      }
-    if (!again) return true;
+  for (int u = 0; u < 4; ++u) {
+    const int q = u < count ? u : count > 0 ? count - 1 : 0;
+    w[u] = ld_word(cur, off + (uint32_t)(q * stride));
   }
-  return false;
+}
+// ... again until none is missing, and their sum; false when the spins run out.
+__device__ __forceinline__ bool res_sum4(u64 (&w)[4], Msg cur, uint32_t off, int stride, int count,
+                                         double& sum) {
+  bool fine = false;
+  for (int spin = 0; spin < kResSpins; ++spin) {
+    uint32_t g = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g = WordOf<double>::gap(g, w[u]);
+    fine = g != 0xffffffffu || count < 1;
+    if (fine) break;
+    res_load4(w, cur, off, stride, count);
+  }
+  sum = 0.0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) sum += u < count ? __builtin_bit_cast(double, w[u]) : 0.0;
+  return fine;
+}
+
+// Read and add a thread's column words (nc of them, the same for its wave,
+// stride sc) and row words (nr, stride sr), NC and NR at a time; nq rounds.
+// All loads of a round are in flight together, and so are the repeats.
+template <typename T, int NC, int NR, int PW>
+__device__ __forceinline__ bool res_read(Msg pcol, uint32_t ocol, int sc, int nc, Msg prow,
+                                         uint32_t orow, int sr, int nr, int nq, double (&cs)[PW],
+                                         double (&rs)[PW]) {
+  using Wd = WordOf<T>;
+  bool fine = true;
+  for (int q = 0; q < nq; ++q) {
+    u64 wc[NC], wr[NR];
+    bool ok = false;
+    for (int spin = 0; spin < kResSpins; ++spin) {
+#pragma unroll
+      for (int u = 0; u < NC; ++u) {
+        const int i = q * NC + u < nc ? q * NC + u : nc > 0 ? nc - 1 : 0;
+        wc[u] = ld_word(word_at(pcol, (uint32_t)(i * sc)), ocol);
+      }
+#pragma unroll
+      for (int u = 0; u < NR; ++u) {
+        const int i = q * NR + u < nr ? q * NR + u : nr > 0 ? nr - 1 : 0;
+        wr[u] = ld_word(prow, orow + (uint32_t)(i * sr));
+      }
+      uint32_t g = 0;
+#pragma unroll
+      for (int u = 0; u < NC; ++u) g = Wd::gap(g, wc[u]);
+#pragma unroll
+      for (int u = 0; u < NR; ++u) g = Wd::gap(g, wr[u]);
+      ok = g != 0xffffffffu;
+      if (ok) break;
+    }
+    fine = fine && ok;
+    if (!fine) break;
+#pragma unroll
+    for (int u = 0; u < NC; ++u)
+      if (q * NC + u < nc) Wd::add(wc[u], cs);
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+      if (q * NR + u < nr) Wd::add(wr[u], rs);
+  }
+  return fine;
 }
 
 // The four sums of iteration kt that waves 3 (rows) and 4 (columns) of
@@ -245,12 +329,21 @@ __device__ __forceinline__ void res_keep(double (&mon)[6][kWave], int wave, int 
 // kt < 1) with the sums that the step of iteration kt + 1 (or the closing
 // step) brought into sh.mon: <rho C,X> and sum [t]_+^2 of that step's own
 // iteration, kept for the next call, and the other four of iteration kt.
-__device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][kWave],
-                                         const ResTeam* tm, int kt, double rhoT, int lane) {
-  double v[6];
+__device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][kWave], int kt,
+                                         int lane) {
+  // lane 8 q + s adds eight entries of sum q, then its row of eight lanes
+  double v = 0.0;
+  if (lane < 48) {
+    const double* const p = &mon[0][0] + (lane >> 3) * kWave + (lane & 7);
 #pragma unroll
-  for (int q = 0; q < 6; ++q) v[q] = mon[q][lane];
-  wave_sum_n(v);
+    for (int u = 0; u < 8; ++u) v += p[8 * u];
+  }
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  double w[6];
+#pragma unroll
+  for (int q = 0; q < 6; ++q) w[q] = read_lane(v, 8 * q);
   if (lane != 0) return;
   if (kt >= 1 && sh.ctl == 0.0) {
     ScalarStep f;
@@ -258,9 +351,10 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
     f.cpsi = sh.bc[kt & 3][1];
     f.alpha = sh.bc[kt & 3][2];
     f.k = sh.sv.iter + kt;
-    const double w[8] = {0.0, v[2], v[3], 0.0, v[4], v[5], sh.prev[0] / rhoT, sh.prev[1]};
-    scalar_tests(f, sh.sv, w, false);
-    commit_trace(tm->a, f, sh.sv.t_start, wall_clock64());
+    const double ws[8] = {0.0, w[2], w[3], 0.0, w[4], w[5], sh.prev[0] / sh.rhoT, sh.prev[1]};
+    scalar_tests(f, sh.sv, ws, false);
+    double* const tr = sh.trace + (((int)f.k - 1) & sh.trace_mask) * kTraceWidth;
+    trace_record(tr, f, sh.sv.t_start, wall_clock64(), sh.wall_rate);
     sh.rec[0] = f.pobj;
     sh.rec[1] = f.dobj;
     sh.rec[2] = f.rp;
@@ -272,8 +366,8 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
     sh.rec_status = f.status;
     if (f.done) sh.ctl = (double)kt;
   }
-  sh.prev[0] = v[0];
-  sh.prev[1] = v[1];
+  sh.prev[0] = w[0];
+  sh.prev[1] = w[1];
 }
 
 // RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep rho C in
@@ -293,10 +387,9 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   constexpr int G = RPW < 8 ? RPW : 8;       // rows whose sums are folded together
   constexpr int kHeld = RPW - CL;            // rows with rho C in registers
   constexpr int kBuf = kResWaves * W > GC * W + GR * TR ? kResWaves * W : GC * W + GR * TR;
-  // Words in flight per thread and batch: all of them for the usual team
-  // shapes, within the registers that a tile leaves.
-  constexpr int NBC = RPW >= 24 ? 4 : 8;
-  constexpr int NBR = sizeof(T) == 8 && RPW >= 16 ? 8 : 4;
+  // Row words in flight per thread: all of them for the usual team shapes.
+  constexpr int NR = sizeof(T) == 4 ? (RPW == 4 ? 1 : RPW <= 16 ? 2 : 4)
+                                    : (RPW == 4 ? 2 : RPW <= 16 ? 4 : 8);
   static_assert(RPW % G == 0 && TR <= 256 && W <= 256 && MSG <= kResBlock, "thread roles");
   static_assert(WC == 128, "message layout");
   using Wd = WordOf<T>;
@@ -310,6 +403,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   __shared__ __align__(16) T rowsh[TR];
   __shared__ __align__(16) T colsh[W];
   __shared__ __align__(16) T rowp[TR];
+  __shared__ double accs[kResBlock];  // a_i, b_j of the thread's row or column
   __shared__ ResShared sh;
 
   const uint2 who = map ? map[blockIdx.x] : uint2{0u, blockIdx.x};
@@ -341,48 +435,53 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   const int jl = col0 + lane * VEC;
   const int nv = n - jl >= VEC ? VEC : n > jl ? n - jl : 0;
 
-  // Words of the peers' messages that this thread reads: column word cw of
-  // the tile column's workgroups csub, csub + GC, ... (nc0 of them, from
-  // offset ocol on) and row word rw of the tile row's.
-  const int cw = tid & (WC - 1), csub = tid / WC;
-  const int rw = tid % WR, rsub = tid / WR;
-  const int nc0 = col0 + cw * PW < n && csub < R ? (R - csub + GC - 1) / GC : 0;
-  const int nr0 = rsub < GR && row0 + rw * PW < m && rsub < S ? (S - rsub + GR - 1) / GR : 0;
-  const int ocol = (csub * S + tj) * MSG + WR + cw, orow = (ti * S + rsub) * MSG + rw;
+  // Words of the peers' messages that a thread reads: column word tid mod WC
+  // of the tile column's workgroups csub, csub + GC, ... (nc0 of them), and
+  // row word tid mod WR of the tile row's.  Only scalars are kept; what depends
+  // on the thread is made again in every step, which costs a few operations
+  // where keeping it would cost registers that the plan needs.
+  const int csub = uni(tid / WC);
+  const int nc0 = csub < R ? (R - csub + GC - 1) / GC : 0;
+  const int ocol = 8 * ((csub < R ? csub : 0) * S + tj) * MSG;
+  const int nqr = (S + GR * NR - 1) / (GR * NR);  // rounds for the row words
+  // Scalar words that a wave reads, up to four per lane: word ox + (lane mod
+  // (1 << xsh)) of every xstep-th byte from lane >> xsh on, xcnt of them.
+  // Every workgroup: wave 7 the totals, wave 2 the stop word.  Workgroup 0:
+  // waves 5 and 6 <rho C,X> and the dual sums of all tiles, wave 3 the row sums
+  // (first tile column), wave 4 the column sums (first tile row), two words
+  // of a workgroup by two lanes.
+  int xcnt = R * S, xstep = 8 * MSG, xsh = 0, xw = kRwTot;
+  if (wave == 2) xcnt = 1, xstep = 0, xw = kRwCtl;
+  if (wave == 3) xcnt = R, xstep = 8 * MSG * S, xsh = 1, xw = kRwR2;
+  if (wave == 4) xcnt = S, xsh = 1, xw = kRwS2;
+  if (wave == 5) xw = kRwS0;
+  if (wave == 6) xw = kRwS1;
+  const bool extra = wave == 2 || wave == 7 || (b == 0 && wave > 2);
+  // Words of its own message that a thread writes: column and row words by
+  // number, the scalar words in the last wave, which has no others.
+  static_assert(WC + WR <= kResBlock - kWave, "the last wave writes the scalar words");
+  static_assert(WC % kWave == 0, "a wave holds words of one kind and of one peer");
 
-  // Scalar words that a wave reads, up to four per lane, from word ox on with
-  // stride sx.  Every workgroup: wave 7 the totals, wave 2 the stop word.
-  // Workgroup 0: waves 5 and 6 <rho C,X> and the dual sums of all tiles, wave
-  // 3 the row sums (first tile column), wave 4 the column sums (first tile
-  // row), two words of every second workgroup.
-  int nx0 = 0, ox = WR + WC, sx = kWave * MSG;
-  if (wave == 7 || (b == 0 && (wave == 5 || wave == 6))) {
-    nx0 = R * S > lane ? (R * S - lane + kWave - 1) / kWave : 0;
-    ox += lane * MSG + (wave == 7 ? kRwTot : wave == 5 ? kRwS0 : kRwS1);
-  } else if (wave == 2) {
-    nx0 = 1;
-    ox += kRwCtl;
-  } else if (b == 0 && (wave == 3 || wave == 4)) {
-    const int cnt = wave == 3 ? R : S, step = wave == 3 ? S * MSG : MSG;
-    nx0 = cnt > (lane >> 1) ? (cnt - (lane >> 1) + kWave / 2 - 1) / (kWave / 2) : 0;
-    ox += (lane >> 1) * step + (wave == 3 ? kRwR2 : kRwS2) + (lane & 1);
-    sx = (kWave / 2) * step;
-  }
-
-  double marg = 0.0;
-  if (own_r) marg = (double)static_cast<const T*>(tm->a.p)[gid];
-  if (own_c) marg = (double)static_cast<const T*>(tm->a.q)[gid];
+  T marg = (T)0;
+  if (own_r) marg = static_cast<const T*>(tm->a.p)[gid];
+  if (own_c) marg = static_cast<const T*>(tm->a.q)[gid];
   T xr[RPW][VEC], pc[kHeld][VEC];
   const T rhoT = (T)st->rho;
   T* const stage = cl + (wave * SR * kWave + lane) * VEC;  // + u * W: row u of the wave
   if (tid == 0) {
     sh.sv = load_state(st);
+    sh.inv[0] = 1.0 / (double)n;
+    sh.inv[1] = 1.0 / (double)m;
+    sh.inv[2] = 1.0 / ((double)m + (double)n);
+    sh.rhoT = (double)rhoT;
+    sh.wall_rate = tm->a.wall_rate;
+    sh.trace = tm->a.trace;
+    sh.trace_mask = (int)tm->a.trace_cap - 1;
     sh.ctl = 0.0;
     sh.dead = 0;
     sh.rec_k = sh.rec_done = sh.rec_status = 0;
   }
 
-  double acc = 0.0, dual = 0.0;
   bool replay = false;
   int k = 0;
   for (;;) {  // the iterations, and after a stop once more up to it
@@ -486,7 +585,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         }
       }
     }
-    acc = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
+    accs[tid] = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
     if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : (T)0;
     if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : (T)0;
     if (tid == 0) {
@@ -504,7 +603,9 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       // and the stopping-test sums.  A lane's float32 sums run over at most
       // 8 rows; from there on everything is float64.
       {
+        const int lane = fresh_lane(tid) & (kWave - 1);
         const T shift = (T)(sh.bc[k & 3][0] + sh.bc[k & 3][1]);
+        T* const held = cl + (wave * SR * kWave + lane) * VEC;
         T colv[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) colv[e] = colsh[lane * VEC + e];
@@ -523,7 +624,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
 #pragma unroll
               for (int e = 0; e < VEC; ++e) c[e] = pc[r < kHeld ? r : 0][e];
             } else {
-              load_chunk<T, VEC, false>(stage + (r - kHeld) * W, c);
+              load_chunk<T, VEC, false>(held + (r - kHeld) * W, c);
             }
             T rsum = (T)0;
 #pragma unroll
@@ -569,119 +670,97 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
 
-      // Publish: thread t writes word t.
+      // Publish, then clear the words for the step after the next.
       {
-        const Msg dst = cur + b * MSG + tid;
-        if (tid < WR) {
-          if constexpr (PW == 2) st_word(dst, Wd::pack(rowp[2 * tid], rowp[2 * tid + 1]));
-          else st_word(dst, pack_double((double)rowp[tid]));
-        } else if (tid < WR + WC) {
-          const int w = (tid - WR) * PW;
+        const int t = fresh_lane(tid);
+        const Msg dst = word_at(cur, 8 * b * MSG);
+        const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
+        if (wave < WC / kWave) {
           double v[PW];
 #pragma unroll
-          for (int e = 0; e < PW; ++e) v[e] = buf[w + e];
+          for (int e = 0; e < PW; ++e) v[e] = buf[t * PW + e];
 #pragma unroll
           for (int q = 1; q < kResWaves; ++q)
 #pragma unroll
-            for (int e = 0; e < PW; ++e) v[e] += buf[q * W + w + e];
-          if constexpr (PW == 2) st_word(dst, Wd::pack((float)v[0], (float)v[PW - 1]));
-          else st_word(dst, pack_double(v[0]));
-        } else if (tid < WR + WC + kRwCount) {
-          const int q = tid - WR - WC;
-          double v = 0.0;
-          if (q <= kRwS1) {
-#pragma unroll
-            for (int w = 0; w < kResWaves; ++w) v += sh.wsum[q][w];
-          } else if (q == kRwCtl) {
-            v = sh.ctl;
-          } else {
-            const int side = q >= kRwS2, which = (q - kRwR2) & 1;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) v += sh.esum[which][4 * side + w];
+            for (int e = 0; e < PW; ++e) v[e] += buf[q * W + t * PW + e];
+          if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack((float)v[0], (float)v[PW - 1]));
+          else st_word(dst, 8 * t, pack_double(v[0]));
+          st_word(clr, 8 * t, kSent);
+        } else if (wave == kResWaves - 1) {
+          // the sum of eight (or four) LDS values from `src` on
+          const int q = t & (kWave - 1);
+          if (q < kRwCount) {
+            const double* src = q <= kRwS1 ? sh.wsum[q] : &sh.esum[q & 1][q >= kRwS2 ? 4 : 0];
+            double v = (src[0] + src[1]) + (src[2] + src[3]);
+            if (q <= kRwS1) v += (src[4] + src[5]) + (src[6] + src[7]);
+            if (q == kRwCtl) v = sh.ctl;
+            st_word(dst, 8 * (WC + WR + q), pack_double(v));
+            st_word(clr, 8 * (WC + WR + q), kSent);
           }
-          st_word(dst, pack_double(v));
+        } else if (t < WC + WR) {
+          const int w = t - WC;
+          if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack(rowp[2 * w], rowp[2 * w + 1]));
+          else st_word(dst, 8 * t, pack_double((double)rowp[w]));
+          st_word(clr, 8 * t, kSent);
         }
-        if (tid < MSG) st_word(xch + ((seq + 2) & 3) * phase + b * MSG + tid, kSent);
       }
       __syncthreads();  // `buf` changes its use
 
       // While the peers' words are on their way: the test of iteration k - 1.
       if (b == 0 && wave == 6 && !replay && k >= 1)
-        res_test(sh, sh.mon[(seq - 1) & 1], fresh(tm), k - 1, (double)rhoT, lane);
+        res_test(sh, sh.mon[(seq - 1) & 1], k - 1, lane);
 
       // Read the peers' words.  All loads of a batch are in flight together,
       // and so are the repeats of those that came too early.
       bool fine = true;
       {
-        const int nc = fresh_lane(nc0), nr = fresh_lane(nr0), nx = fresh_lane(nx0);
-        const Msg pcol = cur + ocol, prow = cur + orow, px = cur + ox;
-        const int sc = GC * S * MSG, sr = GR * MSG;
+        const int t = fresh_lane(tid), nc = fresh(nc0);
+        const int rsub = t / WR;
+        const int nr = rsub < GR && rsub < S ? (S - rsub + GR - 1) / GR : 0;
+        const uint32_t orow = 8 * ((nr > 0 ? rsub : 0) * MSG + t % WR);
+        const int sc = 8 * GC * S * MSG, sr = 8 * GR * MSG;
+        const Msg pcol = word_at(cur, ocol), prow = word_at(cur, 8 * (ti * S * MSG + WC));
+        const uint32_t vcol = 8 * (t & (WC - 1));
+        const int xl = (t & (kWave - 1)) >> xsh;  // which workgroup's word
+        const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
+        const uint32_t ox = 8 * (WC + WR + xw + (t & xsh)) + (nx > 0 ? xl * xstep : 0);
+        const int sx = xstep << (6 - xsh);
         double cs[PW], rsu[PW];
         u64 wx[4];
 #pragma unroll
         for (int e = 0; e < PW; ++e) cs[e] = rsu[e] = 0.0;
+        if (extra) res_load4(wx, cur, ox, sx, nx);
+        auto rounds = [&](int rc) { return rc > nqr ? rc : nqr; };
+        if (RPW >= 24 || (R > 2 * GC && R <= 4 * GC))
+          fine = res_read<T, 4, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 4 * GC - 1) / (4 * GC)), cs, rsu);
+        else if (R <= 2 * GC)
+          fine = res_read<T, 2, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds(1), cs, rsu);
+        else
+          fine = res_read<T, 8, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 8 * GC - 1) / (8 * GC)), cs, rsu);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (u < nx) wx[u] = ld_word(px + u * sx);
-        for (int qc = 0, qr = 0; qc < nc || qr < nr; qc += NBC, qr += NBR) {
-          u64 wc[NBC], wr[NBR];
+        for (int e = 0; e < PW; ++e) buf[t * PW + e] = cs[e];  // [csub][column]
+        if (t < GR * WR)
 #pragma unroll
-          for (int u = 0; u < NBC; ++u)
-            if (qc + u < nc) wc[u] = ld_word(pcol + (qc + u) * sc);
-#pragma unroll
-          for (int u = 0; u < NBR; ++u)
-            if (qr + u < nr) wr[u] = ld_word(prow + (qr + u) * sr);
-          bool again = fine;
-          for (int spin = 0; again; ++spin) {
-            again = false;
-#pragma unroll
-            for (int u = 0; u < NBC; ++u)
-              if (qc + u < nc && Wd::missing(wc[u])) {
-                wc[u] = ld_word(pcol + (qc + u) * sc);
-                again = true;
-              }
-#pragma unroll
-            for (int u = 0; u < NBR; ++u)
-              if (qr + u < nr && Wd::missing(wr[u])) {
-                wr[u] = ld_word(prow + (qr + u) * sr);
-                again = true;
-              }
-            if (again && spin > kResSpins) fine = again = false;
-          }
-#pragma unroll
-          for (int u = 0; u < NBC; ++u)
-            if (qc + u < nc) Wd::add(wc[u], cs);
-#pragma unroll
-          for (int u = 0; u < NBR; ++u)
-            if (qr + u < nr) Wd::add(wr[u], rsu);
-        }
-#pragma unroll
-        for (int e = 0; e < PW; ++e) buf[tid * PW + e] = cs[e];  // [csub][column]
-        if (tid < GR * WR)
-#pragma unroll
-          for (int e = 0; e < PW; ++e) buf[GC * W + tid * PW + e] = rsu[e];  // [rsub][row]
-        if (wave >= 2) {
-          if (fine) fine = res_poll(wx, px, sx, nx);
+          for (int e = 0; e < PW; ++e) buf[GC * W + t * PW + e] = rsu[e];  // [rsub][row]
+        if (extra) {
           double v = 0.0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (u < nx) v += __builtin_bit_cast(double, wx[u]);
+          if (fine) fine = res_sum4(wx, cur, ox, sx, nx, v);
           if (wave == 7) {
             // beta from the total of X, and the scalar parts of the shifts
             v = wave_sum(v);
             if (lane == 0) {
-              const double beta = (v - sh.sv.sum_p) / ((double)m + (double)n);
+              const double beta = div_by(v - sh.sv.sum_p, (double)fresh_lane(m) + (double)fresh_lane(n), sh.inv[2]);
               const double alpha = sh.bc[k & 3][2];
               const double cc = 2.0 * beta - alpha;
-              sh.bc[(k + 1) & 3][0] = cc / (double)n;
-              sh.bc[(k + 1) & 3][1] = cc / (double)m;
+              sh.bc[(k + 1) & 3][0] = div_by(cc, (double)fresh_lane(n), sh.inv[0]);
+              sh.bc[(k + 1) & 3][1] = div_by(cc, (double)fresh_lane(m), sh.inv[1]);
               sh.bc[(k + 1) & 3][2] = alpha - beta;
             }
           } else if (wave == 2) {
             if (lane == 0 && !replay) sh.stop_at = (int)v;
-          } else if (b == 0 && wave >= 5) {
+          } else if (wave >= 5) {
             sh.mon[seq & 1][wave - 5][lane] = v;
-          } else if (b == 0) {
+          } else {
             res_keep(sh.mon[seq & 1], wave, lane, v);
           }
         }
@@ -692,23 +771,39 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
 
       // Steps 5-8 of this tile's rows and columns.
       {
+        const int tid = fresh_lane((int)threadIdx.x), cc0 = tid - 256;
+        const bool is_row = tid < TR, is_col = cc0 >= 0 && cc0 < W;
+        const int gid = is_row ? row0 + tid : col0 + cc0;
+        const bool own_r = is_row && gid < m, own_c = is_col && gid < n;
         double tot = 0.0;
         if (is_row) {
-          const int gr = S < GR ? S : GR;
-          for (int q = 0; q < gr; ++q) tot += buf[GC * W + q * TR + tid];
+          for (int q = 0; q < GR && q < S; q += 4) {
+            // the peers' sums in order, zeros where there is no peer
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (q + u < GR) tot += buf[GC * W + (q + u) * TR + tid];
+          }
         } else if (is_col) {
-          const int gc = R < GC ? R : GC;
-          for (int q = 0; q < gc; ++q) tot += buf[q * W + cc0];
+#pragma unroll
+          for (int q = 0; q < GC; ++q) tot += buf[q * W + cc0];
         }
         double e[2] = {0.0, 0.0};
         if (own_r || own_c) {
-          const double res = tot - marg;
-          dual = (acc - 2.0 * res) / (double)(is_row ? n : m);
-          acc -= res;
+          const double mg = (double)fresh_lane(marg), acc = accs[tid];
+          const double res = tot - mg;
+          const int len = is_row ? n : m;
+          const double dual = div_by(acc - 2.0 * res, (double)fresh_lane(len), sh.inv[is_row ? 0 : 1]);
+          accs[tid] = acc - res;
           if (is_row) rowsh[tid] = (T)dual;
           else colsh[cc0] = (T)dual;
           e[0] = res * res;
-          e[1] = marg * dual;
+          e[1] = mg * dual;
+          // phi~ and psi~ in full, of what may be the last iteration
+          if (k + 1 == limit) {
+            const ResTeam* const t4 = fresh(tm);
+            if (is_row && tj == 0) t4->a.phi64[gid] = dual;
+            if (!is_row && ti == 0) t4->a.psi64[gid] = dual;
+          }
         }
         __syncthreads();
         // The sums that the test needs, from the first tile column and row
@@ -730,37 +825,37 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       // The closing exchange: the scalar words alone, for the last two tests.
       const Msg cur = xch + (seq & 3) * phase;
       if (b == 0 && wave == 6)
-        res_test(sh, sh.mon[(seq - 1) & 1], fresh(tm), k - 1, (double)rhoT, lane);
+        res_test(sh, sh.mon[(seq - 1) & 1], k - 1, lane);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      const int q = tid - WR - WC;
-      if (q >= 0 && q < kRwCount) {
-        double v = q == kRwCtl ? sh.ctl : 0.0;
-        if (q >= kRwR2) {
-          const int side = q >= kRwS2, which = (q - kRwR2) & 1;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) v += sh.esum[which][4 * side + w];
+      const Msg dst = word_at(cur, 8 * b * MSG);
+      const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
+      if (wave == kResWaves - 1) {
+        if (lane < kRwCount) {
+          const double* src = &sh.esum[lane & 1][lane >= kRwS2 ? 4 : 0];
+          double v = lane >= kRwR2 ? (src[0] + src[1]) + (src[2] + src[3]) : 0.0;
+          if (lane == kRwCtl) v = sh.ctl;
+          st_word(dst, 8 * (WC + WR + lane), pack_double(v));
+          st_word(clr, 8 * (WC + WR + lane), kSent);
         }
-        st_word(cur + b * MSG + tid, pack_double(v));
+      } else if (tid < WC + WR) {
+        st_word(clr, 8 * tid, kSent);
       }
-      if (tid < MSG) st_word(xch + ((seq + 2) & 3) * phase + b * MSG + tid, kSent);
       if (wave == 2 || (b == 0 && (wave == 3 || wave == 4))) {
-        const Msg px = cur + ox;
+        const int xl = lane >> xsh;
+        const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
+        const uint32_t ox = 8 * (WC + WR + xw + (lane & xsh)) + (nx > 0 ? xl * xstep : 0);
+        const int sx = xstep << (6 - xsh);
         u64 wx[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (u < nx0) wx[u] = ld_word(px + u * sx);
-        if (!res_poll(wx, px, sx, nx0)) sh.dead = 1;
         double v = 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (u < nx0) v += __builtin_bit_cast(double, wx[u]);
+        res_load4(wx, cur, ox, sx, nx);
+        if (!res_sum4(wx, cur, ox, sx, nx, v)) sh.dead = 1;
         if (wave != 2) res_keep(sh.mon[seq & 1], wave, lane, v);
         else if (lane == 0) sh.stop_at = (int)v;
       }
       __syncthreads();
       if (b == 0 && wave == 6)
-        res_test(sh, sh.mon[seq & 1], fresh(tm), k, (double)rhoT, lane);
+        res_test(sh, sh.mon[seq & 1], k, lane);
       ++seq;
     }
     if (uni(sh.dead) || replay || uni(sh.stop_at) == 0) break;
@@ -805,14 +900,12 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     }
   }
   if (own_r && tj == 0) {
-    t3->a.a[gid] = acc;
-    t3->a.phi64[gid] = dual;
-    static_cast<T*>(t3->a.phiT)[gid] = (T)dual;
+    t3->a.a[gid] = accs[tid];
+    static_cast<T*>(t3->a.phiT)[gid] = rowsh[tid];
   }
   if (own_c && ti == 0) {
-    t3->a.b[gid] = acc;
-    t3->a.psi64[gid] = dual;
-    static_cast<T*>(t3->a.psiT)[gid] = (T)dual;
+    t3->a.b[gid] = accs[tid];
+    static_cast<T*>(t3->a.psiT)[gid] = colsh[cc0];
   }
   if (b == 0 && tid == 6 * kWave) {
     const uint64_t now = wall_clock64();
