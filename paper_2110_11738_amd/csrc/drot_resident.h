@@ -729,6 +729,17 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         u64 wx[4];
 #pragma unroll
         for (int e = 0; e < PW; ++e) cs[e] = rsu[e] = 0.0;
+        // wave 7's scalar step: everything but the total, ready beforehand
+        double sum_p = 0.0, alpha = 0.0, dn = 0.0, dm = 0.0, inv[3] = {0.0, 0.0, 0.0};
+        auto scalars = [&]() {
+          sum_p = sh.sv.sum_p;
+          alpha = sh.bc[k & 3][2];
+          dn = (double)fresh_lane(n);
+          dm = (double)fresh_lane(m);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) inv[q] = sh.inv[q];
+        };
+        if (RPW <= 16 && wave == 7) scalars();
         if (extra) res_load4(wx, cur, ox, sx, nx);
         auto rounds = [&](int rc) { return rc > nqr ? rc : nqr; };
         if (RPW >= 24 || (R > 2 * GC && R <= 4 * GC))
@@ -748,12 +759,13 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           if (wave == 7) {
             // beta from the total of X, and the scalar parts of the shifts
             v = wave_sum(v);
+            if (RPW > 16) scalars();
+            const double beta = div_by(v - sum_p, dm + dn, inv[2]);
+            const double cc = 2.0 * beta - alpha;
+            const double nphi = div_by(cc, dn, inv[0]), npsi = div_by(cc, dm, inv[1]);
             if (lane == 0) {
-              const double beta = div_by(v - sh.sv.sum_p, (double)fresh_lane(m) + (double)fresh_lane(n), sh.inv[2]);
-              const double alpha = sh.bc[k & 3][2];
-              const double cc = 2.0 * beta - alpha;
-              sh.bc[(k + 1) & 3][0] = div_by(cc, (double)fresh_lane(n), sh.inv[0]);
-              sh.bc[(k + 1) & 3][1] = div_by(cc, (double)fresh_lane(m), sh.inv[1]);
+              sh.bc[(k + 1) & 3][0] = nphi;
+              sh.bc[(k + 1) & 3][1] = npsi;
               sh.bc[(k + 1) & 3][2] = alpha - beta;
             }
           } else if (wave == 2) {
@@ -809,11 +821,14 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         // The sums that the test needs, from the first tile column and row
         // (waves 0-3 hold rows, 4-7 columns).
         if (!replay && ((wave < 4 && tj == 0) || (wave >= 4 && ti == 0))) {
-          wave_sum_n(e);
-          if (lane == 0) {
-            sh.esum[0][wave] = e[0];
-            sh.esum[1][wave] = e[1];
-          }
+          double v = fold32(e[0], e[1]);  // lanes < 32: e[0], others: e[1]
+          v += dpp<0xB1>(v);
+          v += dpp<0x4E>(v);
+          v += dpp<0x141>(v);
+          v += dpp<0x140>(v);
+          v += dpp<0x142, 0xA>(v);
+          if (lane == 31) sh.esum[0][wave] = v;
+          if (lane == 63) sh.esum[1][wave] = v;
         }
       }
       ++seq;
