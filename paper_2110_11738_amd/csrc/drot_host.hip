@@ -133,24 +133,31 @@ void drop_graph(drot_ctx* c) {
 // Device memory of the resident iteration: the step counter, the team record,
 // then the messages of the largest team.
 constexpr size_t kResTeamOff = 256, kResMsgOff = 4096;
-constexpr int kResMaxTiles = 256, kResMaxSide = 128;
 static_assert(kResTeamOff + sizeof(ResTeam) <= kResMsgOff, "team record");
 size_t res_msg_bytes(int dtype, int rpw, int tiles) {
   return sizeof(unsigned long long) * kResPhases * (size_t)tiles * res_msg_words(dtype, rpw);
 }
 
+// Tiles of an m x n problem with `rpw` rows per wave; false if they are too
+// many for the compute units.
+bool resident_tiles(int dtype, int64_t m, int64_t n, int rpw, int cus, int* R, int* S) {
+  const int64_t s = (n + res_cols(dtype) - 1) / res_cols(dtype);
+  const int64_t r = (m + kResWaves * rpw - 1) / (kResWaves * rpw);
+  if (s > kResMaxSide || r > kResMaxSide || r * s > std::min(cus, kResMaxTiles)) return false;
+  *R = (int)r;
+  *S = (int)s;
+  return true;
+}
+
 // Rows per wave of the resident iteration for an m x n problem on `cus`
 // compute units, and its tiles; 0 if it does not fit.
 int choose_resident(int dtype, int64_t m, int64_t n, int cus, int* R, int* S) {
-  const int tiles = std::min(cus, kResMaxTiles);
-  const int64_t s = (n + res_cols(dtype) - 1) / res_cols(dtype);
-  int fit = 0;
-  for (int rpw : {4, 8, 16, 24, 32}) {
-    const int64_t r = (m + kResWaves * rpw - 1) / (kResWaves * rpw);
-    if (s > kResMaxSide || r > kResMaxSide || r * s > tiles) continue;
+  int fit = 0, r = 0, s = 0;
+  for (int rpw : kResRpw) {
+    if (!resident_tiles(dtype, m, n, rpw, cus, &r, &s)) continue;
     fit = rpw;
-    *R = (int)r;
-    *S = (int)s;
+    *R = r;
+    *S = s;
     if (r <= 32) break;  // more tiles down: the column exchange outweighs the sweep
   }
   return fit;
@@ -539,6 +546,27 @@ int harvest_events(drot_ctx* c, int pairs) {
   return DROT_OK;
 }
 
+// Whether a cooperative launch of `blocks` workgroups can go to `s` now: not into
+// a capture, and not onto a stream restricted to fewer compute units.
+bool resident_stream(hipStream_t s, int blocks) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (s) {
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
+      int bits = 0;
+      for (uint32_t w : mask) bits += __builtin_popcount(w);
+      if (bits > 0 && bits < blocks) return false;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  return true;
+}
+
 int check_ctx(drot_ctx* c) {
   if (!c) return fail(DROT_EINVAL, "ctx is NULL");
   HIP_TRY(hipSetDevice(c->device));
@@ -571,6 +599,24 @@ int drot_internal_batch_chunks(const drot_ctx* c, int key) {
 
 void drot_internal_set_batch_chunks(drot_ctx* c, int key, int chunks) {
   if (key >= 0 && key < 4) c->batch_chunks[key] = chunks;
+}
+
+// The resident iteration for the batched driver: the tiles of a problem (false
+// if they do not fit the chip), the message bytes of a launch, whether a
+// launch can go to a stream, and the launch.
+bool drot_internal_resident_tiles(const drot_ctx* c, int dtype, int64_t m, int64_t n, int rpw,
+                                  int* R, int* S) {
+  return resident_tiles(dtype, m, n, rpw, c->cus, R, S);
+}
+int drot_internal_resident_cap(const drot_ctx* c) { return std::min(c->cus, kResMaxTiles); }
+size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles) {
+  return res_msg_bytes(dtype, rpw, tiles);
+}
+bool drot_internal_resident_stream(hipStream_t s, int blocks) { return resident_stream(s, blocks); }
+hipError_t drot_internal_resident_launch(int dtype, int rpw, const ResTeam* teams,
+                                         const uint2* map, int blocks, int64_t iters,
+                                         hipStream_t s) {
+  return launch_resident(dtype, rpw, teams, map, blocks, iters, s);
 }
 
 // Make the context's workspace at least `bytes` large for a batched solve.
@@ -854,27 +900,6 @@ int run_eager(drot_ctx* c, hipStream_t s, int64_t count) {
   return DROT_OK;
 }
 
-// Whether a cooperative launch of the bound team can go to `s` now: not into
-// a capture, and not onto a stream restricted to fewer compute units.
-bool resident_stream(const drot_ctx* c, hipStream_t s) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (s) {
-    uint32_t mask[32] = {};
-    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
-      int bits = 0;
-      for (uint32_t w : mask) bits += __builtin_popcount(w);
-      if (bits > 0 && bits < c->team_host->R * c->team_host->S) return false;
-    } else {
-      (void)hipGetLastError();
-    }
-  }
-  return true;
-}
-
 }  // namespace
 
 extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
@@ -897,7 +922,8 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     return DROT_OK;
   }
   if (c->res && iters == 0) return DROT_OK;
-  if (c->res && iters >= kResMinIters && resident_stream(c, s)) {
+  const int res_blocks = c->res ? c->team_host->R * c->team_host->S : 0;
+  if (c->res && iters >= kResMinIters && resident_stream(s, res_blocks)) {
     // Bounded launches, as above; a rest too short for one, and everything
     // where a launch is refused, goes to sweep + aux, from the same state.
     constexpr int64_t kChunk = 4096;
@@ -905,7 +931,7 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
       const int64_t k = std::min(iters, kChunk);
       const char* rws = static_cast<const char*>(c->res_ws);
       if (launch_resident(c->dtype, c->res_rpw, reinterpret_cast<const ResTeam*>(rws + kResTeamOff),
-                          nullptr, c->team_host->R * c->team_host->S, k, s) != hipSuccess) {
+                          nullptr, res_blocks, k, s) != hipSuccess) {
         (void)hipGetLastError();
         c->res = false;
         break;

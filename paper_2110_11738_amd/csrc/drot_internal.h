@@ -165,6 +165,8 @@ constexpr int kResWaves = 8;
 constexpr int kResBlock = kResWaves * kWave;
 constexpr int kResPhases = 4;  // message buffers per workgroup
 constexpr int kResMinIters = 8;  // shorter runs go to sweep + aux
+constexpr int kResRpw[] = {4, 8, 16, 24, 32};
+constexpr int kResMaxTiles = 256, kResMaxSide = 128;  // workgroups of a team, tiles of a side
 struct ResTeam {
   SweepArgs a;
   int R, S;              // tiles down and across
