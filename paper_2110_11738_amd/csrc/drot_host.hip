@@ -616,7 +616,7 @@ bool drot_internal_resident_stream(hipStream_t s, int blocks) { return resident_
 hipError_t drot_internal_resident_launch(int dtype, int rpw, const ResTeam* teams,
                                          const uint2* map, int blocks, int64_t iters,
                                          hipStream_t s) {
-  return launch_resident(dtype, rpw, teams, map, blocks, iters, s);
+  return launch_resident(dtype, rpw, true, teams, map, blocks, iters, s);
 }
 
 // Make the context's workspace at least `bytes` large for a batched solve.
@@ -930,8 +930,9 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     while (c->res && iters >= kResMinIters) {
       const int64_t k = std::min(iters, kChunk);
       const char* rws = static_cast<const char*>(c->res_ws);
-      if (launch_resident(c->dtype, c->res_rpw, reinterpret_cast<const ResTeam*>(rws + kResTeamOff),
-                          nullptr, res_blocks, k, s) != hipSuccess) {
+      if (launch_resident(c->dtype, c->res_rpw, resident_fine(c->team_host->a.g.m, c->team_host->a.g.n),
+                          reinterpret_cast<const ResTeam*>(rws + kResTeamOff), nullptr, res_blocks,
+                          k, s) != hipSuccess) {
         (void)hipGetLastError();
         c->res = false;
         break;

@@ -373,7 +373,16 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
 // RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep rho C in
 // LDS.  `map`: the (team, workgroup) of each block, or null for the one team
 // teams[0].
-template <typename T, int RPW, int CL>
+//
+// FINE: column sums cross tiles unrounded where a plan has few columns or few
+// rows.  Such a side sums many entries into few duals, and a float rounding of
+// every tile's sum shows in them: nu of a float32 plan of 583 x 26 is 6.4e-7
+// off after 1000 iterations, 4.4e-7 with sweeps over blocks of four rows and
+// here.  With at most half a tile's columns (`slim`) each has a whole word, for
+// the sum as a float and what that leaves out; with one tile row (`lone`) the
+// tile's sums are the totals and are taken as they are.  In the other plans
+// the two cases would cost 0.1 us of 4.1 per iteration.
+template <typename T, int RPW, int CL, bool FINE>
 __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* teams,
                                                                 const uint2* map, int64_t iters) {
   constexpr int VEC = 16 / sizeof(T);
@@ -420,6 +429,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   const int R = uni(tm->R), S = uni(tm->S);
   const int ti = uni(b / S), tj = b - ti * S;
   const int m = uni((int)tm->a.g.m), n = uni((int)tm->a.g.n);
+  const bool slim = FINE && PW == 2 && n <= WC && R > 1;
+  const bool lone = FINE && R == 1;
   int seq = uni((int)*tm->seq);
   const Msg xch = (Msg)uni(tm->xch);
   const int phase = R * S * MSG;
@@ -441,7 +452,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   // on the thread is made again in every step, which costs a few operations
   // where keeping it would cost registers that the plan needs.
   const int csub = uni(tid / WC);
-  const int nc0 = csub < R ? (R - csub + GC - 1) / GC : 0;
+  const int nc0 = csub < R && !lone ? (R - csub + GC - 1) / GC : 0;
   const int ocol = 8 * ((csub < R ? csub : 0) * S + tj) * MSG;
   const int nqr = (S + GR * NR - 1) / (GR * NR);  // rounds for the row words
   // Scalar words that a wave reads, up to four per lane: word ox + (lane mod
@@ -671,18 +682,29 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       __syncthreads();
 
       // Publish, then clear the words for the step after the next.
+      double own[PW];
+#pragma unroll
+      for (int e = 0; e < PW; ++e) own[e] = 0.0;
       {
         const int t = fresh_lane(tid);
         const Msg dst = word_at(cur, 8 * b * MSG);
         const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
         if (wave < WC / kWave) {
           double v[PW];
+          const double* const src = buf + (slim ? t : t * PW);
 #pragma unroll
-          for (int e = 0; e < PW; ++e) v[e] = buf[t * PW + e];
+          for (int e = 0; e < PW; ++e) v[e] = src[e];
 #pragma unroll
           for (int q = 1; q < kResWaves; ++q)
 #pragma unroll
-            for (int e = 0; e < PW; ++e) v[e] += buf[q * W + t * PW + e];
+            for (int e = 0; e < PW; ++e) v[e] += src[q * W + e];
+          if (lone)
+#pragma unroll
+            for (int e = 0; e < PW; ++e) own[e] = v[e];
+          if (slim) {  // the column's sum as a float and what that leaves out
+            const double rest = v[0] - (double)(float)v[0];
+            v[PW - 1] = rest - rest == 0.0 ? rest : 0.0;
+          }
           if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack((float)v[0], (float)v[PW - 1]));
           else st_word(dst, 8 * t, pack_double(v[0]));
           st_word(clr, 8 * t, kSent);
@@ -749,7 +771,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         else
           fine = res_read<T, 8, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 8 * GC - 1) / (8 * GC)), cs, rsu);
 #pragma unroll
-        for (int e = 0; e < PW; ++e) buf[t * PW + e] = cs[e];  // [csub][column]
+        for (int e = 0; e < PW; ++e) buf[t * PW + e] = lone ? own[e] : cs[e];  // [csub][column]
         if (t < GR * WR)
 #pragma unroll
           for (int e = 0; e < PW; ++e) buf[GC * W + t * PW + e] = rsu[e];  // [rsub][row]
@@ -797,7 +819,9 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           }
         } else if (is_col) {
 #pragma unroll
-          for (int q = 0; q < GC; ++q) tot += buf[q * W + cc0];
+          for (int q = 0; q < GC; ++q)
+            tot += slim ? buf[q * W + 2 * (cc0 & (WC - 1))] + buf[q * W + 2 * (cc0 & (WC - 1)) + 1]
+                        : buf[q * W + cc0];
         }
         double e[2] = {0.0, 0.0};
         if (own_r || own_c) {
@@ -945,23 +969,30 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   }
 }
 
+// Plans with few rows or columns, which have the smallest tiles.
+inline bool resident_fine(int64_t m, int64_t n) {
+  return m <= kResWaves * kResRpw[0] || n <= kResBlock / 4;
+}
+
 template <typename T>
-const void* resident_entry(int rpw) {
+const void* resident_entry(int rpw, bool fine) {
   switch (rpw) {
-    case 4: return reinterpret_cast<const void*>(&resident_kernel<T, 4, 0>);
-    case 8: return reinterpret_cast<const void*>(&resident_kernel<T, 8, 0>);
-    case 16: return reinterpret_cast<const void*>(&resident_kernel<T, 16, 0>);
-    case 24: return reinterpret_cast<const void*>(&resident_kernel<T, 24, 0>);
-    case 32: return reinterpret_cast<const void*>(&resident_kernel<T, 32, 16>);
+    case 4: return fine ? reinterpret_cast<const void*>(&resident_kernel<T, 4, 0, true>)
+                        : reinterpret_cast<const void*>(&resident_kernel<T, 4, 0, false>);
+    case 8: return reinterpret_cast<const void*>(&resident_kernel<T, 8, 0, false>);
+    case 16: return reinterpret_cast<const void*>(&resident_kernel<T, 16, 0, false>);
+    case 24: return reinterpret_cast<const void*>(&resident_kernel<T, 24, 0, false>);
+    case 32: return reinterpret_cast<const void*>(&resident_kernel<T, 32, 16, false>);
   }
   return nullptr;
 }
 
 // Launch `blocks` workgroups of teams with `rpw` rows per wave.  Cooperative:
 // the workgroups wait for each other, so they have to be on the chip together.
-hipError_t launch_resident(int dtype, int rpw, const ResTeam* teams, const uint2* map, int blocks,
-                           int64_t iters, hipStream_t s) {
-  const void* f = dtype == 0 ? resident_entry<float>(rpw) : resident_entry<double>(rpw);
+// `fine`: for teams with a plan that resident_fine() names, at the smallest rpw.
+hipError_t launch_resident(int dtype, int rpw, bool fine, const ResTeam* teams, const uint2* map,
+                           int blocks, int64_t iters, hipStream_t s) {
+  const void* f = dtype == 0 ? resident_entry<float>(rpw, fine) : resident_entry<double>(rpw, fine);
   if (!f || blocks < 1) return hipErrorInvalidValue;
   void* args[] = {(void*)&teams, (void*)&map, (void*)&iters};
   return hipLaunchCooperativeKernel(f, dim3((unsigned)blocks), dim3(kResBlock), args, 0, s);

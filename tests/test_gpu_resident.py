@@ -156,3 +156,11 @@ def test_batch_stops_each_problem_on_its_own(ctx):
         R = ref.solve(inst.C, inst.p, inst.q, inst.rho, pr["tol"], max_iter=20000)
         assert res["status"] == 0 and res["iters"] == R.info["iters"]
         assert _rel(X.cpu().numpy(), R.X) <= TOL["float64"][0]
+
+
+# Few columns or one tile row: the column sums that cross tiles unrounded.
+@pytest.mark.parametrize("dtype,m,n", [
+    ("float32", 257, 128), ("float32", 583, 26), ("float32", 4096, 5), ("float32", 32, 513),
+    ("float32", 9, 530), ("float32", 12, 16640), ("float64", 32, 513), ("float64", 600, 26)])
+def test_trajectory_few_rows_or_columns(ctx, dtype, m, n):
+    test_trajectory(ctx, dtype, m, n)
