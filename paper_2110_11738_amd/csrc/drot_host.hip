@@ -191,11 +191,17 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
   if (aligned) {
     // Measured on MI355X: while X and C fit in the last-level cache, cached
     // accesses with 2 chunks per lane and 32-row blocks; above it, streaming
-    // accesses with 1 chunk per lane and 16-row blocks.
+    // accesses in 16-row blocks, with 1 chunk per lane where a dense cost takes
+    // the pass beyond 1 GB (2 chunks: 20000 x 20000 float32 776 -> 855 us per
+    // iteration, 14000 x 14000 371 -> 400) and 2 chunks otherwise (10000 x 10000
+    // float32 187 -> 180 us, 10000 x 15000 coordinates 205 -> 192, bf16
+    // 267 -> 257).  Narrow plans keep 1: a strip of 2 would be mostly padding.
     g.tile.vec = V;
     g.tile.stream = p->cache_mode == DROT_CACHE_STREAM ||
                     (p->cache_mode == DROT_CACHE_AUTO && bytes > 192.0 * 1024 * 1024);
-    g.tile.chunks = p->tile_chunks > 0 ? p->tile_chunks : (g.tile.stream ? 1 : 2);
+    const bool one = g.tile.stream && (g.tile.comp || n < 2048 ||
+                                       (cost->kind == DROT_COST_DENSE && bytes > 1e9));
+    g.tile.chunks = p->tile_chunks > 0 ? p->tile_chunks : (one ? 1 : 2);
     g.tile.unroll = p->tile_unroll > 0 ? p->tile_unroll : 4;
     g.tile.ragged = n % V != 0;
     if (g.tile.ragged || g.tile.comp) g.tile.unroll = 4;
@@ -217,14 +223,24 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
     while (rows > 4 && ((m + rows - 1) / rows) * n_ct < 512) rows /= 2;
   }
   const int64_t n_rb = (m + rows - 1) / rows;
-  // Row groups (workgroups per strip).  Cached problems: one row block per
-  // workgroup, which measured fastest (many short-lived workgroups keep the
-  // band in flight dense).  Streamed problems: two row blocks per workgroup,
-  // which measured 4-5% faster per iteration at 20000 x 20000 and halves the
-  // column partials that the aux kernel reads.
-  int64_t n_rg = p->tile_groups > 0 ? p->tile_groups
-                 : (g.tile.vec > 1 && g.tile.stream && p->tile_rows == 0) ? (n_rb + 1) / 2
-                                                                           : n_rb;
+  // Row groups (workgroups per strip).  A workgroup opens with the scalar step
+  // of the previous iteration and, for a coordinates cost, with its strip's
+  // target points, and each row group adds a row of column partials that the
+  // aux kernel reads: several row blocks per workgroup share all three.
+  // Streamed problems take 4 (20000 x 20000 float32 791 -> 776 us per iteration
+  // against 2, 20000 x 20000 coordinates 574 -> 541, 10000 x 15000 bf16
+  // 263 -> 257), dense costs below 1 GB 2 (10000 x 10000 180 us, with 4 188).
+  // Cached problems take 1, and 2 where the cost is not dense and 512
+  // workgroups are left (6900 x 6900 coordinates 71 -> 64 us; a dense
+  // 4500 x 4500 45 and 46).
+  const bool dense = cost->kind == DROT_COST_DENSE;
+  int64_t per = 1;
+  if (g.tile.vec > 1 && p->tile_rows == 0 && g.tile.stream)
+    per = g.tile.comp || (dense && g.tile.chunks == 2) ? 2 : 4;
+  else if (g.tile.vec > 1 && p->tile_rows == 0 && !dense && !g.tile.comp &&
+           (n_rb + 1) / 2 * n_ct >= 512)
+    per = 2;
+  int64_t n_rg = p->tile_groups > 0 ? p->tile_groups : (n_rb + per - 1) / per;
   n_rg = std::max<int64_t>(1, std::min<int64_t>(n_rg, n_rb));
   if (n_ct * n_rg > 0x7fffffffLL) return fail(DROT_EUNSUPPORTED, "too many tiles");
   g.g.m = m;
@@ -236,6 +252,18 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
   g.g.n_rg = (int)n_rg;
   g.g.rows = rows;
   g.g.ldcp = n_ct * W;
+  // Streamed problems still let an even spread of row blocks, kKeepBytes in
+  // all, go through the last-level cache with ordinary accesses: it holds them
+  // from one iteration to the next while the rest passes it by.  Measured, us
+  // per iteration, none kept -> 128 / 160 / 192 / 224 MB: 20000 x 20000 float32
+  // 807 -> 789 / 788 / 784 / 789; 10000 x 10000 218 -> 201 / 198 / 196 / 196;
+  // 10000 x 15000 coordinates 241 -> 231 / 230 / 229 / 231; 6000 x 6000 float32
+  // 91 -> 82 / 81 / 80 / 81.  A caller that asks for streaming accesses gets
+  // nothing else.
+  constexpr double kKeepBytes = 192e6;
+  g.g.keep = g.tile.stream && p->cache_mode == DROT_CACHE_AUTO
+                 ? (int)std::min(1024.0, 1024.0 * kKeepBytes / bytes)
+                 : 0;
   g.n_tiles = (int)(n_ct * n_rg);
   *out = g;
   return DROT_OK;

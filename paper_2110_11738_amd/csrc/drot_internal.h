@@ -118,6 +118,7 @@ struct SweepGeom {
   int n_rb;         // row blocks of `rows` rows
   int n_rg;         // row groups: workgroup (strip, g) sweeps row blocks g, g + n_rg, ...
   int rows;         // rows per row block
+  int keep;         // streamed problems: of 1024 row blocks, how many use the caches
 };
 
 struct SweepArgs {

@@ -1024,7 +1024,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
 
   P* __restrict__ rowpart = static_cast<P*>(a.rowpart);
 
-  for (int64_t rb = rg; rb < a.g.n_rb; rb += a.g.n_rg) {
+  // One row block; the policy says whether its accesses are nontemporal.
+  auto block = [&](int64_t rb, auto policy) {
+  constexpr bool STREAM = decltype(policy)::value;
   const int64_t row0 = rb * a.g.rows;
   const int64_t rowE = row0 + a.g.rows < m ? row0 + a.g.rows : m;
   const int64_t rw0 = row0 + (int64_t)wave * rpw;
@@ -1043,10 +1045,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
         for (int c = 0; c < CH; ++c) {
           if (ok[c]) {
             if constexpr (kReadC && CM == kCostDense)
-              load_chunk<T, VEC, NT>(C + i * a.g.ldc + jc[c], cv[u][c]);
+              load_chunk<T, VEC, STREAM>(C + i * a.g.ldc + jc[c], cv[u][c]);
             if constexpr (kReadC && CM == kCostBF16)
-              load_bf16<VEC, NT>(Cb + i * a.g.ldc + jc[c], cv[u][c]);
-            if (kReadX) load_chunk<T, VEC, NT>(X + i * a.g.ldx + jc[c], xv[u][c]);
+              load_bf16<VEC, STREAM>(Cb + i * a.g.ldc + jc[c], cv[u][c]);
+            if (kReadX) load_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], xv[u][c]);
           }
         }
       }
@@ -1125,7 +1127,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
             }
             if (kWriteX) {
               if (!RAGGED || nv[c] == VEC) {
-                store_chunk<T, VEC, NT>(X + i * a.g.ldx + jc[c], outv);
+                store_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], outv);
               } else {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
@@ -1139,6 +1141,18 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
       }
     }
   }
+  };
+  for (int64_t rb = rg; rb < a.g.n_rb; rb += a.g.n_rg) {
+    if constexpr (NT) {
+      // keep of every 1024 row blocks, evenly spread: each time the running
+      // multiple of keep passes a multiple of 1024.
+      if ((int)((uint32_t)rb * (uint32_t)a.g.keep & 1023u) < a.g.keep)
+        block(rb, std::integral_constant<bool, false>{});
+      else
+        block(rb, std::integral_constant<bool, true>{});
+    } else {
+      block(rb, std::integral_constant<bool, false>{});
+    }
   }
 
   // ---- tile partials: combine the four waves in LDS, fixed order -----------
