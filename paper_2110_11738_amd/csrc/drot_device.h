@@ -81,6 +81,55 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
   for (int s = 0; s < N; ++s) v[s] = lane63(v[s]);
 }
 
+// Lanes l < 32 get a's two halves added, lanes l >= 32 b's (v_permlane32_swap),
+// and the same for the even and odd rows of 16 lanes (v_permlane16_swap).
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a),
+                                                  __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]);
+  b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
+                                                  __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]);
+  b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
+  b = __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
+  b = __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
+}
+template <typename V>
+__device__ __forceinline__ V fold32(V a, V b) {
+  swap32(a, b);
+  return a + b;
+}
+template <typename V>
+__device__ __forceinline__ V fold16(V a, V b) {
+  swap16(a, b);
+  return a + b;
+}
+
+// x / d with r = 1 / d at hand: one Newton step on the quotient, three
+// operations in a row instead of the fifteen of a division.
+__device__ __forceinline__ double div_by(double x, double d, double r) {
+  const double q = x * r;
+  return __builtin_fma(__builtin_fma(-d, q, x), r, q);
+}
+
+__device__ __forceinline__ float relu_of(float v) { return __builtin_fmaxf(v, 0.f); }
+__device__ __forceinline__ double relu_of(double v) { return __builtin_fmax(v, 0.0); }
+
 // ---------------------------------------------------------------------------
 // Types and memory helpers.
 // ---------------------------------------------------------------------------

@@ -17,20 +17,22 @@ constexpr int kTraceWidth = 8;
 constexpr int kAuxCols = 64;       // columns per aux column workgroup
 constexpr int kAuxRows = kWave;    // rows per aux row workgroup
 constexpr int kAuxSplitMin = 256;  // from this many aux workgroups: separate finishing launch
-// One-workgroup iteration for small problems (see small_kernel).
-// One-workgroup path: kSmallBlock threads (16 waves) hold the plan and the
-// cost in registers, small_slots(dtype) entries of each per thread: wave w
-// owns rows w, w + 16, ... (small_rows of them), lane l the columns
-// l, l + 64, ... (small_cols of them, a power of two up to 8).
-constexpr int kSmallBlock = 1024;
-constexpr int kSmallWaves = kSmallBlock / kWave;
-constexpr int small_slots(int dtype) { return dtype == 0 ? 32 : 16; }
+// One-workgroup iteration for small problems (see small_kernel): kSmallWaves
+// waves hold the plan and rho C in registers and one more does the scalar
+// work.  Lane l has the columns l, l + 64, ... (small_cols of them, a power of
+// two up to 8); up to small_rows rows, small_wave_rows of them in a wave.
+constexpr int kSmallWaves = 11;
+constexpr int kSmallBlock = (kSmallWaves + 1) * kWave;
+constexpr int kSmallSnap = 64;  // iterations from one saved state to the next
 constexpr int small_cols(int64_t n) {
   return n <= kWave ? 1 : n <= 2 * kWave ? 2 : n <= 4 * kWave ? 4 : n <= 8 * kWave ? 8 : 0;
 }
+constexpr int small_rows(int dtype, int cols) { return (dtype == 0 ? 512 : 256) / cols; }
+constexpr int small_wave_rows(int dtype, int cols) {
+  return (small_rows(dtype, cols) + 3 * kSmallWaves - 1) / (3 * kSmallWaves) * 3;
+}
 constexpr bool small_fits(int dtype, int64_t m, int64_t n) {
-  return m >= 1 && n >= 1 && small_cols(n) > 0 &&
-         m <= (int64_t)kSmallWaves * (small_slots(dtype) / small_cols(n));
+  return m >= 1 && n >= 1 && small_cols(n) > 0 && m <= small_rows(dtype, small_cols(n));
 }
 
 // Workgroups of one aux launch: column groups of kAuxCols, then row groups of

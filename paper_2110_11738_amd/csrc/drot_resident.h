@@ -82,13 +82,6 @@ __device__ __forceinline__ void st_word(Msg base, uint32_t off, u64 v) {
   __hip_atomic_store(word_at(base, off), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// x / d with r = 1 / d at hand: one Newton step on the quotient, three
-// operations in a row instead of the fifteen of a division.
-__device__ __forceinline__ double div_by(double x, double d, double r) {
-  const double q = x * r;
-  return __builtin_fma(__builtin_fma(-d, q, x), r, q);
-}
-
 // A message word of T: two floats or one double.  The sentinel is a NaN
 // pattern per value; a value that has it (a NaN) is replaced by another NaN.
 // gap() folds a word into a running maximum, which is all ones if and only if
@@ -129,45 +122,6 @@ struct WordOf<double> {
   }
 };
 
-// Lanes l < 32 get a's two halves added, lanes l >= 32 b's (v_permlane32_swap),
-// and the same for the even and odd rows of 16 lanes (v_permlane16_swap).
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a),
-                                                  __builtin_bit_cast(uint32_t, b), false, false);
-  a = __builtin_bit_cast(float, (uint32_t)r[0]);
-  b = __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-__device__ __forceinline__ void swap16(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
-                                                  __builtin_bit_cast(uint32_t, b), false, false);
-  a = __builtin_bit_cast(float, (uint32_t)r[0]);
-  b = __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-__device__ __forceinline__ void swap32(double& a, double& b) {
-  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-  a = __builtin_bit_cast(double, ((u64)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
-  b = __builtin_bit_cast(double, ((u64)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
-}
-__device__ __forceinline__ void swap16(double& a, double& b) {
-  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-  a = __builtin_bit_cast(double, ((u64)(uint32_t)hi[0] << 32) | (uint32_t)lo[0]);
-  b = __builtin_bit_cast(double, ((u64)(uint32_t)hi[1] << 32) | (uint32_t)lo[1]);
-}
-template <typename V>
-__device__ __forceinline__ V fold32(V a, V b) {
-  swap32(a, b);
-  return a + b;
-}
-template <typename V>
-__device__ __forceinline__ V fold16(V a, V b) {
-  swap16(a, b);
-  return a + b;
-}
-
 // Sums over the wave of G values at once (G = 8 or 4): lane l gets the sum of
 // value l / (64 / G).  Each folding step halves the registers, so eight sums
 // cost 18 operations instead of 48.
@@ -196,9 +150,6 @@ __device__ __forceinline__ V wave_fold(V (&r)[4], int) {
   v += dpp<0x140>(v);
   return v;
 }
-
-__device__ __forceinline__ float relu_of(float v) { return __builtin_fmaxf(v, 0.f); }
-__device__ __forceinline__ double relu_of(double v) { return __builtin_fmax(v, 0.0); }
 
 // Keeps the compiler from carrying `p` (and addresses made from it) in
 // registers from an earlier use: the plan takes most of them.
