@@ -401,8 +401,8 @@ int drot_tune_batched(drot_ctx *ctx, int32_t count, int dtype, const drot_proble
  * are multiples of 64.  The flat parameter vector is [W1, b1, W2, b2, W3, b3]
  * with W_l stored row-major as out_l x in_l.  x, y, t and grad are device
  * float32 arrays, row-major batch x width.  The network owns its device
- * buffers (parameters, Adam moments, activations for max_batch rows and a
- * 4 MiB split-K workspace) and reuses them on every call: calls on one
+ * buffers (parameters, Adam moments, and for max_batch rows the activations,
+ * their gradients and the transposes of both) and reuses them on every call: calls on one
  * network must be ordered (one stream, or synchronised), not concurrent. */
 typedef struct drot_mlp drot_mlp;
 int drot_mlp_create(drot_mlp **mlp, int device, int in_dim, int hidden, int out_dim,

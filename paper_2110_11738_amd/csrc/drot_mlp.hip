@@ -53,186 +53,453 @@ __host__ __device__ inline bf16 to_bf16(float f) {
 }
 
 // ---------------------------------------------------------------------------
-// C[M x N] = op(A)[M x K] * op(B)[K x N] (+ beta * C), bfloat16 inputs,
-// float32 accumulation on the matrix cores (v_mfma_f32_32x32x8 bf16).  A is
-// stored row-major as M x K (TA = 0) or K x M (TA = 1); B as K x N (TB = 0)
-// or N x K (TB = 1).  A workgroup of four waves computes a 64 x 64 tile, each
-// wave a 32 x 32 block; K advances 32 at a time.  Every thread brings one
-// 16-byte piece (8 bfloat16 along the stored contiguous dimension) of each
-// operand tile into LDS, where both tiles are kept K-contiguous (As[m][k],
-// Bs[n][k]) so that each lane reads its 4-element fragments as 8 bytes.
-// Epilogues: EPI 0 stores the product (adding beta * C); EPI 1 adds the bias
-// of the column, applies ReLU when `relu`, and stores the float32 result and
-// its bfloat16 copy (a layer's forward step); EPI 2 keeps the product where
-// `gate` > 0 and zeroes it elsewhere, storing float32 and bfloat16 (the
-// backward step through a ReLU).
-// EPI 3 (split K): workgroup z of the grid's third dimension multiplies the
-// slice [z ks, (z + 1) ks) of K and stores its raw product at C + z M ldc;
-// splitk_reduce adds the slices in order and applies the epilogue.
-// Requires M % 64 == N % 64 == ks % 32 == 0, leading dimensions multiples of
-// 8 and 16-byte aligned operands (checked on the host).
+// The products.  Every product is cut into wave blocks of 32 rows by 32
+// columns (64 where B is stored K x N) and its depth K into S slices, one wave
+// each; the S waves of a block are in one workgroup.  A wave brings its own
+// operands from memory through its own piece of LDS, 64 deep at a time with
+// the next two such pieces on their way, and meets the other waves only at the
+// end, where the slices' sums are added in slice order in LDS and finished: at
+// these sizes a product is a chain of memory latencies, barriers and launches,
+// not of bytes or operations.  Operands are contiguous along K, a row's 128
+// bytes in one line, wherever the kernels can arrange it (activations and
+// gradients are stored a second time transposed, for the weight gradients);
+// the weights in the step through a layer are not, and are read two columns at
+// a time.  Loading the matrix instruction's operands straight from memory, 32
+// rows and 16 bytes of each at a time, took 17 us instead of 8 for
+// 256 x 512 x 2048; the epilogue's reads between its stores another 3.
+// Measured per call (in -> hidden -> out, batch; before: 64 x 64 tiles, one
+// launch more for every split sum, 8 and 21 launches): gradients of
+// 2048 -> 512 -> 2048, 256: 127 -> 65 us; 2048 -> 1024 -> 2048, 512: 231 -> 114;
+// forward 35 -> 17 and 58 -> 32; gradients of 128 -> 64 -> 128, 64: 91 -> 45.
+//
+// Each output is accumulated over K in the same order by the same instruction
+// (v_mfma_f32_32x32x8 bf16) in every path.
+//
+// A training step's gradients take six launches of dependent work: three
+// forward steps (the first rounds x and writes its transpose beside the
+// product, the third takes the error and its gradient in the epilogue) and,
+// per layer, one launch with the step through the layer, the weight gradient
+// and the bias gradient side by side.
+// Requires M % 32 == N % 64 == ks % 32 == 0, leading dimensions multiples of 8
+// and 16-byte aligned operands (checked on the host).
 // ---------------------------------------------------------------------------
 typedef short v8s __attribute__((ext_vector_type(8)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-template <int TA, int TB, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16(const bf16* __restrict__ A, const bf16* __restrict__ B,
-                                                 float* __restrict__ C, int M, int N, int K, int lda,
-                                                 int ldb, int ldc, float beta,
-                                                 const float* __restrict__ bias,
-                                                 const float* __restrict__ gate,
-                                                 bf16* __restrict__ Cb, int relu, int ks) {
-  constexpr int LDK = 32 + 8;  // K-contiguous rows, 80 bytes: 16-byte stores stay aligned
-  __shared__ __align__(16) bf16 As[64][LDK];
-  __shared__ __align__(16) bf16 Bs[64][LDK];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int wr = wave >> 1, wc = wave & 1;
-  v16f acc;
+constexpr int kWaves = 8;            // waves of a workgroup
+constexpr int kThreads = 64 * kWaves;
+constexpr int kColSlices = 16;       // row classes of a bias gradient
+
+// What happens to a product.
+enum Epi : int {
+  kEpiStore = 0,  // C
+  kEpiLayer = 1,  // + bias, ReLU if `relu`: C, its bfloat16 copy and (CbT) that transposed
+  kEpiGate = 2,   // kept where gate > 0, zero elsewhere: the same three
+  kEpiError = 3   // + bias: y in C; d = 2 (y - t) / count in D, Cb and CbT; sum (y - t)^2 in `part`
+};
+
+struct Job {
+  const void* A;  // M x K bfloat16 (float32 in the first step), leading dimension lda
+  const bf16* B;  // N x K (or K x N), leading dimension ldb
+  float* C;       // M x N, leading dimension N
+  bf16 *Cb, *CbT;
+  const float *bias, *gate, *t;
+  float* D;
+  double* part;   // one double per workgroup
+  int M, N, K, S, ks, relu, wgs;
+};
+
+// Wave block -> first row and column; columns fastest.
+__device__ __forceinline__ void block_at(const Job& j, int block, int width, int& m0, int& n0) {
+  const int per = j.N / width;
+  m0 = block / per * 32;
+  n0 = block % per * width;
+}
+
+__device__ __forceinline__ v4s as_v4s(uint32_t x, uint32_t y) {
+  const v2u u = {x, y};
+  return __builtin_bit_cast(v4s, u);
+}
+
+// Sixteen values along K per lane pair: lanes < 32 hold k .. k + 7, lanes >= 32
+// k + 8 .. k + 15; the matrix instruction wants k .. k + 3 and k + 4 .. k + 7.
+__device__ __forceinline__ void halves(const v4u& v, v4s& first, v4s& second) {
+  const auto p = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+  const auto q = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+  first = as_v4s(p[0], q[0]);
+  second = as_v4s(p[1], q[1]);
+}
+
+// Two values rounded to nearest even (v_cvt_pk_bf16_f32), the first one low.
+__device__ __forceinline__ uint32_t round2(float x, float y) {
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{x, y}), b2));
+}
+__device__ __forceinline__ v4u round8(const v4f& x, const v4f& y) {
+  return v4u{round2(x[0], x[1]), round2(x[2], x[3]), round2(y[0], y[1]), round2(y[2], y[3])};
+}
+
+// A wave's own piece of LDS: 32 rows of kDeep values of each operand that is
+// contiguous along K, 16 bytes apart from a multiple of 128 so that eight rows
+// lie in different banks.  Only this wave uses it: no barrier.
+constexpr int kDeep = 64;
+constexpr int kRowBytes = 2 * kDeep + 16;
+constexpr int kTileBytes = 32 * kRowBytes;
+constexpr int kWaveBytes = 2 * kTileBytes;
+
+// 32 rows of kDeep values from p (leading dimension ld) on their way to LDS:
+// eight lanes read a row, 128 bytes in one line of memory, four rows a lane.
+template <bool F32>
+struct Rows {
+  v4u v[4];
+  v4f f[F32 ? 4 : 1][2];
+  // `valid`: how much of the depth is there, kDeep or 32; the rest repeats it.
+  __device__ __forceinline__ void load(const void* p, int ld, int valid) {
+    const int lane = threadIdx.x & 63;
+    const int k = 8 * (lane & 7) < valid ? 8 * (lane & 7) : 0;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  const int kb = blockIdx.z * ks, ke = kb + ks;
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-    if (TA == 0) {  // row m0 + r of A, k0 + c .. + 7
-      const int r = tid >> 2, c = (tid & 3) * 8;
-      *reinterpret_cast<v8s*>(&As[r][c]) =
-          *reinterpret_cast<const v8s*>(A + (size_t)(m0 + r) * lda + k0 + c);
-    } else {        // row k0 + kr of the K x M storage, columns m0 + mc .. + 7
-      const int kr = tid >> 3, mc = (tid & 7) * 8;
-      const v8s v = *reinterpret_cast<const v8s*>(A + (size_t)(k0 + kr) * lda + m0 + mc);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) As[mc + e][kr] = (bf16)v[e];
-    }
-    if (TB == 1) {  // row n0 + r of the N x K storage, k0 + c .. + 7
-      const int r = tid >> 2, c = (tid & 3) * 8;
-      *reinterpret_cast<v8s*>(&Bs[r][c]) =
-          *reinterpret_cast<const v8s*>(B + (size_t)(n0 + r) * ldb + k0 + c);
-    } else {        // row k0 + kr of the K x N storage, columns n0 + nc .. + 7
-      const int kr = tid >> 3, nc = (tid & 7) * 8;
-      const v8s v = *reinterpret_cast<const v8s*>(B + (size_t)(k0 + kr) * ldb + n0 + nc);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) Bs[nc + e][kr] = (bf16)v[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 32; kk += 8) {
-      const v4s a = *reinterpret_cast<const v4s*>(&As[wr * 32 + (lane & 31)][kk + 4 * (lane >> 5)]);
-      const v4s b = *reinterpret_cast<const v4s*>(&Bs[wc * 32 + (lane & 31)][kk + 4 * (lane >> 5)]);
-      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, acc, 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  // lane holds column (lane % 32) and rows 8 (r / 4) + 4 (lane / 32) + r % 4
-  const int col = n0 + wc * 32 + (lane & 31);
-  const float bcol = EPI == 1 ? bias[col] : 0.f;
-  if (EPI == 3) C += (size_t)blockIdx.z * M * ldc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = m0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    const size_t o = (size_t)row * ldc + col;
-    if (EPI == 3) {
-      C[o] = acc[r];
-    } else if (EPI == 0) {
-      C[o] = acc[r] + (beta != 0.f ? beta * C[o] : 0.f);
-    } else {
-      float v = acc[r];
-      if (EPI == 1) {
-        v += bcol;
-        if (relu && !(v > 0.f)) v = 0.f;
-      } else if (!(gate[o] > 0.f)) {
-        v = 0.f;
+    for (int u = 0; u < 4; ++u) {
+      const size_t o = (size_t)(8 * u + (lane >> 3)) * ld + k;
+      if constexpr (F32) {
+        f[u][0] = *reinterpret_cast<const v4f*>(static_cast<const float*>(p) + o);
+        f[u][1] = *reinterpret_cast<const v4f*>(static_cast<const float*>(p) + o + 4);
+      } else {
+        v[u] = *reinterpret_cast<const v4u*>(static_cast<const bf16*>(p) + o);
       }
-      C[o] = v;
-      Cb[o] = to_bf16(v);
     }
+  }
+  __device__ __forceinline__ void store(char* tile) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if constexpr (F32) v[u] = round8(f[u][0], f[u][1]);
+      *reinterpret_cast<v4u*>(tile + (8 * u + (lane >> 3)) * kRowBytes + 16 * (lane & 7)) = v[u];
+    }
+  }
+};
+
+// The operand of two matrix instructions, 16 deep from 16 step on.
+__device__ __forceinline__ void operand(const char* tile, int step, v4s (&v)[2]) {
+  const int lane = threadIdx.x & 63;
+  const v4u w = *reinterpret_cast<const v4u*>(tile + (lane & 31) * kRowBytes + 32 * step + 16 * (lane >> 5));
+  halves(w, v[0], v[1]);
+}
+
+// acc += A[m0 .. m0 + 31][kb .. kb + ks) B[n0 .. n0 + 31][same]^T, kDeep at a
+// time with the next two such pieces on their way.
+template <bool F32A>
+__device__ __forceinline__ void product_nt(v16f& acc, const Job& j, int m0, int n0, int kb, char* own) {
+  const char* const ap = static_cast<const char*>(j.A) + ((size_t)m0 * j.K + kb) * (F32A ? 4 : 2);
+  const bf16* const bp = j.B + (size_t)n0 * j.K + kb;
+  const int n = (j.ks + kDeep - 1) / kDeep;
+  Rows<F32A> a[2];
+  Rows<false> b[2];
+  auto load = [&](int s, int c) {
+    if (c >= n) return;
+    const int valid = j.ks - c * kDeep < kDeep ? j.ks - c * kDeep : kDeep;
+    a[s].load(ap + (size_t)c * kDeep * (F32A ? 4 : 2), j.K, valid);
+    b[s].load(bp + (size_t)c * kDeep, j.K, valid);
+  };
+  auto multiply = [&](int s, int c) {
+    if (c >= n) return;
+    a[s].store(own);
+    b[s].store(own + kTileBytes);
+    load(s, c + 2);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {  // the second is missing where ks / 32 is odd
+      if (half == 1 && j.ks - c * kDeep < kDeep) continue;
+#pragma unroll
+      for (int i = 2 * half; i < 2 * half + 2; ++i) {
+        v4s x[2], y[2];
+        operand(own, i, x);
+        operand(own + kTileBytes, i, y);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x[e], y[e], acc, 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  load(0, 0);
+  load(1, 1);
+  for (int c = 0; c < n; c += 2) {
+    multiply(0, c);
+    multiply(1, c + 1);
   }
 }
 
-// The split-K sum: C = sum over z = 0, 1, ... of P[z] (M x N slices, leading
-// dimension N, added in that order), then GEMM epilogue EPI (0, 1 or 2).
+// acc[q] += A[m0 .. m0 + 31][kb .. kb + ks) B[same][n0 + 2 (lane mod 32) + q]
+__device__ __forceinline__ void product_nn(v16f (&acc)[2], const Job& j, int m0, int n0, int kb, char* own) {
+  const int lane = threadIdx.x & 63;
+  const bf16* const ap = static_cast<const bf16*>(j.A) + (size_t)m0 * j.K + kb;
+  const bf16* const bp = j.B + (size_t)(kb + 4 * (lane >> 5)) * j.N + n0 + 2 * (lane & 31);
+  const int n = (j.ks + kDeep - 1) / kDeep;
+  Rows<false> a[2];
+  uint32_t b[2][kDeep / 8][4];
+  auto load = [&](int s, int c) {
+    if (c >= n) return;
+    const int valid = j.ks - c * kDeep < kDeep ? j.ks - c * kDeep : kDeep;
+    a[s].load(ap + (size_t)c * kDeep, j.K, valid);
+#pragma unroll
+    for (int i = 0; i < kDeep / 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        b[s][i][e] = *reinterpret_cast<const uint32_t*>(
+            bp + (size_t)(c * kDeep + (8 * i < valid ? 8 * i : 0) + e) * j.N);
+  };
+  auto multiply = [&](int s, int c) {
+    if (c >= n) return;
+    a[s].store(own);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half == 1 && j.ks - c * kDeep < kDeep) continue;
+#pragma unroll
+      for (int i = 2 * half; i < 2 * half + 2; ++i) {
+        v4s x[2];
+        operand(own, i, x);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const uint32_t* const w = b[s][2 * i + e];
+          // the low halves are column q = 0, the high halves q = 1
+          const v4s b0 = as_v4s((w[0] & 0xffffu) | w[1] << 16, (w[2] & 0xffffu) | w[3] << 16);
+          const v4s b1 = as_v4s(w[0] >> 16 | (w[1] & 0xffff0000u), w[2] >> 16 | (w[3] & 0xffff0000u));
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x[e], b0, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x[e], b1, acc[1], 0, 0, 0);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    load(s, c + 2);
+  };
+  load(0, 0);
+  load(1, 1);
+  for (int c = 0; c < n; c += 2) {
+    multiply(0, c);
+    multiply(1, c + 1);
+  }
+}
+
+// Two consecutive rows of one column, with the column's bias and the entries of
+// gate or t; returns (y - t)^2 of kEpiError.
 template <int EPI>
-__global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ P, int S, int M,
-                                                     int N, float* __restrict__ C, int ldc,
-                                                     float beta, const float* __restrict__ bias,
-                                                     const float* __restrict__ gate,
-                                                     bf16* __restrict__ Cb, int relu) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)M * N) return;
-  const int row = (int)(i / N), col = (int)(i % N);
-  float v = P[i];
-  for (int z = 1; z < S; ++z) v += P[(size_t)z * M * N + i];
-  const size_t o = (size_t)row * ldc + col;
-  if (EPI == 0) {
-    C[o] = v + (beta != 0.f ? beta * C[o] : 0.f);
-    return;
-  }
-  if (EPI == 1) {
-    v += bias[col];
-    if (relu && !(v > 0.f)) v = 0.f;
-  } else if (!(gate[o] > 0.f)) {
-    v = 0.f;
-  }
-  C[o] = v;
-  Cb[o] = to_bf16(v);
-}
-
-// Mean squared error: dy = 2 (y - t) / count; per-block partial sums of
-// (y - t)^2 in float64 (fixed order), summed by the host.
-__global__ void mse_grad(const float* __restrict__ y, const float* __restrict__ t,
-                         float* __restrict__ dy, bf16* __restrict__ dyb, double* __restrict__ part,
-                         int64_t count) {
-  __shared__ double red[256];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double s = 0.0;
-  if (i < count) {
-    const float d = y[i] - t[i];
-    const float g = 2.f * d / (float)count;
-    dy[i] = g;
-    dyb[i] = to_bf16(g);
-    s = (double)d * (double)d;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// Column sums of a rows x cols float32 matrix (bias gradients), fixed order:
-// a workgroup owns 64 columns; its kColSlices waves each add the rows
-// congruent to the wave index (mod kColSlices), four loads in flight, and
-// wave 0 adds the slices' sums in slice order.
-constexpr int kColSlices = 16;
-__global__ __launch_bounds__(kColSlices * 64) void col_sum(const float* __restrict__ g,
-                                                           float* __restrict__ out, int rows,
-                                                           int cols) {
-  __shared__ float part[kColSlices][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (j < cols) {
-    int r = w;
-    for (; r + 3 * kColSlices < rows; r += 4 * kColSlices) {
-      const float v0 = g[(int64_t)r * cols + j];
-      const float v1 = g[(int64_t)(r + kColSlices) * cols + j];
-      const float v2 = g[(int64_t)(r + 2 * kColSlices) * cols + j];
-      const float v3 = g[(int64_t)(r + 3 * kColSlices) * cols + j];
-      s += v0;
-      s += v1;
-      s += v2;
-      s += v3;
+__device__ __forceinline__ double finish(const Job& j, int row, int col, float v0, float v1, float bcol,
+                                         float x0, float x1) {
+  const size_t o = (size_t)row * j.N + col;
+  float v[2] = {v0, v1};
+  const float x[2] = {x0, x1};
+  double err = 0.0;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const size_t oe = o + (size_t)e * j.N;
+    if constexpr (EPI == kEpiGate) {
+      if (!(x[e] > 0.f)) v[e] = 0.f;
+    } else if constexpr (EPI != kEpiStore) {
+      v[e] += bcol;
+      if (EPI == kEpiLayer && j.relu && !(v[e] > 0.f)) v[e] = 0.f;
     }
-    for (; r < rows; r += kColSlices) s += g[(int64_t)r * cols + j];
+    j.C[oe] = v[e];
+    if constexpr (EPI == kEpiError) {
+      const float d = v[e] - x[e];
+      err += (double)d * (double)d;
+      v[e] = 2.f * d / (float)((int64_t)j.M * j.N);
+      j.D[oe] = v[e];
+    }
   }
-  part[w][lane] = s;
+  if constexpr (EPI != kEpiStore) {
+    const uint32_t both = round2(v[0], v[1]);
+    j.Cb[o] = (bf16)both;
+    j.Cb[o + j.N] = (bf16)(both >> 16);
+    if (j.CbT) *reinterpret_cast<uint32_t*>(j.CbT + (size_t)col * j.M + row) = both;
+  }
+  return err;
+}
+
+// Workgroup `wg` of a product with S slices: NQ = 1: B stored N x K; NQ = 2:
+// K x N.  `sm`: kWaveBytes for each wave.  All waves of the workgroup call it.
+template <int NQ, int EPI, bool F32A, int S>
+__device__ __forceinline__ void product_s(const Job& j, int wg, char* sm) {
+  static_assert(16 * 2 * 64 * sizeof(float) <= kWaveBytes, "the sums reuse the operands' LDS");
+  constexpr int P = 16 / S;  // of a block's 16 rows per lane, those that a wave finishes
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int z = wave % S, r0 = P * z;
+  const int block = wg * ((int)(blockDim.x >> 6) / S) + wave / S;
+  const bool work = block < (j.M / 32) * (j.N / (32 * NQ));
+  int m0 = 0, n0 = 0;
+  if (work) block_at(j, block, 32 * NQ, m0, n0);
+  // acc[q][r]: column n0 + NQ (lane mod 32) + q, row m0 + 8 (r / 4) + 4 (lane / 32) + r % 4
+  const int col = n0 + NQ * (lane & 31), rbase = m0 + 4 * (lane >> 5);
+  auto row = [&](int i) { return rbase + 8 * ((r0 + i) >> 2) + ((r0 + i) & 3); };
+  v16f acc[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+  // What the epilogue reads is asked for before the product: between the
+  // epilogue's stores each load would be a round trip to memory of its own.
+  float bcol = 0.f, extra[NQ][P];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int i = 0; i < P; ++i) extra[q][i] = 0.f;
+  if (work) {
+    if (EPI == kEpiLayer || EPI == kEpiError) bcol = j.bias[col];
+    if (EPI == kEpiGate || EPI == kEpiError) {
+      const float* const src = EPI == kEpiGate ? j.gate : j.t;
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) extra[q][i] = src[(size_t)row(i) * j.N + col + q];
+    }
+    char* const own = sm + wave * kWaveBytes;
+    if constexpr (NQ == 1) product_nt<F32A>(acc[0], j, m0, n0, z * j.ks, own);
+    else product_nn(acc, j, m0, n0, z * j.ks, own);
+  }
+  float v[NQ][P];
+  if constexpr (S == 1) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int i = 0; i < P; ++i) v[q][i] = acc[q][i];
+  } else {  // the slices' sums, in order
+    constexpr int kStride = kWaveBytes / sizeof(float);  // from slice to slice
+    float* const mine = reinterpret_cast<float*>(sm) + wave * kStride + lane;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[(q * 16 + r) * 64] = acc[q][r];
+    __syncthreads();
+    const float* const src = mine - z * kStride + r0 * 64;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        v[q][i] = src[(q * 16 + i) * 64];
+#pragma unroll
+        for (int y = 1; y < S; ++y) v[q][i] += src[y * kStride + (q * 16 + i) * 64];
+      }
+  }
+  double err = 0.0;
+  if (work)
+#pragma unroll
+    for (int i = 0; i < P; i += 2)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        err += finish<EPI>(j, row(i), col + q, v[q][i], v[q][i + 1], bcol, extra[q][i], extra[q][i + 1]);
+  if constexpr (EPI == kEpiError) {
+    __syncthreads();
+    double* const red = reinterpret_cast<double*>(sm);
+    red[threadIdx.x] = err;
+    __syncthreads();
+    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) j.part[wg] = red[0];
+  }
+}
+
+template <int NQ, int EPI, bool F32A>
+__device__ __forceinline__ void product(const Job& j, int wg, char* sm) {
+  switch (j.S) {
+    case 1: return product_s<NQ, EPI, F32A, 1>(j, wg, sm);
+    case 2: return product_s<NQ, EPI, F32A, 2>(j, wg, sm);
+    case 4: return product_s<NQ, EPI, F32A, 4>(j, wg, sm);
+    default: return product_s<NQ, EPI, F32A, 8>(j, wg, sm);
+  }
+}
+
+// The transpose in bfloat16 of a 64 x 64 tile of x (rows x cols float32).
+__device__ __forceinline__ void transpose_tile(const float* x, bf16* xt, int rows, int cols, int tile,
+                                               float* sm) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int r0 = tile / (cols / 64) * 64, c0 = tile % (cols / 64) * 64;
+#pragma unroll 8
+  for (int r = w; r < 64; r += waves) sm[r * 65 + lane] = x[(size_t)(r0 + r) * cols + c0 + lane];
   __syncthreads();
-  if (w == 0 && j < cols) {
+#pragma unroll 8
+  for (int c = w; c < 64; c += waves)
+    xt[(size_t)(c0 + c) * rows + r0 + lane] = to_bf16(sm[lane * 65 + c]);
+}
+
+// Column sums of a rows x cols float32 matrix (bias gradients) for 64 columns,
+// in a fixed order: rows congruent mod kColSlices in order, then these sums.
+__device__ __forceinline__ void col_sums(const float* g, float* out, int rows, int cols, int group,
+                                         float* part) {
+  constexpr int P = kColSlices / kWaves;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int j = group * 64 + lane;
+  float s[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) s[p] = 0.f;
+  int r = w;
+  for (; r + 3 * kColSlices + kWaves * (P - 1) < rows; r += 4 * kColSlices) {
+    float v[4][P];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p) v[u][p] = g[(int64_t)(r + u * kColSlices + p * kWaves) * cols + j];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p) s[p] += v[u][p];
+  }
+  for (; r < rows; r += kColSlices)
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (r + p * kWaves < rows) s[p] += g[(int64_t)(r + p * kWaves) * cols + j];
+#pragma unroll
+  for (int p = 0; p < P; ++p) part[(w + p * kWaves) * 64 + lane] = s[p];
+  __syncthreads();
+  if (w == 0) {
     float t = 0.f;
 #pragma unroll
-    for (int k = 0; k < kColSlices; ++k) t += part[k][lane];
+    for (int k = 0; k < kColSlices; ++k) t += part[k * 64 + lane];
     out[j] = t;
   }
+}
+
+// A forward step; in a first step with XT given the workgroups after the
+// product's write the transpose of x.
+template <int EPI, bool F32A>
+__global__ __launch_bounds__(kThreads) void forward_step(Job j, const float* x, bf16* xt) {
+  extern __shared__ __align__(16) char sm[];
+  if ((int)blockIdx.x < j.wgs) product<1, EPI, F32A>(j, blockIdx.x, sm);
+  else transpose_tile(x, xt, j.M, j.K, blockIdx.x - j.wgs, reinterpret_cast<float*>(sm));
+}
+
+// The backward work of a layer: the step through it (dx, none in the first
+// layer: no workgroups), the weight gradient dw and the column sums of g; in
+// the first layer, whose workgroups come last, also the sum of the loss's
+// `parts` partial sums into host memory (kernels before it would wait for the
+// write's way over the bus).
+__global__ __launch_bounds__(kThreads) void backward_layer(Job dx, Job dw, const float* g, float* gb,
+                                                           int rows, int cols, const double* part,
+                                                           int parts, double* loss) {
+  extern __shared__ __align__(16) char sm[];
+  int b = blockIdx.x;
+  if (parts > 0 && b-- == 0) {
+    double* const red = reinterpret_cast<double*>(sm);
+    double v = 0.0;
+    for (int k = threadIdx.x; k < parts; k += kThreads) v += part[k];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = kThreads / 2; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *loss = red[0];
+    return;
+  }
+  if (b < dx.wgs) return product<2, kEpiGate, false>(dx, b, sm);
+  b -= dx.wgs;
+  if (b < dw.wgs) return product<1, kEpiStore, false>(dw, b, sm);
+  col_sums(g, gb, rows, cols, b - dw.wgs, reinterpret_cast<float*>(sm));
 }
 
 __global__ void cast_bf16(const float* __restrict__ x, bf16* __restrict__ y, int64_t count) {
@@ -275,12 +542,12 @@ struct drot_mlp {
   float* m1 = nullptr;
   float* m2 = nullptr;
   float* a[3] = {};  // activations (layer outputs)
-  bf16 *ab[3] = {}, *xb = nullptr;
+  bf16 *ab[3] = {}, *xb = nullptr;    // bfloat16 copies
+  bf16 *abt[3] = {}, *xbt = nullptr;  // and their transposes (of the last layer: none)
   float* d[3] = {};  // gradients with respect to the pre-activations
-  bf16 *db[3] = {};
-  double* part = nullptr;
-  double* part_host = nullptr;
-  float* ksplit = nullptr;  // split-K partial products (kSplitCap floats)
+  bf16 *db[3] = {}, *dbt[3] = {};
+  double* part = nullptr;  // the loss's partial sums
+  double* loss = nullptr;  // their sum, in pinned host memory
   int64_t step = 0;
 };
 
@@ -289,12 +556,8 @@ namespace {
 int64_t layer_in(const drot_mlp* n, int l) { return l == 0 ? n->in : n->hid; }
 int64_t layer_out(const drot_mlp* n, int l) { return l == 2 ? n->out : n->hid; }
 
-// Split-K workspace: S slices of M x N with S (M / 64) (N / 64) <= 256.
-constexpr size_t kSplitCap = (size_t)256 * 64 * 64;
-
-// K slices for an M x N x K product: while the grid has fewer than 256
-// workgroups (one per compute unit), halve the depth per workgroup, down to
-// 128 (four K steps of 32), up to 8 slices.
+// K slices of an M x N x K product: while 64 x 64 tiles would be fewer than 256
+// (one per compute unit), halve the depth of a slice, down to 128, up to 8.
 int split_k(int M, int N, int K) {
   const int grid = (M / 64) * (N / 64);
   int S = 1;
@@ -302,52 +565,25 @@ int split_k(int M, int N, int K) {
   return S;
 }
 
-// One GEMM (see gemm_bf16): epi 0 plain, 1 bias (+ ReLU), 2 ReLU gate; split
-// over K (partials in `ws`, then splitk_reduce) when the tile grid alone
-// would leave compute units idle.
-hipError_t gemm(const bf16* A, const bf16* B, float* C, int M, int N, int K, int lda, int ldb,
-                int ldc, int ta, int tb, float beta, hipStream_t s, float* ws, int epi = 0,
-                const float* bias = nullptr, const float* gate = nullptr, bf16* Cb = nullptr,
-                int relu = 0) {
-  const int S = ws ? split_k(M, N, K) : 1;
-  const dim3 grid(N / 64, M / 64, S), block(256);
-  float* dst = S > 1 ? ws : C;
-  const int ldd = S > 1 ? N : ldc;
-  const int e = S > 1 ? 3 : epi;
-  const int ks = K / S;
-#define DROT_GEMM(TA_, TB_, E_)                                                                \
-  hipLaunchKernelGGL((gemm_bf16<TA_, TB_, E_>), grid, block, 0, s, A, B, dst, M, N, K, lda, ldb, \
-                     ldd, beta, bias, gate, Cb, relu, ks)
-  switch (ta * 8 + tb * 4 + e) {
-    case 0: DROT_GEMM(0, 0, 0); break;
-    case 1: DROT_GEMM(0, 0, 1); break;
-    case 2: DROT_GEMM(0, 0, 2); break;
-    case 3: DROT_GEMM(0, 0, 3); break;
-    case 4: DROT_GEMM(0, 1, 0); break;
-    case 5: DROT_GEMM(0, 1, 1); break;
-    case 6: DROT_GEMM(0, 1, 2); break;
-    case 7: DROT_GEMM(0, 1, 3); break;
-    case 8: DROT_GEMM(1, 0, 0); break;
-    case 9: DROT_GEMM(1, 0, 1); break;
-    case 10: DROT_GEMM(1, 0, 2); break;
-    case 11: DROT_GEMM(1, 0, 3); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef DROT_GEMM
-  if (S == 1) return hipGetLastError();
-  const unsigned nb = (unsigned)(((int64_t)M * N + 255) / 256);
-#define DROT_RED(E_)                                                                          \
-  hipLaunchKernelGGL((splitk_reduce<E_>), dim3(nb), block, 0, s, ws, S, M, N, C, ldc, beta, bias, \
-                     gate, Cb, relu)
-  switch (epi) {
-    case 0: DROT_RED(0); break;
-    case 1: DROT_RED(1); break;
-    case 2: DROT_RED(2); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef DROT_RED
-  return hipGetLastError();
+// The product's shape, slices and workgroups of `waves` (at least S of them);
+// NQ as in product().
+Job make_job(const void* A, const bf16* B, float* C, int M, int N, int K, int NQ, int waves) {
+  Job j{};
+  j.A = A;
+  j.B = B;
+  j.C = C;
+  j.M = M;
+  j.N = N;
+  j.K = K;
+  j.S = split_k(M, N, K);
+  j.ks = K / j.S;
+  const int blocks = (M / 32) * (N / (32 * NQ)), per = waves / j.S;
+  j.wgs = (blocks + per - 1) / per;
+  return j;
 }
+
+// Waves of a forward step's workgroups: four fill more compute units.
+int forward_waves(int M, int N, int K) { return split_k(M, N, K) > 4 ? 8 : 4; }
 
 int check_batch(const drot_mlp* n, int batch) {
   if (!n) return mfail(DROT_EINVAL, "mlp is NULL");
@@ -357,46 +593,72 @@ int check_batch(const drot_mlp* n, int batch) {
   return DROT_OK;
 }
 
-int forward(drot_mlp* n, int B, const float* x, hipStream_t s) {
-  hipLaunchKernelGGL(cast_bf16, dim3(nblk((int64_t)B * n->in)), dim3(256), 0, s, x, n->xb,
-                     (int64_t)B * n->in);
-  MHIP(hipGetLastError());
-  const bf16* inp = n->xb;
+// y = f(x); with targets `t` also the error's gradient, the loss's partial
+// sums and the transposes that backward() needs.
+int forward(drot_mlp* n, int B, const float* x, float* y, const float* t, hipStream_t s) {
+  // x is read in 16-byte pieces where it lies so; else it is rounded first.
+  const bool direct = reinterpret_cast<uintptr_t>(x) % 16 == 0;
+  if (!direct) {
+    hipLaunchKernelGGL(cast_bf16, dim3(nblk((int64_t)B * n->in)), dim3(256), 0, s, x, n->xb,
+                       (int64_t)B * n->in);
+    MHIP(hipGetLastError());
+  }
   for (int l = 0; l < 3; ++l) {
     const int K = (int)layer_in(n, l), N = (int)layer_out(n, l);
-    // a_l = act(x_l W_l^T + b_l) and its bfloat16 copy, from the epilogue
-    MHIP(gemm(inp, n->wb + n->off_w[l], n->a[l], B, N, K, K, K, N, 0, 1, 0.f, s, n->ksplit, 1,
-              n->w + n->off_b[l], nullptr, n->ab[l], l < 2 ? 1 : 0));
-    inp = n->ab[l];
+    const void* in = l > 0 ? (const void*)n->ab[l - 1] : direct ? (const void*)x : (const void*)n->xb;
+    // a_l = act(x_l W_l^T + b_l)
+    const int waves = forward_waves(B, N, K);
+    Job j = make_job(in, n->wb + n->off_w[l], l == 2 ? y : n->a[l], B, N, K, 1, waves);
+    j.bias = n->w + n->off_b[l];
+    j.relu = l < 2;
+    if (l == 2 && t) {
+      j.t = t;
+      j.D = n->d[2];
+      j.Cb = n->db[2];
+      j.CbT = n->dbt[2];
+      j.part = n->part;
+    } else {
+      j.Cb = n->ab[l];
+      j.CbT = t ? n->abt[l] : nullptr;
+    }
+    const dim3 grid(j.wgs + (l == 0 && t ? (B / 64) * (K / 64) : 0)), block(64 * waves);
+    const size_t lds = (size_t)waves * kWaveBytes;
+    if (l == 0 && direct)
+      hipLaunchKernelGGL((forward_step<kEpiLayer, true>), grid, block, lds, s, j, x, n->xbt);
+    else if (l == 2 && t)
+      hipLaunchKernelGGL((forward_step<kEpiError, false>), grid, block, lds, s, j, x, n->xbt);
+    else
+      hipLaunchKernelGGL((forward_step<kEpiLayer, false>), grid, block, lds, s, j, x, n->xbt);
+    MHIP(hipGetLastError());
   }
   return DROT_OK;
 }
 
-// Gradients of the mean-squared error into n->g; loss to *loss (host).
-int backward(drot_mlp* n, int B, const float* t, double* loss, hipStream_t s) {
-  const int64_t cnt = (int64_t)B * n->out;
-  const unsigned nb = nblk(cnt);
-  hipLaunchKernelGGL(mse_grad, dim3(nb), dim3(256), 0, s, n->a[2], t, n->d[2], n->db[2], n->part, cnt);
-  MHIP(hipGetLastError());
+// Gradients of the mean-squared error into `grad`; loss to *loss (host).
+int backward(drot_mlp* n, int B, float* grad, double* loss, hipStream_t s) {
+  const int parts = make_job(nullptr, nullptr, nullptr, B, n->out, n->hid, 1,
+                             forward_waves(B, n->out, n->hid)).wgs;
   for (int l = 2; l >= 0; --l) {
     const int K = (int)layer_in(n, l), N = (int)layer_out(n, l);
-    const bf16* inp = l == 0 ? n->xb : n->ab[l - 1];
     // dW_l = dZ_l^T x_l  (N x K);  db_l = column sums of dZ_l
-    MHIP(gemm(n->db[l], inp, n->g + n->off_w[l], N, K, B, N, K, K, 1, 0, 0.f, s, n->ksplit));
-    hipLaunchKernelGGL(col_sum, dim3((N + 63) / 64), dim3(kColSlices * 64), 0, s, n->d[l],
-                       n->g + n->off_b[l], B, N);
-    MHIP(hipGetLastError());
+    Job dw = make_job(n->dbt[l], l == 0 ? n->xbt : n->abt[l - 1], grad + n->off_w[l], N, K, B, 1,
+                      kWaves);
+    Job dx{};
     if (l > 0) {
-      // dZ_{l-1} = (dZ_l W_l) * [a_{l-1} > 0] (B x K), the ReLU gate in the epilogue
-      MHIP(gemm(n->db[l], n->wb + n->off_w[l], n->d[l - 1], B, K, N, N, K, K, 0, 0, 0.f, s,
-                n->ksplit, 2, nullptr, n->a[l - 1], n->db[l - 1]));
+      // dZ_{l-1} = (dZ_l W_l) * [a_{l-1} > 0] (B x K)
+      dx = make_job(n->db[l], n->wb + n->off_w[l], n->d[l - 1], B, K, N, 2, kWaves);
+      dx.gate = n->a[l - 1];
+      dx.Cb = n->db[l - 1];
+      dx.CbT = n->dbt[l - 1];
     }
+    const int sums = l == 0 ? parts : 0;
+    hipLaunchKernelGGL(backward_layer, dim3(dx.wgs + dw.wgs + N / 64 + (sums > 0)), dim3(kThreads),
+                       (size_t)kWaves * kWaveBytes, s, dx, dw, n->d[l], grad + n->off_b[l], B, N,
+                       n->part, sums, n->loss);
+    MHIP(hipGetLastError());
   }
-  MHIP(hipMemcpyAsync(n->part_host, n->part, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
   MHIP(hipStreamSynchronize(s));
-  double acc = 0.0;
-  for (unsigned k = 0; k < nb; ++k) acc += n->part_host[k];
-  if (loss) *loss = acc / (double)cnt;
+  if (loss) *loss = *n->loss / (double)((int64_t)B * n->out);
   return DROT_OK;
 }
 
@@ -455,16 +717,17 @@ int drot_mlp_create(drot_mlp** out, int device, int in, int hidden, int outd, in
             hipMalloc(&n->m1, sizeof(float) * o) == hipSuccess &&
             hipMalloc(&n->m2, sizeof(float) * o) == hipSuccess &&
             hipMalloc(&n->xb, sizeof(bf16) * (size_t)max_batch * in) == hipSuccess &&
-            hipMalloc(&n->part, sizeof(double) * nblk((int64_t)max_batch * outd)) == hipSuccess &&
-            hipMalloc(&n->ksplit, sizeof(float) * kSplitCap) == hipSuccess &&
-            hipHostMalloc((void**)&n->part_host, sizeof(double) * nblk((int64_t)max_batch * outd),
-                          hipHostMallocDefault) == hipSuccess;
+            hipMalloc(&n->xbt, sizeof(bf16) * (size_t)max_batch * in) == hipSuccess &&
+            hipMalloc(&n->part, sizeof(double) * (size_t)(max_batch / 32) * (outd / 32)) == hipSuccess &&
+            hipHostMalloc((void**)&n->loss, sizeof(double), hipHostMallocDefault) == hipSuccess;
   for (int l = 0; l < 3 && ok; ++l) {
     const size_t c = (size_t)max_batch * layer_out(n, l);
     ok = hipMalloc(&n->a[l], sizeof(float) * c) == hipSuccess &&
          hipMalloc(&n->ab[l], sizeof(bf16) * c) == hipSuccess &&
+         (l == 2 || hipMalloc(&n->abt[l], sizeof(bf16) * c) == hipSuccess) &&
          hipMalloc(&n->d[l], sizeof(float) * c) == hipSuccess &&
-         hipMalloc(&n->db[l], sizeof(bf16) * c) == hipSuccess;
+         hipMalloc(&n->db[l], sizeof(bf16) * c) == hipSuccess &&
+         hipMalloc(&n->dbt[l], sizeof(bf16) * c) == hipSuccess;
   }
   if (!ok) {
     (void)hipGetLastError();
@@ -483,15 +746,15 @@ int drot_mlp_destroy(drot_mlp* n) {
   if (!n) return DROT_OK;
   (void)hipSetDevice(n->device);
   (void)hipDeviceSynchronize();
-  void* bufs[] = {n->w, n->wb, n->g, n->m1, n->m2, n->xb, n->part, n->ksplit};
+  void* bufs[] = {n->w, n->wb, n->g, n->m1, n->m2, n->xb, n->xbt, n->part};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   for (int l = 0; l < 3; ++l) {
-    void* lb[] = {n->a[l], n->ab[l], n->d[l], n->db[l]};
+    void* lb[] = {n->a[l], n->ab[l], n->abt[l], n->d[l], n->db[l], n->dbt[l]};
     for (void* b : lb)
       if (b) (void)hipFree(b);
   }
-  if (n->part_host) (void)hipHostFree(n->part_host);
+  if (n->loss) (void)hipHostFree(n->loss);
   delete n;
   return DROT_OK;
 }
@@ -528,9 +791,7 @@ int drot_mlp_forward(drot_mlp* n, int batch, const float* x, float* y, void* str
   if (rc) return rc;
   if (!x || !y) return mfail(DROT_EINVAL, "NULL argument");
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = forward(n, batch, x, s))) return rc;
-  MHIP(hipMemcpyAsync(y, n->a[2], sizeof(float) * (size_t)batch * n->out, hipMemcpyDeviceToDevice, s));
-  return DROT_OK;
+  return forward(n, batch, x, y, nullptr, s);
 }
 
 int drot_mlp_gradients(drot_mlp* n, int batch, const float* x, const float* t, float* grad,
@@ -539,10 +800,8 @@ int drot_mlp_gradients(drot_mlp* n, int batch, const float* x, const float* t, f
   if (rc) return rc;
   if (!x || !t) return mfail(DROT_EINVAL, "NULL argument");
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = forward(n, batch, x, s))) return rc;
-  if ((rc = backward(n, batch, t, loss, s))) return rc;
-  if (grad) MHIP(hipMemcpyAsync(grad, n->g, sizeof(float) * n->n_params, hipMemcpyDeviceToDevice, s));
-  return DROT_OK;
+  if ((rc = forward(n, batch, x, n->a[2], t, s))) return rc;
+  return backward(n, batch, grad ? grad : n->g, loss, s);
 }
 
 }  // extern "C"

@@ -177,3 +177,36 @@ def test_adam_ten_steps_on_given_gradients():
     with pytest.raises(Exception):
         net.apply_gradients(torch.zeros(n - 1, device="cuda"), lr)
     net.close()
+
+
+# Depth slices of each count (1, 2, 4, 8), odd numbers of 32 in a slice, and x
+# at an address that 16-byte loads cannot use.
+@pytest.mark.parametrize("dims,batch", [((320, 64, 192), 64), ((1024, 192, 576), 64),
+                                        ((2048, 1024, 1088), 512)])
+def test_slices_and_unaligned_input(dims, batch):
+    import torch
+    rng = np.random.default_rng([24, dims[0], batch])
+    net = _net(dims, batch, seed=3)
+    theta = net.get_weights().astype(np.float64)
+    x = rng.standard_normal((batch, dims[0])).astype(np.float32)
+    t = torch.tensor(rng.standard_normal((batch, dims[2])).astype(np.float32), device="cuda")
+    flat = torch.empty(x.size + 1, dtype=torch.float32, device="cuda")
+    odd = flat[1:].view(batch, dims[0])
+    odd.copy_(torch.tensor(x, device="cuda"))
+    assert odd.data_ptr() % 16 == 4
+    xd = odd.clone()
+    y = net.forward(xd)
+    assert torch.equal(y, net.forward(odd))
+    (la, ga), (lb, gb) = net.gradients(xd, t), net.gradients(odd, t)
+    assert la == lb and torch.equal(ga, gb)
+    y_ref = mlp_ref.forward(theta, x, dims)
+    loss_ref, g_ref = mlp_ref.loss_and_grad(theta, x, t.cpu().numpy(), dims)
+    g = ga.cpu().numpy().astype(np.float64)
+    assert np.abs(y.cpu().numpy() - y_ref).max() <= 2e-2 * np.abs(y_ref).max()
+    assert abs(la - loss_ref) <= 1e-2 * loss_ref
+    assert float(g @ g_ref / np.linalg.norm(g) / np.linalg.norm(g_ref)) >= 0.9999
+    b = _blocks(dims)
+    for k in range(6):
+        gk, rk = g[b[k]:b[k + 1]], g_ref[b[k]:b[k + 1]]
+        assert np.abs(gk - rk).max() <= 2e-2 * np.abs(rk).max() + 1e-12, k
+    net.close()
