@@ -135,7 +135,8 @@ void drop_graph(drot_ctx* c) {
 constexpr size_t kResTeamOff = 256, kResMsgOff = 4096;
 static_assert(kResTeamOff + sizeof(ResTeam) <= kResMsgOff, "team record");
 size_t res_msg_bytes(int dtype, int rpw, int tiles) {
-  return sizeof(unsigned long long) * kResPhases * (size_t)tiles * res_msg_words(dtype, rpw);
+  return sizeof(unsigned long long) * (size_t)tiles *
+         (kResPhases * (size_t)res_msg_words(dtype, rpw) + res_saved_words());
 }
 
 // Tiles of an m x n problem with `rpw` rows per wave; false if they are too

@@ -169,15 +169,18 @@ constexpr int kResBlock = kResWaves * kWave;
 constexpr int kResPhases = 4;  // message buffers per workgroup
 constexpr int kResMinIters = 8;  // shorter runs go to sweep + aux
 constexpr int kResRpw[] = {4, 8, 16, 24, 32};
+constexpr int kResSaves[] = {32, 128, 256};  // iterations between saved states
 constexpr int kResMaxTiles = 256, kResMaxSide = 128;  // workgroups of a team, tiles of a side
 struct ResTeam {
   SweepArgs a;
   int R, S;              // tiles down and across
   int vec_c, vec_x;      // C, X readable as 16-byte chunks
-  unsigned long long* xch;  // [kResPhases][R S] messages of res_msg_words words
+  unsigned long long* xch;  // [kResPhases][R S] messages of res_msg_words words, then the
+                            // saved vectors, res_saved_words() for each of the R S
   uint32_t* seq;         // steps taken since the buffers were cleared
 };
 constexpr int res_cols(int dtype) { return kWave * (dtype == 0 ? 4 : 2); }
+constexpr int res_saved_words() { return 2 * kResBlock; }
 constexpr int res_msg_words(int dtype, int rpw) {
   return kResWaves * rpw / (dtype == 0 ? 2 : 1) + 128 + 16;
 }

@@ -33,9 +33,14 @@
 // follow from this exchange, so it trails: workgroup 0 tests iteration k
 // while it waits for the words of iteration k + 2, and announces a stop in
 // its next message.
-// By then X has moved on; the workgroups load the plan as it was when the
-// launch began and repeat the iterations up to the stopping one (everything
-// is deterministic), so the result is exactly X at the stopping iteration.
+// By then X has moved on; the workgroups load the last saved state and repeat
+// the iterations up to the stopping one (everything is deterministic), so the
+// result is exactly X at the stopping iteration.  A state is saved when two
+// exchanges of scalar words have told everybody that no test up to it ended
+// the solve: after kResSaves[1] iterations of the solve (kResSaves[0] beyond 32
+// tile rows, where an iteration costs more than half of the sweeps'), then
+// each time they have doubled, then every kResSaves[2].  A save takes about two
+// iterations' time and the write of X, 8 us at 517 x 483 and 25 at 4096 x 4096.
 //
 // What bounds it: up to about 2000 x 2000 latency.  In 10.6 k clocks at
 // 517 x 483, 3.0 go to the sweep and its reductions (two waves share a SIMD),
@@ -195,6 +200,7 @@ struct ResShared {
   double* trace;
   double ctl;                 // workgroup 0: stop iteration to announce
   int trace_mask;
+  double base[3];             // cphi, cpsi, alpha of the saved state
   int rec_k, rec_status, rec_done;
   int stop_at, dead;
 };
@@ -444,9 +450,81 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     sh.rec_k = sh.rec_done = sh.rec_status = 0;
   }
 
+  // The state is saved between segments of the launch (kResSaves says when),
+  // except where X's way to memory leads through LDS that holds rho C.
+  const bool saves = CL == 0 || (uni(tm->vec_x) && n % VEC == 0);
+  const int seg0 = R > 32 ? kResSaves[0] : kResSaves[1];
   bool replay = false;
-  int k = 0;
-  for (;;) {  // the iterations, and after a stop once more up to it
+  int base = 0, k = 0;  // iterations of this launch in the saved state, and done
+  auto saved = [&]() {  // this thread's accs[] and shift in the saved state
+    return reinterpret_cast<double*>((uintptr_t)(xch + kResPhases * phase)) +
+           2 * (b * kResBlock + fresh_lane(tid));
+  };
+  // X to memory.
+  auto store_x = [&]() {
+    const ResTeam* const t3 = fresh(tm);
+    const int ws0 = fresh(wr0), nvs = fresh_lane(nv);
+    T* const X = uni(static_cast<T*>(t3->a.X));
+    const int64_t ldx = uni(t3->a.g.ldx);
+    const bool vec = uni(t3->vec_x) != 0;
+    if (vec && nvs == VEC) {
+#pragma unroll
+      for (int r = 0; r < RPW; ++r)
+        if (ws0 + r < m) store_chunk<T, VEC, false>(X + (int64_t)(ws0 + r) * ldx + jl, xr[r]);
+    }
+    if (!vec || n % VEC != 0) {  // the other chunks, element by element
+      const int ne = vec && nvs == VEC ? 0 : nvs;
+#pragma unroll
+      for (int g = 0; g < RPW / SR; ++g) {
+#pragma unroll
+        for (int u = 0; u < SR; ++u) store_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
+#pragma unroll 1
+        for (int u = 0; u < SR; ++u) {
+          const int i = ws0 + g * SR + u;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e)
+            if (i < m && e < ne) X[i * ldx + jl + e] = stage[u * W + e];
+        }
+      }
+    }
+  };
+  // An exchange of the scalar words alone, with workgroup 0's stop word.
+  // Workgroup 0 reads the sums of iteration k too.
+  auto exchange = [&]() {
+    const Msg cur = xch + (seq & 3) * phase;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const Msg dst = word_at(cur, 8 * b * MSG);
+    const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
+    if (wave == kResWaves - 1) {
+      if (lane < kRwCount) {
+        const double* src = &sh.esum[lane & 1][lane >= kRwS2 ? 4 : 0];
+        double v = lane >= kRwR2 ? (src[0] + src[1]) + (src[2] + src[3]) : 0.0;
+        if (lane == kRwCtl) v = sh.ctl;
+        st_word(dst, 8 * (WC + WR + lane), pack_double(v));
+        st_word(clr, 8 * (WC + WR + lane), kSent);
+      }
+    } else if (tid < WC + WR) {
+      st_word(clr, 8 * tid, kSent);
+    }
+    // Wave 7 waits for everybody's word, as in an iteration: whoever has it
+    // is done with the message before, which the next step clears.
+    if (wave == 2 || wave == 7 || (b == 0 && (wave == 3 || wave == 4))) {
+      const int xl = lane >> xsh;
+      const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
+      const uint32_t ox = 8 * (WC + WR + xw + (lane & xsh)) + (nx > 0 ? xl * xstep : 0);
+      const int sx = xstep << (6 - xsh);
+      u64 wx[4];
+      double v = 0.0;
+      res_load4(wx, cur, ox, sx, nx);
+      if (!res_sum4(wx, cur, ox, sx, nx, v)) sh.dead = 1;
+      if (wave == 3 || wave == 4) res_keep(sh.mon[seq & 1], wave, lane, v);
+      else if (wave == 2 && lane == 0) sh.stop_at = (int)v;
+    }
+    __syncthreads();
+    ++seq;
+  };
+  for (;;) {  // from the saved state on: the iterations, and after a stop once more up to it
     const ResTeam* const t2 = fresh(tm);
     const int wl0 = fresh(wr0), nvl = fresh_lane(nv);
     {
@@ -547,19 +625,39 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         }
       }
     }
-    accs[tid] = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
-    if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : (T)0;
-    if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : (T)0;
+    if (base == 0) {
+      accs[tid] = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
+      if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : (T)0;
+      if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : (T)0;
+      if (tid == 0) {
+        sh.base[0] = st->cphi;
+        sh.base[1] = st->cpsi;
+        sh.base[2] = st->alpha;
+      }
+    } else {
+      const double* const v = saved();
+      accs[tid] = v[0];
+      if (is_row) rowsh[tid] = (T)v[1];
+      if (is_col) colsh[cc0] = (T)v[1];
+    }
     if (tid == 0) {
-      sh.bc[0][0] = st->cphi;
-      sh.bc[0][1] = st->cpsi;
-      sh.bc[0][2] = st->alpha;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sh.bc[base & 3][q] = sh.base[q];
       sh.stop_at = 0;
     }
     if (tid < 2 * kResWaves) sh.esum[tid & 1][tid >> 1] = 0.0;
     __syncthreads();
 
-    for (k = 0; k < limit;) {  // sweep iteration k + 1, exchange, steps 5-8
+    k = base;
+    for (;;) {  // segments
+    const int start = k;
+    int end = limit;
+    if (saves && !replay) {
+      const int64_t total = uni(sh.sv.iter) + k;
+      const int len = total < seg0 ? seg0 : total < kResSaves[2] ? (int)total : kResSaves[2];
+      if (limit - k > len) end = k + len;
+    }
+    while (k < end) {  // sweep iteration k + 1, exchange, steps 5-8
       const Msg cur = xch + (seq & 3) * phase;
       // Step 4 on the held entries, with the row and column sums of step 5
       // and the stopping-test sums.  A lane's float32 sums run over at most
@@ -680,8 +778,9 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       __syncthreads();  // `buf` changes its use
 
       // While the peers' words are on their way: the test of iteration k - 1.
-      if (b == 0 && wave == 6 && !replay && k >= 1)
-        res_test(sh, sh.mon[(seq - 1) & 1], k - 1, lane);
+      // (A segment begins with both iterations before it tested.)
+      if (b == 0 && wave == 6 && !replay && k > start)
+        res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
 
       // Read the peers' words.  All loads of a batch are in flight together,
       // and so are the repeats of those that came too early.
@@ -786,7 +885,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           e[0] = res * res;
           e[1] = mg * dual;
           // phi~ and psi~ in full, of what may be the last iteration
-          if (k + 1 == limit) {
+          if (k + 1 == end) {
             const ResTeam* const t4 = fresh(tm);
             if (is_row && tj == 0) t4->a.phi64[gid] = dual;
             if (!is_row && ti == 0) t4->a.psi64[gid] = dual;
@@ -810,46 +909,31 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       ++k;
       if (uni(sh.stop_at) > 0) break;
     }
-    if (uni(sh.dead)) break;
-    if (!replay && uni(sh.stop_at) == 0) {
-      // The closing exchange: the scalar words alone, for the last two tests.
-      const Msg cur = xch + (seq & 3) * phase;
-      if (b == 0 && wave == 6)
-        res_test(sh, sh.mon[(seq - 1) & 1], k - 1, lane);
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      const Msg dst = word_at(cur, 8 * b * MSG);
-      const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
-      if (wave == kResWaves - 1) {
-        if (lane < kRwCount) {
-          const double* src = &sh.esum[lane & 1][lane >= kRwS2 ? 4 : 0];
-          double v = lane >= kRwR2 ? (src[0] + src[1]) + (src[2] + src[3]) : 0.0;
-          if (lane == kRwCtl) v = sh.ctl;
-          st_word(dst, 8 * (WC + WR + lane), pack_double(v));
-          st_word(clr, 8 * (WC + WR + lane), kSent);
-        }
-      } else if (tid < WC + WR) {
-        st_word(clr, 8 * tid, kSent);
-      }
-      if (wave == 2 || (b == 0 && (wave == 3 || wave == 4))) {
-        const int xl = lane >> xsh;
-        const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
-        const uint32_t ox = 8 * (WC + WR + xw + (lane & xsh)) + (nx > 0 ? xl * xstep : 0);
-        const int sx = xstep << (6 - xsh);
-        u64 wx[4];
-        double v = 0.0;
-        res_load4(wx, cur, ox, sx, nx);
-        if (!res_sum4(wx, cur, ox, sx, nx, v)) sh.dead = 1;
-        if (wave != 2) res_keep(sh.mon[seq & 1], wave, lane, v);
-        else if (lane == 0) sh.stop_at = (int)v;
-      }
-      __syncthreads();
-      if (b == 0 && wave == 6)
-        res_test(sh, sh.mon[seq & 1], k, lane);
-      ++seq;
+    if (uni(sh.dead) || replay || uni(sh.stop_at) > 0) break;
+    // The end of a segment: an exchange for the last two tests.
+    if (b == 0 && wave == 6)
+      res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
+    exchange();
+    if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
+    if (b == 0 && wave == 6)
+      res_test(sh, sh.mon[(seq - 1) & 1], k, lane);
+    if (k == limit) break;
+    // Another one for the word that the launch goes on, and the state is saved.
+    __syncthreads();  // every thread has read stop_at
+    exchange();
+    if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
+    store_x();
+    double* const v = saved();
+    v[0] = accs[tid];
+    v[1] = is_row ? (double)rowsh[tid] : is_col ? (double)colsh[cc0] : 0.0;
+    if (tid == 0)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sh.base[q] = sh.bc[k & 3][q];
+    base = k;
     }
-    if (uni(sh.dead) || replay || uni(sh.stop_at) == 0) break;
-    limit = uni(sh.stop_at);
+    const int stop = uni(sh.stop_at);
+    if (uni(sh.dead) || replay || stop == 0 || stop == k) break;
+    limit = stop;
     replay = true;
     __syncthreads();  // every thread has read stop_at
   }
@@ -862,33 +946,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   }
 
   // Write back X, the vectors and the state.
+  store_x();
   const ResTeam* const t3 = fresh(tm);
-  const int ws0 = fresh(wr0), nvs = fresh_lane(nv);
-  {
-    T* const X = uni(static_cast<T*>(t3->a.X));
-    const int64_t ldx = uni(t3->a.g.ldx);
-    const bool vec = uni(t3->vec_x) != 0;
-    if (vec && nvs == VEC) {
-#pragma unroll
-      for (int r = 0; r < RPW; ++r)
-        if (ws0 + r < m) store_chunk<T, VEC, false>(X + (int64_t)(ws0 + r) * ldx + jl, xr[r]);
-    }
-    if (!vec || n % VEC != 0) {  // the other chunks, element by element
-      const int ne = vec && nvs == VEC ? 0 : nvs;
-#pragma unroll
-      for (int g = 0; g < RPW / SR; ++g) {
-#pragma unroll
-        for (int u = 0; u < SR; ++u) store_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
-#pragma unroll 1
-        for (int u = 0; u < SR; ++u) {
-          const int i = ws0 + g * SR + u;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e)
-            if (i < m && e < ne) X[i * ldx + jl + e] = stage[u * W + e];
-        }
-      }
-    }
-  }
   if (own_r && tj == 0) {
     t3->a.a[gid] = accs[tid];
     static_cast<T*>(t3->a.phiT)[gid] = rowsh[tid];

@@ -164,3 +164,38 @@ def test_batch_stops_each_problem_on_its_own(ctx):
     ("float32", 9, 530), ("float32", 12, 16640), ("float64", 32, 513), ("float64", 600, 26)])
 def test_trajectory_few_rows_or_columns(ctx, dtype, m, n):
     test_trajectory(ctx, dtype, m, n)
+
+
+# Stops on both sides of saved states (after 32 iterations beyond 32 tile rows,
+# else 128; doubling; then every 256), against runs of that many iterations.
+@pytest.mark.parametrize("dtype,m,n", [("float32", 300, 301), ("float32", 1100, 40),
+                                       ("float64", 257, 300), ("float32", 3300, 3200),
+                                       ("float32", 3300, 3203)])
+def test_stop_after_saved_states(ctx, dtype, m, n):
+    import torch
+    from paper_2110_11738_amd import drot
+    inst = _instance(43, m, n, dtype)
+    args = _inputs(inst, dtype)
+    K = 620
+
+    def solve(tol, max_iter):
+        X, res, mu, nu = drot.solve(*args, inst.rho, tol=tol, max_iter=max_iter, ctx=ctx)
+        torch.cuda.synchronize()
+        return res, (X, mu, nu)
+
+    solve(0.0, K)
+    test = ctx.trace(1, K)[:, 5]
+    low = [k + 1 for k in range(K) if k == 0 or test[k] < test[:k].min()]  # a tolerance stops there
+    picks = {low[0], low[-1]}
+    for save in (32, 64, 128, 256, 512):
+        picks |= {k for k in low if abs(k - save) <= 1}
+        picks |= {max([k for k in low if k <= save + 40], default=low[0])}
+    for k in sorted(picks):
+        if k < 8:
+            continue  # solve(0, k) would be single iterations, sweep + aux
+        a, x = solve(float(test[k - 1]), K)
+        b, y = solve(0.0, k)
+        print(f"[resident] {m}x{n} stop at {k}: {a['iters']} {a['status']}", flush=True)
+        assert (a["iters"], a["status"], a["path"]) == (k, 0, 0) and b["iters"] == k
+        for u, v in zip(x, y):
+            assert torch.equal(u, v)
