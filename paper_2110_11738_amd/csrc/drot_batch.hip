@@ -43,6 +43,7 @@ int drot_internal_batch_chunks(const drot_ctx* c, int key);
 void drot_internal_set_batch_chunks(drot_ctx* c, int key, int chunks);
 bool drot_internal_resident_tiles(const drot_ctx* c, int dtype, int64_t m, int64_t n, int rpw,
                                   int* R, int* S);
+void* drot_internal_staging(drot_ctx* c, size_t bytes);
 int drot_internal_resident_cap(const drot_ctx* c);
 size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles);
 bool drot_internal_resident_stream(hipStream_t s, int blocks);
@@ -150,6 +151,8 @@ struct BatchRun {
   size_t off_team = 0, off_map = 0, off_seq = 0, off_msg = 0;
   ResTeam* h_team = nullptr;
   uint2* h_map = nullptr;
+  void* own_host = nullptr;  // their memory, where it is not the context's
+  bool waited = false;       // nothing of this run is under way any more
   int64_t max_map = 0;
   std::vector<char> fits;  // problem fits the chip
   struct Launch {
@@ -163,14 +166,11 @@ struct BatchRun {
   DevState& hst(int b) { return *reinterpret_cast<DevState*>(h_st + SS * b); }
 
   ~BatchRun() {
+    // A run that ended early may have copies from its staging memory under way.
+    if (base && !waited) (void)hipDeviceSynchronize();
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (cap) (void)hipStreamDestroy(cap);
-    if (h_args) (void)hipHostFree(h_args);
-    if (h_sw) (void)hipHostFree(h_sw);
-    if (h_aw) (void)hipHostFree(h_aw);
-    if (h_st) (void)hipHostFree(h_st);
-    if (h_team) (void)hipHostFree(h_team);
-    if (h_map) (void)hipHostFree(h_map);
+    if (own_host) (void)hipHostFree(own_host);
   }
 
   // Layout and staging.  stream_mode: -1 chooses from the batch's footprint;
@@ -294,15 +294,27 @@ struct BatchRun {
     int rc = drot_internal_ctx_prepare(c, &ws, total);
     if (rc) return rc;
     base = static_cast<char*>(ws);
-    BHIP(hipHostMalloc((void**)&h_args, sizeof(SweepArgs) * count, hipHostMallocDefault));
-    BHIP(hipHostMalloc((void**)&h_sw, sizeof(uint2) * std::max<int64_t>(1, max_sweep), hipHostMallocDefault));
-    BHIP(hipHostMalloc((void**)&h_aw, sizeof(uint2) * std::max<int64_t>(1, max_aux), hipHostMallocDefault));
-    BHIP(hipHostMalloc((void**)&h_st, SS * count, hipHostMallocDefault));
-    if (res) {
-      BHIP(hipHostMalloc((void**)&h_team, sizeof(ResTeam) * count, hipHostMallocDefault));
-      BHIP(hipHostMalloc((void**)&h_map, sizeof(uint2) * max_map, hipHostMallocDefault));
+    // One piece of pinned memory for everything that is staged: the context's,
+    // which stays from call to call (six allocations, their release and a
+    // stream took 0.35 ms of every call), or one of this run where it is larger
+    // than the context keeps.
+    const size_t part[6] = {up(sizeof(SweepArgs) * count), up(sizeof(uint2) * (size_t)max_sweep),
+                            up(sizeof(uint2) * (size_t)max_aux), up(SS * count),
+                            res ? up(sizeof(ResTeam) * count) : 0,
+                            res ? up(sizeof(uint2) * (size_t)max_map) : 0};
+    size_t host = 0;
+    for (size_t b : part) host += b;
+    char* h = static_cast<char*>(drot_internal_staging(c, host));
+    if (!h) {
+      BHIP(hipHostMalloc(&own_host, host, hipHostMallocDefault));
+      h = static_cast<char*>(own_host);
     }
-    BHIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+    h_args = reinterpret_cast<SweepArgs*>(h);
+    h_sw = reinterpret_cast<uint2*>(h += part[0]);
+    h_aw = reinterpret_cast<uint2*>(h += part[1]);
+    h_st = h += part[2];
+    h_team = reinterpret_cast<ResTeam*>(h += part[3]);
+    h_map = reinterpret_cast<uint2*>(h += part[4]);
     for (int b = 0; b < count; ++b) {
       const drot_problem& P = probs[b];
       SweepArgs& a = h_args[b];
@@ -407,6 +419,7 @@ struct BatchRun {
       if (rc) return rc;
       BHIP(hipStreamSynchronize(s));
       hipGraph_t graph = nullptr;
+      if (!cap) BHIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
       BHIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
       hipError_t le = hipSuccess;
       for (int k = 0; k < G && le == hipSuccess; ++k)
@@ -571,6 +584,7 @@ struct BatchRun {
     BHIP(launch_batch_step(dtype, kFinal, tile, d_args(), d_sw(), n_sw, d_aw(), n_aw, count, s));
     BHIP(hipMemcpyAsync(h_st, base, SS * count, hipMemcpyDeviceToHost, s));
     BHIP(hipStreamSynchronize(s));
+    waited = true;
     return DROT_OK;
   }
 

@@ -89,6 +89,8 @@ struct drot_ctx {
   int res_rpw = 0, cus = 0;
   void* res_ws = nullptr;
   ResTeam* team_host = nullptr;  // pinned
+  void* staging = nullptr;       // pinned, of the batched solver
+  size_t staging_bytes = 0;
 
   // Small problems iterate in one workgroup (small_kernel) instead of
   // sweep + aux launches.
@@ -648,6 +650,26 @@ hipError_t drot_internal_resident_launch(int dtype, int rpw, const ResTeam* team
   return launch_resident(dtype, rpw, true, teams, map, blocks, iters, s);
 }
 
+// Pinned memory of the context for what a batched solve stages, kept from
+// call to call up to kStagingMax; null beyond that.  A call has waited for its
+// copies when it returns, so the next one finds it free.
+void* drot_internal_staging(drot_ctx* c, size_t bytes) {
+  constexpr size_t kStagingMax = (size_t)16 << 20;
+  if (bytes > kStagingMax) return nullptr;
+  if (bytes > c->staging_bytes) {
+    if (c->staging) (void)hipHostFree(c->staging);
+    c->staging = nullptr;
+    c->staging_bytes = 0;
+    if (hipHostMalloc(&c->staging, bytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      c->staging = nullptr;
+      return nullptr;
+    }
+    c->staging_bytes = bytes;
+  }
+  return c->staging;
+}
+
 // Make the context's workspace at least `bytes` large for a batched solve.
 // The single-problem binding lives in the same workspace and is released.
 int drot_internal_ctx_prepare(drot_ctx* c, void** ws, size_t bytes) {
@@ -738,6 +760,7 @@ int drot_ctx_destroy(drot_ctx* c) {
   if (c->res_ws) (void)hipFree(c->res_ws);
   if (c->st_host) (void)hipHostFree(c->st_host);
   if (c->team_host) (void)hipHostFree(c->team_host);
+  if (c->staging) (void)hipHostFree(c->staging);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   delete c;
   return DROT_OK;

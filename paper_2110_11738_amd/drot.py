@@ -58,7 +58,10 @@ class Result(ctypes.Structure):
                 ("sweep_timed", ctypes.c_int64), ("cost_scale", ctypes.c_double)]
 
     def as_dict(self) -> dict:
-        return {k: getattr(self, k) for k, _ in self._fields_ if k != "reserved"}
+        return {k: getattr(self, k) for k in _RESULT_FIELDS}
+
+
+_RESULT_FIELDS = tuple(k for k, _ in Result._fields_ if k != "reserved")
 
 
 class Cost(ctypes.Structure):
@@ -348,7 +351,7 @@ def row_pitch(n: int, itemsize: int) -> int:
 def empty_plan(m: int, n: int, dtype, device):
     """An m x n tensor (a view) whose rows start on 128-byte cache lines."""
     import torch
-    ld = row_pitch(n, torch.empty((), dtype=dtype).element_size())
+    ld = row_pitch(n, dtype.itemsize)
     return torch.empty((m, ld), dtype=dtype, device=device)[:, :n]
 
 
@@ -374,17 +377,21 @@ def _batch_arrays(problems):
     arr = (Problem * len(problems))()
     outs = (Result * len(problems))()
     keep = []
+    dtype, f64, empty, esize = C0.dtype, torch.float64, torch.empty, C0.element_size()
     for k, pr in enumerate(problems):
         C = pr["C"]
         m, n = C.shape
-        if C.dtype != C0.dtype:
+        if C.dtype != dtype:
             raise TypeError("all problems of a batch share one dtype")
-        X = empty_plan(m, n, C.dtype, C.device)
-        mu = torch.empty(m, dtype=torch.float64, device=C.device)
-        nu = torch.empty(n, dtype=torch.float64, device=C.device)
+        device, ld = C.device, row_pitch(n, esize)
+        X = empty((m, ld), dtype=dtype, device=device)
+        if ld != n:
+            X = X[:, :n]
+        mu = empty(m, dtype=f64, device=device)
+        nu = empty(n, dtype=f64, device=device)
         mu0, nu0 = pr.get("mu0"), pr.get("nu0")
         arr[k] = Problem(m, n, C.data_ptr(), _ld(C), pr["p"].data_ptr(), pr["q"].data_ptr(),
-                         X.data_ptr(), _ld(X), float(pr["rho"]), float(pr["tol"]),
+                         X.data_ptr(), ld, float(pr["rho"]), float(pr["tol"]),
                          mu.data_ptr(), nu.data_ptr(),
                          None if mu0 is None else mu0.data_ptr(),
                          None if nu0 is None else nu0.data_ptr())
