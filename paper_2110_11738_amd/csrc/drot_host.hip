@@ -262,9 +262,10 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
   // 807 -> 789 / 788 / 784 / 789; 10000 x 10000 218 -> 201 / 198 / 196 / 196;
   // 10000 x 15000 coordinates 241 -> 231 / 230 / 229 / 231; 6000 x 6000 float32
   // 91 -> 82 / 81 / 80 / 81.  A caller that asks for streaming accesses gets
-  // nothing else.
+  // nothing else, and so do compensated sums, whose registers the second form
+  // of a row block would spill (10000 x 15000: 320 us, 332 with kept blocks).
   constexpr double kKeepBytes = 192e6;
-  g.g.keep = g.tile.stream && p->cache_mode == DROT_CACHE_AUTO
+  g.g.keep = g.tile.stream && !g.tile.comp && p->cache_mode == DROT_CACHE_AUTO
                  ? (int)std::min(1024.0, 1024.0 * kKeepBytes / bytes)
                  : 0;
   g.n_tiles = (int)(n_ct * n_rg);

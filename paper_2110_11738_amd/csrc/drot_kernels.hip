@@ -830,7 +830,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
   }
   };
   for (int64_t rb = rg; rb < a.g.n_rb; rb += a.g.n_rg) {
-    if constexpr (NT) {
+    if constexpr (NT && !KC) {
       // keep of every 1024 row blocks, evenly spread: each time the running
       // multiple of keep passes a multiple of 1024.
       if ((int)((uint32_t)rb * (uint32_t)a.g.keep & 1023u) < a.g.keep)
@@ -838,7 +838,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
       else
         block(rb, std::integral_constant<bool, true>{});
     } else {
-      block(rb, std::integral_constant<bool, false>{});
+      block(rb, std::integral_constant<bool, NT>{});
     }
   }
 

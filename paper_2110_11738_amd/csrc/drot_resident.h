@@ -42,20 +42,21 @@
 // each time they have doubled, then every kResSaves[2].  A save takes about two
 // iterations' time and the write of X, 8 us at 517 x 483 and 25 at 4096 x 4096.
 //
-// What bounds it: up to about 2000 x 2000 latency.  In 10.6 k clocks at
-// 517 x 483, 3.0 go to the sweep and its reductions (two waves share a SIMD),
-// 0.8 to publishing, 2.5 to 3.8 to the words' trip through memory, 1.8 to the
+// What bounds it: up to about 2000 x 2000 latency.  In 9.8 k clocks at
+// 517 x 483, 2.9 go to the sweep and its reductions (two waves share a SIMD),
+// 0.8 to publishing, 2.5 to 3.8 to the words' trip through memory, 1.3 to the
 // total and the scalar step, 1.0 to steps 5-8.  Beyond that the vector units:
 // nine operations per entry, 64 lanes per clock and compute unit, make 13.1 k
-// of the 22.7 k clocks at 4096 x 4096.  So nothing is spilled inside the
+// of the 18.5 k clocks at 4096 x 4096.  So nothing is spilled inside the
 // iteration loop (with spills: 12.4 us instead of 7.7 at 4096 x 4096): values
 // that depend on the thread number are made again in each step instead of
 // being kept, and the words of a poll are loaded without branches, all in
 // flight together (a branch and a wait per word: 5.1 us instead of 4.3 at
 // 517 x 483).
-// Measured per iteration, float32, against sweep + aux launches: 4.3 us (10.6)
-// at 517 x 483, 4.4 (13.5) at 1000^2, 5.1 (17) at 2000^2, 7.7 (36.5) at 4096^2;
-// float64: 4.1 (14) at 700 x 901, 9.0 at 2800^2.
+// Measured per iteration against sweep + aux launches, float32: 4.1 us (10.6)
+// at 517 x 483, 4.15 (13.5) at 1000^2, 4.75 (17) at 2000^2, 7.0 at 3000^2, 7.65
+// (36.5) at 4096^2, 9.6 (17.3) at 16384 x 64; float64: 4.15 (14) at 700 x 901,
+// 5.0 at 2000^2, 8.9 at 2800^2.
 #pragma once
 
 #include "drot_device.h"
@@ -561,7 +562,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     }
     __builtin_amdgcn_sched_barrier(0);
     {
-      const T kFar = (T)1e30;  // rho c outside the matrix: such entries stay 0
+      // rho c outside the matrix: such entries stay 0
+      const T kFar = std::is_same<T, float>::value ? (T)3e38f : (T)1e300;
       const int64_t ldc = uni(t2->a.g.ldc);
       const int wc0 = fresh(wr0), nvc = fresh_lane(nv);
       if (uni(t2->vec_c)) {
