@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/drot.h"
@@ -535,7 +536,8 @@ struct drot_mlp {
   int in = 0, hid = 0, out = 0, max_batch = 0;
   int64_t n_params = 0;
   int64_t off_w[3], off_b[3];  // offsets into the flat parameter vector
-  // device buffers
+  // device buffers, in device_mem
+  char* device_mem = nullptr;
   float* w = nullptr;    // float32 master parameters (flat)
   bf16* wb = nullptr;    // bfloat16 copy
   float* g = nullptr;    // gradients (flat)
@@ -711,24 +713,36 @@ int drot_mlp_create(drot_mlp** out, int device, int in, int hidden, int outd, in
       hw[n->off_w[l] + k] = (float)((2.0 * u - 1.0) * lim);
     }
   }
-  bool ok = hipMalloc(&n->w, sizeof(float) * o) == hipSuccess &&
-            hipMalloc(&n->wb, sizeof(bf16) * o) == hipSuccess &&
-            hipMalloc(&n->g, sizeof(float) * o) == hipSuccess &&
-            hipMalloc(&n->m1, sizeof(float) * o) == hipSuccess &&
-            hipMalloc(&n->m2, sizeof(float) * o) == hipSuccess &&
-            hipMalloc(&n->xb, sizeof(bf16) * (size_t)max_batch * in) == hipSuccess &&
-            hipMalloc(&n->xbt, sizeof(bf16) * (size_t)max_batch * in) == hipSuccess &&
-            hipMalloc(&n->part, sizeof(double) * (size_t)(max_batch / 32) * (outd / 32)) == hipSuccess &&
-            hipHostMalloc((void**)&n->loss, sizeof(double), hipHostMallocDefault) == hipSuccess;
-  for (int l = 0; l < 3 && ok; ++l) {
-    const size_t c = (size_t)max_batch * layer_out(n, l);
-    ok = hipMalloc(&n->a[l], sizeof(float) * c) == hipSuccess &&
-         hipMalloc(&n->ab[l], sizeof(bf16) * c) == hipSuccess &&
-         (l == 2 || hipMalloc(&n->abt[l], sizeof(bf16) * c) == hipSuccess) &&
-         hipMalloc(&n->d[l], sizeof(float) * c) == hipSuccess &&
-         hipMalloc(&n->db[l], sizeof(bf16) * c) == hipSuccess &&
-         hipMalloc(&n->dbt[l], sizeof(bf16) * c) == hipSuccess;
-  }
+  // All device buffers in one allocation, each on a 256-byte boundary.
+  size_t bytes = 0;
+  auto place = [&](auto** p, size_t count) {
+    if (n->device_mem) *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(n->device_mem + bytes);
+    bytes += (sizeof(**p) * count + 255) / 256 * 256;
+  };
+  auto place_all = [&]() {
+    bytes = 0;
+    place(&n->w, (size_t)o);
+    place(&n->wb, (size_t)o);
+    place(&n->g, (size_t)o);
+    place(&n->m1, (size_t)o);
+    place(&n->m2, (size_t)o);
+    place(&n->xb, (size_t)max_batch * in);
+    place(&n->xbt, (size_t)max_batch * in);
+    place(&n->part, (size_t)(max_batch / 32) * (outd / 32));
+    for (int l = 0; l < 3; ++l) {
+      const size_t c = (size_t)max_batch * layer_out(n, l);
+      place(&n->a[l], c);
+      place(&n->ab[l], c);
+      place(&n->abt[l], l == 2 ? 0 : c);
+      place(&n->d[l], c);
+      place(&n->db[l], c);
+      place(&n->dbt[l], c);
+    }
+  };
+  place_all();
+  const bool ok = hipMalloc((void**)&n->device_mem, bytes) == hipSuccess &&
+                  hipHostMalloc((void**)&n->loss, sizeof(double), hipHostMallocDefault) == hipSuccess;
+  if (ok) place_all();
   if (!ok) {
     (void)hipGetLastError();
     drot_mlp_destroy(n);
@@ -746,14 +760,7 @@ int drot_mlp_destroy(drot_mlp* n) {
   if (!n) return DROT_OK;
   (void)hipSetDevice(n->device);
   (void)hipDeviceSynchronize();
-  void* bufs[] = {n->w, n->wb, n->g, n->m1, n->m2, n->xb, n->xbt, n->part};
-  for (void* b : bufs)
-    if (b) (void)hipFree(b);
-  for (int l = 0; l < 3; ++l) {
-    void* lb[] = {n->a[l], n->ab[l], n->abt[l], n->d[l], n->db[l], n->dbt[l]};
-    for (void* b : lb)
-      if (b) (void)hipFree(b);
-  }
+  if (n->device_mem) (void)hipFree(n->device_mem);
   if (n->loss) (void)hipHostFree(n->loss);
   delete n;
   return DROT_OK;
