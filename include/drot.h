@@ -119,14 +119,15 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
 #define DROT_FLAG_COMPENSATED 0x8
 
 /* Small problems take a one-workgroup path: a dense cost whose plan fits the
- * registers of one 1024-thread workgroup -- in float32 n <= 64 and m <= 512,
+ * registers of one workgroup -- in float32 n <= 64 and m <= 512,
  * n <= 128 and m <= 256, n <= 256 and m <= 128, or n <= 512 and m <= 64; in
  * float64 half those rows -- with all sweep-schedule fields 0, cache_mode
  * AUTO, neither DROT_FLAG_SKIP_C nor DROT_FLAG_TIME_SWEEP, and in float32 not
  * DROT_FLAG_COMPENSATED.  There a single workgroup runs many whole
- * iterations per launch (the same steps, state and stopping test; each
- * lane's partial sums of at most 32 entries are in the problem's type, as in
- * the sweep, and everything after them in float64), since at these sizes two
+ * iterations per launch (the same steps, state and stopping test; a lane's
+ * partial sums of a row, at most 8 entries, are in the problem's type and
+ * everything after them in float64; the test trails by one iteration, and a
+ * stop repeats at most 64), since at these sizes two
  * launches per iteration would cost more than the memory traffic;
  * DROT_FLAG_NO_GRAPH has no effect on it.  Setting any tile field keeps a
  * small problem on the sweep + aux path.  drot_result.path reports which
@@ -141,8 +142,9 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * being captured or has fewer compute units, runs sweep + aux launches from
  * the same state.  Steps, state and stopping test are the same; sums are
  * formed in another order, so results agree with sweep + aux to rounding.  A
- * run that stops inside a launch repeats the iterations of that launch up to
- * the stopping one (the test trails by two).  path reports 0. */
+ * run that stops inside a launch repeats the iterations since its last saved
+ * state up to the stopping one (the test trails by two; a state is saved after
+ * 32 or 128 iterations, then at each doubling and every 256).  path reports 0. */
 typedef struct {
   double rho;          /* penalty parameter rho > 0 (the paper uses rho0/(m+n)) */
   double tol;          /* stopping tolerance >= 0; 0 runs exactly max_iter iterations */
@@ -290,7 +292,8 @@ int drot_iterate(drot_ctx *ctx, int64_t iters, void *stream);
  * operation of the paper: the sweep of Algorithm 1 (Section 3) can be tiled
  * many ways, and which is fastest depends on the shape.  Each candidate --
  * rows per block in {8, 16, 32} x {1, 2} 16-byte chunks per lane (on the
- * scalar path 1 or 4 elements) x one or two row blocks per workgroup, with
+ * scalar path 1 or 4 elements) x one or two (streamed problems: two or four)
+ * row blocks per workgroup, with
  * the bound cache_mode -- is bound (initialisation included), warmed up for
  * one graph and timed over `iters` iterations (0 = four graphs; rounded up to
  * whole graphs) with hipEvents on `stream`.  The fastest is then bound again

@@ -167,7 +167,7 @@ int choose_resident(int dtype, int64_t m, int64_t n, int cus, int* R, int* S) {
 }
 
 int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, const void* X,
-                    int64_t ldx, const drot_params* p, Geometry* out) {
+                    int64_t ldx, const drot_params* p, bool fixed_ws, Geometry* out) {
   const size_t es = dtype == DROT_F32 ? 4 : 8;
   const int V = (int)(16 / es);
   // 16-byte path: X (and a dense C) 16-byte aligned with leading dimensions
@@ -202,7 +202,7 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
     g.tile.vec = V;
     g.tile.stream = p->cache_mode == DROT_CACHE_STREAM ||
                     (p->cache_mode == DROT_CACHE_AUTO && bytes > 192.0 * 1024 * 1024);
-    const bool one = g.tile.stream && (g.tile.comp || n < 2048 ||
+    const bool one = g.tile.stream && (g.tile.comp || n < 2048 || fixed_ws ||
                                        (cost->kind == DROT_COST_DENSE && bytes > 1e9));
     g.tile.chunks = p->tile_chunks > 0 ? p->tile_chunks : (one ? 1 : 2);
     g.tile.unroll = p->tile_unroll > 0 ? p->tile_unroll : 4;
@@ -235,11 +235,12 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
   // 263 -> 257), dense costs below 1 GB 2 (10000 x 10000 180 us, with 4 188).
   // Cached problems take 1, and 2 where the cost is not dense and 512
   // workgroups are left (6900 x 6900 coordinates 71 -> 64 us; a dense
-  // 4500 x 4500 45 and 46).
+  // 4500 x 4500 45 and 46).  A solve in fixed scratch memory keeps 1 chunk and 2
+  // blocks, whose partials decide which problems fit.
   const bool dense = cost->kind == DROT_COST_DENSE;
   int64_t per = 1;
   if (g.tile.vec > 1 && p->tile_rows == 0 && g.tile.stream)
-    per = g.tile.comp || (dense && g.tile.chunks == 2) ? 2 : 4;
+    per = g.tile.comp || fixed_ws || (dense && g.tile.chunks == 2) ? 2 : 4;
   else if (g.tile.vec > 1 && p->tile_rows == 0 && !dense && !g.tile.comp &&
            (n_rb + 1) / 2 * n_ct >= 512)
     per = 2;
@@ -774,7 +775,7 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
   if (rc) return rc;
   if ((rc = check_ctx(c))) return rc;
   Geometry g;
-  if ((rc = choose_geometry(dtype, m, n, cost, X, ldx, prm, &g))) return rc;
+  if ((rc = choose_geometry(dtype, m, n, cost, X, ldx, prm, c->fixed_ws, &g))) return rc;
   size_t offs[12];
   if ((rc = ensure_workspace(c, m, n, g, offs))) return rc;
   hipStream_t s = (hipStream_t)stream;
@@ -1080,15 +1081,18 @@ extern "C" int drot_tune(drot_ctx* c, int64_t iters, drot_params* best, double* 
   }
   double best_ms = -1.0;
   drot_params winner = user;
+  // One or two row blocks per workgroup; streamed problems two or four, as the
+  // default does (one is 4-5% slower there).
+  const int few = c->geo.tile.stream ? 2 : 1;
   for (int rows : kRows)
     for (int chunks = 1; chunks <= 2 && !rc; ++chunks)
-      for (int per = 1; per <= 2 && !rc; ++per) {
+      for (int per = few; per <= 2 * few && !rc; per += few) {
         const int64_t n_rb = (A.m + rows - 1) / rows;
-        if (per == 2 && n_rb < 2) continue;
+        if (per > few && n_rb < per) continue;
         drot_params t = trial;
         t.tile_rows = rows;
         t.tile_chunks = chunks;
-        t.tile_groups = per == 1 ? 0 : (int)((n_rb + 1) / 2);
+        t.tile_groups = per == 1 ? 0 : (int)((n_rb + per - 1) / per);
         rc = drot_bind_cost(c, A.m, A.n, c->dtype, &A.cost, A.p, A.q, &t, A.X, A.ldx, A.mu0,
                             A.nu0, stream);
         if (!rc) rc = drot_iterate(c, G, stream);
@@ -1403,7 +1407,7 @@ extern "C" int drot_solve_noalloc(int64_t m, int64_t n, int dtype, const void* C
                                    "create");
   // Size check before any device call.
   Geometry g;
-  if ((rc = choose_geometry(dtype, m, n, &cost, X, ldx, params, &g))) return rc;
+  if ((rc = choose_geometry(dtype, m, n, &cost, X, ldx, params, true, &g))) return rc;
   size_t offs[12];
   const size_t need = workspace_layout(m, n, g, offs);
   if (need > kScratchBytes)
