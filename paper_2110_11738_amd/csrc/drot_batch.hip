@@ -502,7 +502,7 @@ struct BatchRun {
         t.vec_x = (uintptr_t)P.X % 16 == 0 && P.ldx % V == 0;
         t.xch = reinterpret_cast<unsigned long long*>(base + off_msg) + words;
         t.seq = reinterpret_cast<uint32_t*>(base + off_seq) + b;
-        words += (size_t)R * S * (kResPhases * (size_t)res_msg_words(dtype, L0.rpw) + res_saved_words());
+        words += drot_internal_resident_bytes(dtype, L0.rpw, R * S) / sizeof(unsigned long long);
         for (int w = 0; w < R * S; ++w) h_map[at++] = uint2{(unsigned)b, (unsigned)w};
       }
       L0.blocks = (int)(at - L0.first);

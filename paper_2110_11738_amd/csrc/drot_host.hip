@@ -137,8 +137,10 @@ void drop_graph(drot_ctx* c) {
 constexpr size_t kResTeamOff = 256, kResMsgOff = 4096;
 static_assert(kResTeamOff + sizeof(ResTeam) <= kResMsgOff, "team record");
 size_t res_msg_bytes(int dtype, int rpw, int tiles) {
+  // The smallest float32 tiles may have a word for each row instead of for two.
+  const int more = dtype == DROT_F32 && rpw == kResRpw[0] ? kResWaves * rpw / 2 : 0;
   return sizeof(unsigned long long) * (size_t)tiles *
-         (kResPhases * (size_t)res_msg_words(dtype, rpw) + res_saved_words());
+         (kResPhases * (size_t)(res_msg_words(dtype, rpw) + more) + res_saved_words());
 }
 
 // Tiles of an m x n problem with `rpw` rows per wave; false if they are too

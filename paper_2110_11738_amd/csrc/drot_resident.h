@@ -338,8 +338,10 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
 // off after 1000 iterations, 4.4e-7 with sweeps over blocks of four rows and
 // here.  With at most half a tile's columns (`slim`) each has a whole word, for
 // the sum as a float and what that leaves out; with one tile row (`lone`) the
-// tile's sums are the totals and are taken as they are.  In the other plans
-// the two cases would cost 0.1 us of 4.1 per iteration.
+// tile's sums are the totals and are taken as they are.  A float32 row's sum is
+// formed in float64 across the lanes and has a whole word too: a flat plan's
+// few rows sum as many entries.  In the other plans all this would cost 0.1 us
+// of 4.1 per iteration.
 template <typename T, int RPW, int CL, bool FINE>
 __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* teams,
                                                                 const uint2* map, int64_t iters) {
@@ -347,15 +349,18 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   constexpr int W = kWave * VEC;             // tile columns
   constexpr int TR = kResWaves * RPW;        // tile rows
   constexpr int PW = 8 / sizeof(T);          // values per message word
-  constexpr int WR = TR / PW, WC = W / PW;   // row and column words
+  // Rows in full (see FINE): a word for each, their sums over the wave in float64.
+  constexpr bool kRows64 = FINE && PW == 2;
+  using RowSum = typename std::conditional<kRows64, double, T>::type;
+  constexpr int WR = kRows64 ? TR : TR / PW, WC = W / PW;  // row and column words
   constexpr int MSG = WR + WC + kResScal;
   constexpr int GC = kResBlock / WC;         // peers read side by side, columns
   constexpr int GR = kResBlock / WR;         // and rows
   constexpr int G = RPW < 8 ? RPW : 8;       // rows whose sums are folded together
   constexpr int kHeld = RPW - CL;            // rows with rho C in registers
-  constexpr int kBuf = kResWaves * W > GC * W + GR * TR ? kResWaves * W : GC * W + GR * TR;
+  constexpr int kBuf = kResWaves * W > GC * W + GR * WR * PW ? kResWaves * W : GC * W + GR * WR * PW;
   // Row words in flight per thread: all of them for the usual team shapes.
-  constexpr int NR = sizeof(T) == 4 ? (RPW == 4 ? 1 : RPW <= 16 ? 2 : 4)
+  constexpr int NR = sizeof(T) == 4 ? (kRows64 ? 2 : RPW == 4 ? 1 : RPW <= 16 ? 2 : 4)
                                     : (RPW == 4 ? 2 : RPW <= 16 ? 4 : 8);
   static_assert(RPW % G == 0 && TR <= 256 && W <= 256 && MSG <= kResBlock, "thread roles");
   static_assert(WC == 128, "message layout");
@@ -369,7 +374,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   __shared__ __align__(16) T cl[kResWaves * SR * W];
   __shared__ __align__(16) T rowsh[TR];
   __shared__ __align__(16) T colsh[W];
-  __shared__ __align__(16) T rowp[TR];
+  __shared__ __align__(16) RowSum rowp[TR];
   __shared__ double accs[kResBlock];  // a_i, b_j of the thread's row or column
   __shared__ ResShared sh;
 
@@ -676,7 +681,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         for (int e = 0; e < VEC; ++e) cd[e] = 0.0;
 #pragma unroll
         for (int g = 0; g < RPW / G; ++g) {
-          T ca[VEC], s0 = (T)0, s1 = (T)0, rs[G];
+          T ca[VEC], s0 = (T)0, s1 = (T)0;
+          RowSum rs[G];
 #pragma unroll
           for (int u = 0; u < G; ++u) {
             const int r = g * G + u;
@@ -700,13 +706,13 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
               ca[e] = u == 0 ? x : ca[e] + x;
               s0 += c[e] * x;
             }
-            rs[u] = rsum;
+            rs[u] = (RowSum)rsum;
           }
 #pragma unroll
           for (int e = 0; e < VEC; ++e) cd[e] += (double)ca[e];
           s0d += (double)s0;
           s1d += (double)s1;
-          const T v = wave_fold(rs, lane);
+          const RowSum v = wave_fold(rs, lane);
           rowp[wave * RPW + g * G + lane / (kWave / G)] = v;  // its 64 / G lanes agree
           rtot += (double)v;
           __builtin_amdgcn_sched_barrier(0);
@@ -772,7 +778,10 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           }
         } else if (t < WC + WR) {
           const int w = t - WC;
-          if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack(rowp[2 * w], rowp[2 * w + 1]));
+          if constexpr (kRows64) {
+            const double v = rowp[w], rest = v - (double)(float)v;
+            st_word(dst, 8 * t, Wd::pack((float)v, rest - rest == 0.0 ? (float)rest : 0.f));
+          } else if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack(rowp[2 * w], rowp[2 * w + 1]));
           else st_word(dst, 8 * t, pack_double((double)rowp[w]));
           st_word(clr, 8 * t, kSent);
         }
@@ -867,7 +876,14 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
             // the peers' sums in order, zeros where there is no peer
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-              if (q + u < GR) tot += buf[GC * W + (q + u) * TR + tid];
+              if (q + u < GR) {
+                if constexpr (kRows64) {
+                  const double* const v = buf + GC * W + ((q + u) * WR + tid) * 2;
+                  tot += v[0] + v[1];
+                } else {
+                  tot += buf[GC * W + (q + u) * TR + tid];
+                }
+              }
           }
         } else if (is_col) {
 #pragma unroll
