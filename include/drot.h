@@ -142,6 +142,10 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * being captured or has fewer compute units, runs sweep + aux launches from
  * the same state.  Steps, state and stopping test are the same; sums are
  * formed in another order, so results agree with sweep + aux to rounding.  A
+ * launch whose workgroups do not all reach the chip (other processes' kernels
+ * keep some away for 0.2 s) does nothing; its iterations are run as sweep + aux
+ * before drot_poll, drot_finish, drot_checkpoint or drot_get_trace reports, and
+ * the bound problem then stays there.  A
  * run that stops inside a launch repeats the iterations since its last saved
  * state up to the stopping one (the test trails by two; a state is saved after
  * 32 or 128 iterations, then at each doubling and every 256).  path reports 0. */

@@ -47,9 +47,8 @@ void* drot_internal_staging(drot_ctx* c, size_t bytes);
 int drot_internal_resident_cap(const drot_ctx* c);
 size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles);
 bool drot_internal_resident_stream(hipStream_t s, int blocks);
-hipError_t drot_internal_resident_launch(int dtype, int rpw, const ResTeam* teams,
-                                         const uint2* map, int blocks, int64_t iters,
-                                         hipStream_t s);
+bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, const ResTeam* teams,
+                                   const uint2* map, int blocks, int64_t iters, hipStream_t s);
 
 namespace {
 
@@ -148,7 +147,7 @@ struct BatchRun {
   // Resident iteration: one team per problem, (team, workgroup) maps of the
   // launches, and the messages, which every launch clears and uses anew.
   bool res = false;
-  size_t off_team = 0, off_map = 0, off_seq = 0, off_msg = 0;
+  size_t off_team = 0, off_map = 0, off_sync = 0, off_msg = 0;
   ResTeam* h_team = nullptr;
   uint2* h_map = nullptr;
   void* own_host = nullptr;  // their memory, where it is not the context's
@@ -282,8 +281,8 @@ struct BatchRun {
       o += up(sizeof(ResTeam) * (size_t)count);
       off_map = o;
       o += up(sizeof(uint2) * (size_t)max_map);
-      off_seq = o;
-      o += up(sizeof(uint32_t) * (size_t)count);
+      off_sync = o;
+      o += up(sizeof(ResSync) * (size_t)count);
       off_msg = o;
       o += up(drot_internal_resident_bytes(dtype, 32, kResMaxTiles));
     }
@@ -501,7 +500,7 @@ struct BatchRun {
         t.vec_c = (uintptr_t)P.C % 16 == 0 && P.ldc % V == 0;
         t.vec_x = (uintptr_t)P.X % 16 == 0 && P.ldx % V == 0;
         t.xch = reinterpret_cast<unsigned long long*>(base + off_msg) + words;
-        t.seq = reinterpret_cast<uint32_t*>(base + off_seq) + b;
+        t.sync = reinterpret_cast<ResSync*>(base + off_sync) + b;
         words += drot_internal_resident_bytes(dtype, L0.rpw, R * S) / sizeof(unsigned long long);
         for (int w = 0; w < R * S; ++w) h_map[at++] = uint2{(unsigned)b, (unsigned)w};
       }
@@ -526,19 +525,18 @@ struct BatchRun {
       }
       for (const Launch& l : launches) {
         if (!drot_internal_resident_stream(s, l.blocks)) return 1;
-        BHIP(hipMemsetAsync(base + off_seq, 0, sizeof(uint32_t) * count, s));
+        BHIP(hipMemsetAsync(base + off_sync, 0, sizeof(ResSync) * count, s));
         BHIP(hipMemsetAsync(base + off_msg, 0xff,
                             drot_internal_resident_bytes(dtype, l.rpw, l.blocks), s));
-        if (drot_internal_resident_launch(dtype, l.rpw, d_team, d_map + l.first, l.blocks, G, s) !=
-            hipSuccess) {
-          (void)hipGetLastError();
+        if (!drot_internal_resident_launch(c, dtype, l.rpw, d_team, d_map + l.first, l.blocks, G, s))
           return 1;
-        }
       }
       BHIP(hipMemcpyAsync(h_st, base, SS * count, hipMemcpyDeviceToHost, s));
       BHIP(hipStreamSynchronize(s));
       changed = false;
       for (int b = 0; b < count; ++b) {
+        // A problem whose launch was called off goes to the sweeps.
+        if (fits[b] && active[b] && hst(b).missed) fits[b] = 0, changed = true;
         if (!active[b] || !hst(b).done) continue;
         active[b] = 0;
         changed = true;

@@ -89,6 +89,9 @@ struct drot_ctx {
   int res_rpw = 0, cus = 0;
   void* res_ws = nullptr;
   ResTeam* team_host = nullptr;  // pinned
+  int gate_polls = kResGatePolls;
+  int64_t refuse_after = -1;     // see drot_internal_rare
+  int64_t n_res = 0, n_graph = 0, n_single = 0;  // see drot_internal_counts
   void* staging = nullptr;       // pinned, of the batched solver
   size_t staging_bytes = 0;
 
@@ -432,6 +435,7 @@ int launch_iteration(drot_ctx* c, hipStream_t s, hipEvent_t e0, hipEvent_t e1, i
   const SweepArgs a = step_args(c, j, first);
   HIP_TRY(launch_sweep(c->dtype, mode, c->geo.tile, a, s, e0, e1));
   HIP_TRY(launch_aux(c->dtype, mode, a, s, c->geo.tile.comp, c->pend));
+  ++c->n_single;
   return DROT_OK;
 }
 
@@ -552,6 +556,7 @@ int ensure_graph(drot_ctx* c) {
     int rc = DROT_OK;
     for (int k = 0; k < G && rc == DROT_OK; ++k)
       rc = launch_iteration(c, c->cap_stream, nullptr, nullptr, k, 0);
+    c->n_single -= G;  // recorded, not run
     if (rc == DROT_OK) rc = launch_group_end(c, c->cap_stream, G, 0);
     hipError_t e = hipStreamEndCapture(c->cap_stream, &graph);
     if (rc != DROT_OK) {
@@ -602,6 +607,19 @@ bool resident_stream(hipStream_t s, int blocks) {
   return true;
 }
 
+// A resident launch for this context; false if it is refused.
+bool go_resident(drot_ctx* c, int dtype, int rpw, bool fine, const ResTeam* teams, const uint2* map,
+                 int blocks, int64_t iters, hipStream_t s) {
+  if (c->refuse_after == 0) return false;
+  if (launch_resident(dtype, rpw, fine, teams, map, blocks, iters, c->gate_polls, s) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (c->refuse_after > 0) --c->refuse_after;
+  ++c->n_res;
+  return true;
+}
+
 int check_ctx(drot_ctx* c) {
   if (!c) return fail(DROT_EINVAL, "ctx is NULL");
   HIP_TRY(hipSetDevice(c->device));
@@ -648,10 +666,20 @@ size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles) {
   return res_msg_bytes(dtype, rpw, tiles);
 }
 bool drot_internal_resident_stream(hipStream_t s, int blocks) { return resident_stream(s, blocks); }
-hipError_t drot_internal_resident_launch(int dtype, int rpw, const ResTeam* teams,
-                                         const uint2* map, int blocks, int64_t iters,
-                                         hipStream_t s) {
-  return launch_resident(dtype, rpw, true, teams, map, blocks, iters, s);
+bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, const ResTeam* teams,
+                                   const uint2* map, int blocks, int64_t iters, hipStream_t s) {
+  return go_resident(c, dtype, rpw, true, teams, map, blocks, iters, s);
+}
+
+extern "C" void drot_internal_counts(const drot_ctx* c, int64_t* out) {
+  out[0] = c->n_res;
+  out[1] = c->n_graph;
+  out[2] = c->n_single;
+}
+
+extern "C" void drot_internal_rare(drot_ctx* c, int gate_polls, int64_t refuse_after) {
+  c->gate_polls = gate_polls;
+  c->refuse_after = refuse_after;
 }
 
 // Pinned memory of the context for what a batched solve stages, kept from
@@ -874,7 +902,7 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
     t->vec_c = cost->kind == DROT_COST_DENSE && (uintptr_t)cost->data % 16 == 0 && cost->ld % V == 0;
     t->vec_x = (uintptr_t)X % 16 == 0 && ldx % V == 0;
     t->xch = reinterpret_cast<unsigned long long*>(rws + kResMsgOff);
-    t->seq = reinterpret_cast<uint32_t*>(rws);
+    t->sync = reinterpret_cast<ResSync*>(rws);
     HIP_TRY(hipMemsetAsync(rws, 0, kResTeamOff, s));
     HIP_TRY(hipMemcpyAsync(rws + kResTeamOff, t, sizeof(ResTeam), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemsetAsync(rws + kResMsgOff, 0xff,
@@ -986,10 +1014,10 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     while (c->res && iters >= kResMinIters) {
       const int64_t k = std::min(iters, kChunk);
       const char* rws = static_cast<const char*>(c->res_ws);
-      if (launch_resident(c->dtype, c->res_rpw, resident_fine(c->team_host->a.g.m, c->team_host->a.g.n),
-                          reinterpret_cast<const ResTeam*>(rws + kResTeamOff), nullptr, res_blocks,
-                          k, s) != hipSuccess) {
-        (void)hipGetLastError();
+      if (!go_resident(c, c->dtype, c->res_rpw,
+                       resident_fine(c->team_host->a.g.m, c->team_host->a.g.n),
+                       reinterpret_cast<const ResTeam*>(rws + kResTeamOff), nullptr, res_blocks, k,
+                       s)) {
         c->res = false;
         break;
       }
@@ -1009,6 +1037,7 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
   }
   while (iters - done >= G) {
     HIP_TRY(hipGraphLaunch(c->gexec, s));
+    ++c->n_graph;
     c->enq += G;
     if (timed) {
       HIP_TRY(hipStreamSynchronize(s));
@@ -1126,6 +1155,28 @@ extern "C" int drot_tune(drot_ctx* c, int64_t iters, drot_params* best, double* 
   return DROT_OK;
 }
 
+namespace {
+
+// The device state after the work enqueued on `s`, in st_host.  Iterations of
+// resident launches that were called off (see drot_resident.h) are made up
+// first, and the problem stays with sweeps from then on.
+int read_state(drot_ctx* c, hipStream_t s) {
+  HIP_TRY(hipMemcpyAsync(c->st_host, c->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  const int64_t missed = c->st_host->missed;
+  if (missed == 0) return DROT_OK;
+  c->res = false;
+  HIP_TRY(hipMemsetAsync(&c->st->missed, 0, sizeof(c->st->missed), s));
+  c->enq -= missed;
+  const int rc = drot_iterate(c, missed, s);
+  if (rc) return rc;
+  HIP_TRY(hipMemcpyAsync(c->st_host, c->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  return DROT_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 int drot_poll(drot_ctx* c, int64_t* iters_done, int32_t* stopped, void* stream) {
@@ -1133,8 +1184,7 @@ int drot_poll(drot_ctx* c, int64_t* iters_done, int32_t* stopped, void* stream) 
   if (rc) return rc;
   if (!c->bound) return fail(DROT_ESTATE, "no problem bound");
   hipStream_t s = (hipStream_t)stream;
-  HIP_TRY(hipMemcpyAsync(c->st_host, c->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  if ((rc = read_state(c, s))) return rc;
   if (iters_done) *iters_done = c->st_host->iter;
   if (stopped) *stopped = c->st_host->done;
   return DROT_OK;
@@ -1151,8 +1201,7 @@ int drot_finish(drot_ctx* c, double* mu, double* nu, drot_result* out, void* str
   sa.nu_out = nu;
   // Under the skip-C schedule an odd iteration count leaves W = X - rho C in
   // the array; the final pass then restores X while evaluating it.
-  HIP_TRY(hipMemcpyAsync(c->st_host, c->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  if ((rc = read_state(c, s))) return rc;
   const int fmode = (c->skipc && (c->st_host->iter & 1)) ? kFinalW : kFinal;
   HIP_TRY(launch_sweep(c->dtype, fmode, c->geo.tile, sa, s));
   HIP_TRY(launch_aux(c->dtype, fmode, sa, s));
@@ -1223,7 +1272,7 @@ int drot_checkpoint(drot_ctx* c, void* host_buf, size_t bytes, void* stream) {
     return fail(DROT_ESTATE, "under the skip-C schedule X holds X - rho C after an odd number of "
                              "iterations: checkpoint after an even number");
   hipStream_t s = (hipStream_t)stream;
-  HIP_TRY(hipStreamSynchronize(s));
+  if ((rc = read_state(c, s))) return rc;
   const int64_t m = c->args.m, n = c->args.n;
   const size_t es = c->dtype == DROT_F32 ? 4 : 8;
   char* out = static_cast<char*>(host_buf);
@@ -1310,7 +1359,8 @@ int drot_get_trace(drot_ctx* c, int64_t first, int64_t count, double* host_out) 
   if (!c->bound) return fail(DROT_ESTATE, "no problem bound");
   if (!host_out || count < 0) return fail(DROT_EINVAL, "bad output buffer or count");
   HIP_TRY(hipDeviceSynchronize());
-  HIP_TRY(hipMemcpy(c->st_host, c->st, sizeof(DevState), hipMemcpyDeviceToHost));
+  if ((rc = read_state(c, nullptr))) return rc;
+  HIP_TRY(hipDeviceSynchronize());
   const int64_t last = c->st_host->iter;
   if (first < 1 || first + count - 1 > last || last - first >= kTraceCap)
     return fail(DROT_EINVAL, "records [%lld, %lld] not available (have up to %lld, keep %d)",

@@ -86,7 +86,8 @@ struct DevState {
   // --- problem (host-written at bind) ---
   double rho, tol;
   int64_t max_iter;
-  int32_t tol_mode, pad0;
+  int32_t tol_mode;
+  uint32_t missed;          // iterations of resident launches whose workgroups did not all come
   int64_t m, n;
   // --- filled by the initialisation pass ---
   double sum_p, sum_q, norm_pq, norm_c;
@@ -171,13 +172,22 @@ constexpr int kResMinIters = 8;  // shorter runs go to sweep + aux
 constexpr int kResRpw[] = {4, 8, 16, 24, 32};
 constexpr int kResSaves[] = {32, 128, 256};  // iterations between saved states
 constexpr int kResMaxTiles = 256, kResMaxSide = 128;  // workgroups of a team, tiles of a side
+constexpr int kResGatePolls = 1 << 18;  // of a launch's verdict before giving up (0.2 s)
+// Words that a team's workgroups share beside the messages (all cleared with them).
+struct ResSync {
+  uint32_t seq;      // steps taken since the buffers were cleared
+  uint32_t arrived;  // workgroups of this launch on the chip
+  uint32_t verdict;  // of this launch: 0 open, kResGo, kResOff
+  uint32_t left;     // workgroups that have seen kResOff
+};
+constexpr uint32_t kResGo = 1, kResOff = 2;
 struct ResTeam {
   SweepArgs a;
   int R, S;              // tiles down and across
   int vec_c, vec_x;      // C, X readable as 16-byte chunks
   unsigned long long* xch;  // [kResPhases][R S] messages of res_msg_words words, then the
                             // saved vectors, res_saved_words() for each of the R S
-  uint32_t* seq;         // steps taken since the buffers were cleared
+  ResSync* sync;
 };
 constexpr int res_cols(int dtype) { return kWave * (dtype == 0 ? 4 : 2); }
 constexpr int res_saved_words() { return 2 * kResBlock; }
@@ -224,3 +234,13 @@ hipError_t launch_batch_step(int dtype, int mode, const TileCfg& t, const SweepA
 hipError_t launch_prep_batch(const SweepArgs* args, int count, hipStream_t s);
 
 }  // namespace drot
+
+// For tests, which look them up in the library.  What a context has run since
+// it was created: out[0] resident launches, [1] graph replays, [2] iterations
+// launched singly.
+extern "C" void drot_internal_counts(const struct drot_ctx* c, int64_t* out);
+// Conditions that are rare in use, from now on: how often a workgroup of a
+// resident launch polls for the others before giving up (0: it never waits),
+// and after how many more cooperative launches the next ones are refused
+// (negative: none is).
+extern "C" void drot_internal_rare(struct drot_ctx* c, int gate_polls, int64_t refuse_after);

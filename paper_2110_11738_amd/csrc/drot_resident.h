@@ -21,9 +21,17 @@
 // phase (s + 2) mod 4, i.e. of message s - 2, which every reader has consumed:
 // it published s - 1 after reading s - 2.  That reset is complete (vmcnt 0 and
 // a barrier) before s + 1 is published, so whoever has seen s + 1 and polls
-// for s + 2 cannot see message s - 2 any more.  A poll that runs dry ends the
-// kernel with an error state instead of spinning on.  All workgroups have to
-// be on the chip together: the launch is cooperative.
+// for s + 2 cannot see message s - 2 any more.
+//
+// All workgroups have to be on the chip together.  The launch is cooperative,
+// which does not keep other processes' kernels away: so each workgroup reports
+// as it starts, the last one gives the word to go, and one that has polled for
+// it kResGatePolls times calls the launch off.  Which of the two it is one
+// compare-and-swap decides for all.  A launch that is called off has touched
+// nothing: it adds its iterations to DevState::missed, and the host makes them
+// up with sweeps.  Once all are there nothing keeps one of them away, and a poll
+// of a message that runs dry all the same ends the kernel with an error state
+// instead of spinning on.
 //
 // Every workgroup of a tile row adds the same row partials in the same order
 // (columns likewise), so the row's duals are computed redundantly and
@@ -187,6 +195,42 @@ __device__ __forceinline__ V fresh_lane(V v) {
   return v;
 }
 
+// The gate of a launch (one thread of each workgroup): report, the last of
+// `blocks` giving the word; wait for the word or call the launch off; and, off,
+// leave, true for the last one, which clears the words for the next launch.
+__device__ __forceinline__ void res_say(ResSync* g, uint32_t v) {
+  uint32_t open = 0;
+  __hip_atomic_compare_exchange_strong(&g->verdict, &open, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t res_count(uint32_t* word) {
+  return __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+}
+__device__ __forceinline__ uint32_t res_verdict(ResSync* g) {
+  return __hip_atomic_load(&g->verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// False for the whole workgroup where the launch is off.
+__device__ __forceinline__ bool res_gate(ResSync* g, int blocks, int polls, int& go) {
+  if (threadIdx.x == 0) {
+    uint32_t v = 0;
+    if (res_count(&g->arrived) == (uint32_t)blocks) res_say(g, kResGo);
+    for (int k = 0; k < polls && (v = res_verdict(g)) == 0; ++k) __builtin_amdgcn_s_sleep(2);
+    if (v == 0) {
+      res_say(g, kResOff);
+      v = res_verdict(g);
+    }
+    go = v == kResGo;
+  }
+  __syncthreads();
+  return uni(go);
+}
+__device__ __forceinline__ void res_clear(ResSync* g) { g->arrived = g->verdict = g->left = 0; }
+__device__ __forceinline__ bool res_leave(ResSync* g, int blocks) {
+  if (res_count(&g->left) != (uint32_t)blocks) return false;
+  res_clear(g);
+  return true;
+}
+
 // Shared state of a workgroup outside the sums.
 struct ResShared {
   double wsum[3][kResWaves];  // total, <rho C,X>, sum [t]_+^2 per wave
@@ -203,7 +247,7 @@ struct ResShared {
   int trace_mask;
   double base[3];             // cphi, cpsi, alpha of the saved state
   int rec_k, rec_status, rec_done;
-  int stop_at, dead;
+  int stop_at, dead, go;
 };
 
 // Four words of a lane, `count` of them wanted (the rest repeats the last
@@ -344,7 +388,8 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
 // of 4.1 per iteration.
 template <typename T, int RPW, int CL, bool FINE>
 __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* teams,
-                                                                const uint2* map, int64_t iters) {
+                                                                const uint2* map, int64_t iters,
+                                                                int gate_polls) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int W = kWave * VEC;             // tile columns
   constexpr int TR = kResWaves * RPW;        // tile rows
@@ -394,7 +439,11 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   const int m = uni((int)tm->a.g.m), n = uni((int)tm->a.g.n);
   const bool slim = FINE && PW == 2 && n <= WC && R > 1;
   const bool lone = FINE && R == 1;
-  int seq = uni((int)*tm->seq);
+  if (!res_gate(uni(tm->sync), R * S, gate_polls, sh.go)) {
+    if (tid == 0 && res_leave(uni(tm->sync), R * S)) st->missed += (uint32_t)limit;
+    return;
+  }
+  int seq = uni((int)uni(tm->sync)->seq);
   const Msg xch = (Msg)uni(tm->xch);
   const int phase = R * S * MSG;
 
@@ -976,7 +1025,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   }
   if (b == 0 && tid == 6 * kWave) {
     const uint64_t now = wall_clock64();
-    *t3->seq = (uint32_t)seq;
+    t3->sync->seq = (uint32_t)seq;
+    res_clear(t3->sync);  // everybody is past the gate: their messages have been read
     st->cphi = sh.bc[k & 3][0];
     st->cpsi = sh.bc[k & 3][1];
     st->alpha = sh.bc[k & 3][2];
@@ -1019,10 +1069,10 @@ const void* resident_entry(int rpw, bool fine) {
 // the workgroups wait for each other, so they have to be on the chip together.
 // `fine`: for teams with a plan that resident_fine() names, at the smallest rpw.
 hipError_t launch_resident(int dtype, int rpw, bool fine, const ResTeam* teams, const uint2* map,
-                           int blocks, int64_t iters, hipStream_t s) {
+                           int blocks, int64_t iters, int gate_polls, hipStream_t s) {
   const void* f = dtype == 0 ? resident_entry<float>(rpw, fine) : resident_entry<double>(rpw, fine);
   if (!f || blocks < 1) return hipErrorInvalidValue;
-  void* args[] = {(void*)&teams, (void*)&map, (void*)&iters};
+  void* args[] = {(void*)&teams, (void*)&map, (void*)&iters, (void*)&gate_polls};
   return hipLaunchCooperativeKernel(f, dim3((unsigned)blocks), dim3(kResBlock), args, 0, s);
 }
 

@@ -1,0 +1,123 @@
+"""Which launches the iterations of a problem that fits the chip run as, and that
+the ways off the chip give the same result: launches called off because their
+workgroups are not all there.  The library counts its launches and lets a test
+force such conditions (drot_internal_counts and drot_internal_rare)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from gen import config_mixture_2d, round_to
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def ctx():
+    from paper_2110_11738_amd import drot
+    c = drot.Context(0)
+    yield c
+    c.close()
+
+
+def _counts(ctx):
+    """Resident launches, graph replays, iterations launched singly."""
+    from paper_2110_11738_amd import drot
+    out = (ctypes.c_int64 * 3)()
+    drot.lib().drot_internal_counts(ctx.handle, out)
+    return np.array(out)
+
+
+def _rare(ctx, gate_polls=1 << 18, refuse_after=-1):
+    from paper_2110_11738_amd import drot
+    drot.lib().drot_internal_rare(ctx.handle, ctypes.c_int(gate_polls),
+                                  ctypes.c_int64(refuse_after))
+
+
+def _problem(m, n, dtype, seed=51):
+    import torch
+    inst = config_mixture_2d(seed, m, n)
+    if dtype == "float32":
+        inst = round_to(inst, np.float32)
+    t = lambda a: torch.tensor(a, dtype=getattr(torch, dtype), device="cuda")
+    return t(inst.C), t(inst.p), t(inst.q), inst.rho
+
+
+def _steps(ctx, prob, calls, **kw):
+    """bind, calls of iterate, finish: plan, duals and trace (without times)."""
+    import torch
+    from paper_2110_11738_amd import drot
+    C, p, q, rho = prob
+    X = torch.empty_like(C)
+    mu, nu = (torch.empty(k, dtype=torch.float64, device="cuda") for k in C.shape)
+    ctx.bind(C, p, q, X, drot.make_params(rho, 0.0, 10 ** 6, **kw))
+    for k in calls:
+        ctx.iterate(k)
+    res = ctx.finish(mu, nu)
+    assert res["iters"] == sum(calls)
+    return X, mu, nu, torch.tensor(ctx.trace(1, sum(calls))[:, [0, 1, 2, 3, 4, 5, 7]])
+
+
+def _same(a, b):
+    import torch
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,m,n", [("float32", 700, 300), ("float64", 1100, 260)])
+def test_called_off_launches_are_made_up_by_sweeps(ctx, dtype, m, n):
+    prob = _problem(m, n, dtype)
+    on_chip = _steps(ctx, prob, (40, 24))
+    _rare(ctx, refuse_after=0)
+    c0 = _counts(ctx)
+    sweeps = _steps(ctx, prob, (40, 24))
+    assert _counts(ctx)[0] == c0[0]
+    _rare(ctx, gate_polls=0)
+    c0 = _counts(ctx)
+    _same(_steps(ctx, prob, (40, 24)), sweeps)
+    assert _counts(ctx)[0] == c0[0] + 2  # both went out, and gave up
+    _rare(ctx)
+    c0 = _counts(ctx)
+    _same(_steps(ctx, prob, (40, 24)), on_chip)  # nothing is left behind
+    assert tuple(_counts(ctx) - c0) == (2, 0, 0)
+
+
+def test_called_off_launches_of_a_solve_a_checkpoint_and_a_batch(ctx):
+    import torch
+    from paper_2110_11738_amd import drot
+    prob = _problem(300, 700, "float64")
+    C, p, q, rho = prob
+
+    def runs():
+        X, res, mu, nu = drot.solve(C, p, q, rho, tol=2e-2, max_iter=5000, ctx=ctx)
+        assert res["status"] == 0
+        Xc = torch.empty_like(C)
+        ctx.bind(C, p, q, Xc, drot.make_params(rho, 0.0, 100))
+        ctx.iterate(50)
+        blob = ctx.checkpoint()
+        Xs = Xc.clone()
+        ctx.bind(C, p, q, Xs, drot.make_params(rho, 0.0, 100, x0_mode=drot.X0_GIVEN))
+        ctx.resume(blob)
+        ctx.iterate(50)
+        assert ctx.finish()["iters"] == 100
+        return X, mu, nu, Xs
+
+    def batch():
+        probs = [dict(C=C[:k].contiguous(), p=p[:k] / p[:k].sum(), q=q, rho=rho, tol=0.0)
+                 for k in (300, 40, 150)]
+        for pr in probs:
+            pr["q"] = pr["q"] * (pr["p"].sum() / pr["q"].sum())
+        rc, outs = drot.solve_batched(probs, max_iter=60, ctx=ctx)
+        assert rc == drot.MAXITER and all(r["iters"] == 60 for _, r, _, _ in outs)
+        return [t for X, _, mu, nu in outs for t in (X, mu, nu)]
+
+    _rare(ctx, refuse_after=0)
+    sweeps, one_by_one = runs(), batch()
+    _rare(ctx, gate_polls=0)
+    c0 = _counts(ctx)
+    _same(runs(), sweeps)
+    # a team of one workgroup has nobody to wait for
+    off = batch()
+    assert _counts(ctx)[0] > c0[0] + 2
+    for a, b in zip(off, one_by_one):
+        assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
