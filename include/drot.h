@@ -137,11 +137,12 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * path: one cooperative launch runs many iterations with the plan and the cost
  * on the chip, tile by tile, and the tiles exchange their row and column sums.
  * It needs all sweep-schedule fields 0, cache_mode AUTO, no flags (float64
- * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32 and calls of
- * drot_iterate for at least 8 iterations; anything else, and a stream that is
- * being captured or has fewer compute units, runs sweep + aux launches from
- * the same state.  Steps, state and stopping test are the same; sums are
- * formed in another order, so results agree with sweep + aux to rounding.  A
+ * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32 and max_iter at
+ * least 8; anything else, and a call on a stream that is being captured or has
+ * fewer compute units, runs sweep + aux launches from the same state.  Steps,
+ * state and stopping test are the same; sums are formed in another order, so
+ * results agree with sweep + aux to rounding.  How iterations are split into
+ * calls, and a checkpoint between them, changes no bit on either path.  A
  * launch whose workgroups do not all reach the chip (other processes' kernels
  * keep some away for 0.2 s) does nothing; its iterations are run as sweep + aux
  * before drot_poll, drot_finish, drot_checkpoint or drot_get_trace reports, and
@@ -287,8 +288,8 @@ int drot_bind(drot_ctx *ctx, int64_t m, int64_t n, int dtype, const void *C, int
               const double *mu0, const double *nu0, void *stream);
 
 /* Enqueue `iters` further iterations of Algorithm 1 (one sweep and one dual
- * update each; on the one-workgroup path, launches of up to 4096 whole
- * iterations) on `stream` without waiting.  Iterations after the stopping
+ * update each; on the one-workgroup and resident paths, launches of up to 4096
+ * whole iterations) on `stream` without waiting.  Iterations after the stopping
  * test (or max_iter) has fired are no-ops on the device. */
 int drot_iterate(drot_ctx *ctx, int64_t iters, void *stream);
 

@@ -835,14 +835,16 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
              small_fits(dtype, m, n);
   c->pend = !c->small && aux_workgroups(m, n) < kAuxSplitMin;
   // The resident iteration: default schedule, graphs allowed, plain sums, and
-  // launches long enough to carry their fixed cost (loading and writing back
-  // the plan and one closing exchange, about as much as ten iterations), so
-  // callers that poll more often than every 32 iterations stay on graphs.
+  // launches long enough to carry their fixed cost (31 us at 517 x 483, 71 at
+  // 4096 x 4096: the launch, loading and writing back the plan, a closing
+  // exchange), so callers that poll more often than every 32 iterations stay on
+  // graphs, and solves of few iterations on single launches.
   int res_R = 0, res_S = 0;
   const int plain = DROT_FLAG_NO_GRAPH | DROT_FLAG_TIME_SWEEP | DROT_FLAG_SKIP_C |
                     (dtype == DROT_F32 ? DROT_FLAG_COMPENSATED : 0);
   c->res = !c->small && !c->fixed_ws && c->team_host && !(prm->flags & plain) &&
-           (prm->check_every == 0 || prm->check_every >= 32) && prm->tile_rows == 0 &&
+           (prm->check_every == 0 || prm->check_every >= 32) &&
+           prm->max_iter >= kResMinIters && prm->tile_rows == 0 &&
            prm->tile_chunks == 0 && prm->tile_unroll == 0 && prm->tile_groups == 0 &&
            prm->cache_mode == DROT_CACHE_AUTO &&
            (c->res_rpw = choose_resident(dtype, m, n, c->cus, &res_R, &res_S)) > 0;
@@ -1007,11 +1009,15 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
   }
   if (c->res && iters == 0) return DROT_OK;
   const int res_blocks = c->res ? c->team_host->R * c->team_host->S : 0;
-  if (c->res && iters >= kResMinIters && resident_stream(s, res_blocks)) {
-    // Bounded launches, as above; a rest too short for one, and everything
-    // where a launch is refused, goes to sweep + aux, from the same state.
+  if (c->res && resident_stream(s, res_blocks)) {
+    // Bounded launches, as above, however few iterations a call asks for: the
+    // sweeps add in another order, and a result must not depend on how its
+    // iterations are split into calls.  (A call for one takes 35 us at
+    // 517 x 483 and 79 at 4096 x 4096, as sweep + aux 13 and 38; from four on a
+    // launch is the faster one.)  Where a launch is refused the rest goes to
+    // sweep + aux, from the same state.
     constexpr int64_t kChunk = 4096;
-    while (c->res && iters >= kResMinIters) {
+    while (c->res && iters > 0) {
       const int64_t k = std::min(iters, kChunk);
       const char* rws = static_cast<const char*>(c->res_ws);
       if (!go_resident(c, c->dtype, c->res_rpw,
@@ -1024,7 +1030,7 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
       c->enq += k;
       iters -= k;
     }
-    if (c->res) return run_eager(c, s, iters);
+    if (c->res) return DROT_OK;
   }
   if ((c->prm.flags & DROT_FLAG_NO_GRAPH) || (c->res && iters < group_size(c)))
     return run_eager(c, s, iters);

@@ -168,7 +168,7 @@ struct SweepArgs {
 constexpr int kResWaves = 8;
 constexpr int kResBlock = kResWaves * kWave;
 constexpr int kResPhases = 4;  // message buffers per workgroup
-constexpr int kResMinIters = 8;  // shorter runs go to sweep + aux
+constexpr int kResMinIters = 8;  // max_iter below it: sweep + aux
 constexpr int kResRpw[] = {4, 8, 16, 24, 32};
 constexpr int kResSaves[] = {32, 128, 256};  // iterations between saved states
 constexpr int kResMaxTiles = 256, kResMaxSide = 128;  // workgroups of a team, tiles of a side

@@ -1,6 +1,7 @@
 """Which launches the iterations of a problem that fits the chip run as, and that
 the ways off the chip give the same result: launches called off because their
-workgroups are not all there.  The library counts its launches and lets a test
+workgroups are not all there.  Within a path, splitting the iterations into calls
+changes no bit.  The library counts its launches and lets a test
 force such conditions (drot_internal_counts and drot_internal_rare)."""
 import ctypes
 
@@ -121,3 +122,35 @@ def test_called_off_launches_of_a_solve_a_checkpoint_and_a_batch(ctx):
     assert _counts(ctx)[0] > c0[0] + 2
     for a, b in zip(off, one_by_one):
         assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("dtype,m,n", [("float32", 700, 300), ("float32", 1300, 2700),
+                                       ("float64", 1100, 260)])
+def test_splitting_calls_changes_no_bit(ctx, dtype, m, n):
+    """40 iterations in one call and in several, with single iterations among
+    them, with a checkpoint after any of them, and a solve of 1030 (1024 and 6)."""
+    import torch
+    from paper_2110_11738_amd import drot
+    prob = _problem(m, n, dtype)
+    C, p, q, rho = prob
+    whole = _steps(ctx, prob, (40,))
+    for calls in ((37, 3), (1, 39), (7, 1, 31, 1)):
+        _same(_steps(ctx, prob, calls), whole)
+    prm = dict(rho=rho, tol=0.0, max_iter=100)
+    X = torch.empty_like(C)
+    ctx.bind(C, p, q, X, drot.make_params(**prm))
+    ctx.iterate(37)
+    blob = ctx.checkpoint()
+    other = drot.Context(0)
+    try:
+        Y = X.clone()
+        other.bind(C, p, q, Y, drot.make_params(x0_mode=drot.X0_GIVEN, **prm))
+        other.resume(blob)
+        other.iterate(3)
+        assert other.finish()["iters"] == 40
+        assert torch.equal(Y, whole[0])
+    finally:
+        other.close()
+    X, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=1030, ctx=ctx)
+    assert res["iters"] == 1030
+    _same((X, mu, nu), _steps(ctx, prob, (500, 530))[:3])
