@@ -440,9 +440,10 @@ int launch_iteration(drot_ctx* c, hipStream_t s, hipEvent_t e0, hipEvent_t e1, i
 }
 
 // Iterations per graph / per host poll (even under the skip-C schedule, so
-// that every graph starts with a C-reading iteration).
-int group_size(const drot_ctx* c) {
-  int g = c->prm.check_every > 0 ? c->prm.check_every : (c->small || c->res ? 1024 : 32);
+// that every graph starts with a C-reading iteration).  `on_chip`: they run as
+// resident launches.
+int group_size(const drot_ctx* c, bool on_chip) {
+  int g = c->prm.check_every > 0 ? c->prm.check_every : (c->small || on_chip ? 1024 : 32);
   if (c->skipc && (g & 1)) ++g;
   return g;
 }
@@ -542,7 +543,7 @@ int build_timed_graph(drot_ctx* c, int G, hipGraph_t* out) {
 }
 
 int ensure_graph(drot_ctx* c) {
-  const int G = group_size(c);
+  const int G = group_size(c, false);
   const bool timed = (c->prm.flags & DROT_FLAG_TIME_SWEEP) != 0;
   if (c->gexec && c->g_iters == G && c->g_timed == timed) return DROT_OK;
   drop_graph(c);
@@ -586,14 +587,17 @@ int harvest_events(drot_ctx* c, int pairs) {
   return DROT_OK;
 }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Whether a cooperative launch of `blocks` workgroups can go to `s` now: not into
 // a capture, and not onto a stream restricted to fewer compute units.
 bool resident_stream(hipStream_t s, int blocks) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
+  if (capturing(s)) return false;
   if (s) {
     uint32_t mask[32] = {};
     if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
@@ -605,6 +609,11 @@ bool resident_stream(hipStream_t s, int blocks) {
     }
   }
   return true;
+}
+
+// Whether the bound problem's next call on `s` runs as resident launches.
+bool on_chip(const drot_ctx* c, hipStream_t s) {
+  return c->res && resident_stream(s, c->team_host->R * c->team_host->S);
 }
 
 // A resident launch for this context; false if it is refused.
@@ -963,7 +972,7 @@ namespace {
 // DROT_FLAG_TIME_SWEEP is set).
 int run_eager(drot_ctx* c, hipStream_t s, int64_t count) {
   const bool timed = (c->prm.flags & DROT_FLAG_TIME_SWEEP) != 0;
-  const int G = group_size(c);
+  const int G = group_size(c, false);
   int rc = DROT_OK;
   int64_t done = 0;
   while (done < count) {
@@ -1007,9 +1016,7 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     }
     return DROT_OK;
   }
-  if (c->res && iters == 0) return DROT_OK;
-  const int res_blocks = c->res ? c->team_host->R * c->team_host->S : 0;
-  if (c->res && resident_stream(s, res_blocks)) {
+  if (on_chip(c, s)) {
     // Bounded launches, as above, however few iterations a call asks for: the
     // sweeps add in another order, and a result must not depend on how its
     // iterations are split into calls.  (A call for one takes 35 us at
@@ -1022,8 +1029,8 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
       const char* rws = static_cast<const char*>(c->res_ws);
       if (!go_resident(c, c->dtype, c->res_rpw,
                        resident_fine(c->team_host->a.g.m, c->team_host->a.g.n),
-                       reinterpret_cast<const ResTeam*>(rws + kResTeamOff), nullptr, res_blocks, k,
-                       s)) {
+                       reinterpret_cast<const ResTeam*>(rws + kResTeamOff), nullptr,
+                       c->team_host->R * c->team_host->S, k, s)) {
         c->res = false;
         break;
       }
@@ -1032,10 +1039,10 @@ extern "C" int drot_iterate(drot_ctx* c, int64_t iters, void* stream) {
     }
     if (c->res) return DROT_OK;
   }
-  if ((c->prm.flags & DROT_FLAG_NO_GRAPH) || (c->res && iters < group_size(c)))
+  if ((c->prm.flags & DROT_FLAG_NO_GRAPH) || (c->res && capturing(s)))
     return run_eager(c, s, iters);
   if ((rc = ensure_graph(c))) return rc;
-  const int G = group_size(c);
+  const int G = group_size(c, false);
   int64_t done = 0;
   if (c->skipc && (c->enq & 1) && iters > 0) {  // realign to a C-reading iteration
     if ((rc = run_eager(c, s, 1))) return rc;
@@ -1388,7 +1395,7 @@ int drot_solve_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cos
   int rc = validate(m, n, dtype, cost, p, q, prm, X, ldx, mu0, nu0);
   if (rc) return rc;
   if ((rc = drot_bind_cost(c, m, n, dtype, cost, p, q, prm, X, ldx, mu0, nu0, stream))) return rc;
-  const int G = group_size(c);
+  const int G = group_size(c, on_chip(c, (hipStream_t)stream));
   int64_t done_iters = 0;
   int32_t stopped = 0;
   while (!stopped && done_iters < prm->max_iter) {

@@ -1,6 +1,6 @@
 """Which launches the iterations of a problem that fits the chip run as, and that
 the ways off the chip give the same result: launches called off because their
-workgroups are not all there.  Within a path, splitting the iterations into calls
+workgroups are not all there, streams with fewer compute units.  Within a path, splitting the iterations into calls
 changes no bit.  The library counts its launches and lets a test
 force such conditions (drot_internal_counts and drot_internal_rare)."""
 import ctypes
@@ -154,3 +154,40 @@ def test_splitting_calls_changes_no_bit(ctx, dtype, m, n):
     X, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=1030, ctx=ctx)
     assert res["iters"] == 1030
     _same((X, mu, nu), _steps(ctx, prob, (500, 530))[:3])
+
+
+def _few_units():
+    """A stream on half of the compute units."""
+    import torch
+    hip = ctypes.CDLL("libamdhip64.so")
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    words = (units + 31) // 32
+    mask = (ctypes.c_uint32 * words)(*([0xffffffff] * (words // 2)))
+    s = ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(s), ctypes.c_uint32(words), mask) == 0
+    return torch.cuda.ExternalStream(s.value), lambda: hip.hipStreamDestroy(s)
+
+
+def test_a_stream_with_fewer_units_replays_graphs(ctx):
+    """The sweeps of a problem that would fit the chip go out as on any other
+    stream: graphs of 32 iterations, and no more than that after a stop."""
+    import torch
+    from paper_2110_11738_amd import drot
+    C, p, q, rho = _problem(2100, 2500, "float32")  # more tiles than half of the units
+    _rare(ctx, refuse_after=0)
+    a = drot.solve(C, p, q, rho, tol=0.0, max_iter=100, ctx=ctx)
+    tol = float(ctx.trace(1, 100)[:, 5].min()) * 1.0000001
+    at = int(np.argmax(ctx.trace(1, 100)[:, 5] <= tol)) + 1
+    _rare(ctx)
+    s, drop = _few_units()
+    torch.cuda.synchronize()
+    c0 = _counts(ctx)
+    b = drot.solve(C, p, q, rho, tol=0.0, max_iter=100, ctx=ctx, stream=s)
+    assert tuple(_counts(ctx) - c0) == (0, 3, 4)
+    _same((a[0], a[2], a[3]), (b[0], b[2], b[3]))
+    c0 = _counts(ctx)
+    d = drot.solve(C, p, q, rho, tol=tol, max_iter=2000, ctx=ctx, stream=s)
+    assert d[1]["iters"] == at and d[1]["status"] == 0
+    assert tuple(_counts(ctx) - c0) == (0, (at + 31) // 32, 0)
+    torch.cuda.synchronize()
+    drop()
