@@ -228,6 +228,7 @@ struct BatchRun {
       g.ldc = P.ldc;
       g.ldx = P.ldx;
       g.n_ct = (int)((P.n + W - 1) / W);
+      g.n_rp = row_partials(dtype, tile, g.n_ct);
       g.rows = rows;
       g.n_rb = (int)((P.m + g.rows - 1) / g.rows);
       g.n_rg = prm.tile_groups > 0 ? std::min(prm.tile_groups, g.n_rb)

@@ -257,6 +257,7 @@ int choose_geometry(int dtype, int64_t m, int64_t n, const drot_cost* cost, cons
   g.g.ldc = cost->kind == DROT_COST_COORDS ? 0 : cost->ld;
   g.g.ldx = ldx;
   g.g.n_ct = (int)n_ct;
+  g.g.n_rp = row_partials(dtype, g.tile, g.g.n_ct);
   g.g.n_rb = (int)n_rb;
   g.g.n_rg = (int)n_rg;
   g.g.rows = rows;

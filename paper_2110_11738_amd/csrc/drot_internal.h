@@ -118,6 +118,7 @@ struct SweepGeom {
   int64_t ldc, ldx;
   int64_t ldcp;     // row stride of colpart (n rounded up to a multiple of 4)
   int n_ct;         // column strips
+  int n_rp;         // partials of a row in an iteration (row_partials())
   int n_rb;         // row blocks of `rows` rows
   int n_rg;         // row groups: workgroup (strip, g) sweeps row blocks g, g + n_rg, ...
   int rows;         // rows per row block
@@ -145,7 +146,7 @@ struct SweepArgs {
   double* nu_out;
   DevState* st;
   void* colpart;           // [n_rg][ldcp] (float in the FP32 iteration, else double)
-  void* rowpart;           // [n_ct][m]
+  void* rowpart;           // [n_ct][m], float in the FP32 iteration: [n_rp][m]
   double* tiles;           // [n_rg * n_ct][kTileSlots], workgroup (g, ct) at g * n_ct + ct
   double* blockpart;       // [kSlots][aux workgroups] (slot-major)
   // Pending form of the iteration (few aux workgroups; see drot_kernels.hip):
@@ -206,6 +207,12 @@ struct TileCfg {
   bool ragged;      // 16-byte path with n not a multiple of vec (masked last chunk)
   bool comp = false;  // compensated per-lane sums, float64 partials (float32 iteration)
 };
+
+// A streamed plain float32 iteration in strips of two chunks keeps a row partial
+// for each chunk; else there is one for each strip.
+inline int row_partials(int dtype, const TileCfg& t, int n_ct) {
+  return dtype == 0 && t.vec == 4 && t.chunks == 2 && t.stream && !t.comp ? 2 * n_ct : n_ct;
+}
 
 // Launchers (drot_kernels.hip).
 // With e0 / e1 given, the sweep goes through hipExtLaunchKernel, which

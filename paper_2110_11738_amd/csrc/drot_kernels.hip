@@ -224,8 +224,8 @@ __device__ __forceinline__ void aux_body(const SweepArgs& a, const int b, const 
     const int64_t i = (int64_t)(b - col_wgs) * kAuxRows + lane;
     double u[1] = {0.0};
     if (i < m) {
-      const int n_ct = a.g.n_ct;
-      const int c0 = n_ct * wave / kWaves, c1 = n_ct * (wave + 1) / kWaves;
+      const int n_rp = is_iter(MODE) ? a.g.n_rp : a.g.n_ct;
+      const int c0 = n_rp * wave / kWaves, c1 = n_rp * (wave + 1) / kWaves;
       typedef P P1 __attribute__((ext_vector_type(1)));
       sum_strided<8>(reinterpret_cast<const P1*>(static_cast<const P*>(a.rowpart) + i), m, c0, c1,
                      u);
@@ -469,7 +469,7 @@ __device__ __forceinline__ void aux_wave_iter(const SweepArgs& a, const int b, c
       typedef P P1 __attribute__((ext_vector_type(1)));
       double u[1] = {0.0};
       sum_strided<8>(reinterpret_cast<const P1*>(static_cast<const P*>(a.rowpart) + i), m, 0,
-                     a.g.n_ct, u);
+                     a.g.n_rp, u);
       tot = u[0];
       idx = i;
       w0 = (double)static_cast<const T*>(a.p)[i];
@@ -709,6 +709,31 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
   L colacc[CH][VEC];
   L s0, s1;  // tile scalars (cost & dual, or |C|^2 & bad count)
 
+  // Where a workgroup takes more than one row block and strips of two chunks by
+  // default (kWiden: streamed problems, and costs that are not dense), a lane's
+  // plain float32 sums run over U rows and are then added in float64, the
+  // columns' in LDS, where they take no registers; and a row has a partial for
+  // each chunk (kTwoSums, row_partials()).  So no float32 sum is longer than in
+  // strips of one chunk and two row blocks of 16: after an iteration of random
+  // plans the row sums' error is that of such strips and the column sums' 0.6 to
+  // 0.8 of it, with longer float32 sums 1.4 and 1.5 times (us per iteration with
+  // them -> so: 20000 x 20000 768 -> 770, 6000 x 6000 70.0 -> 72.1, coordinates
+  // 10000 x 15000 189.4 -> 192.6).
+  constexpr bool kWiden = std::is_same<P, float>::value && VEC > 1 && (NT || CM != kCostDense);
+  constexpr bool kTwoSums = kWiden && NT && CH == 2;
+  using S = typename std::conditional<kWiden, double, P>::type;
+  __shared__ __align__(16) S sm[kWaves * W];
+  double s0d = 0.0, s1d = 0.0;
+  // Where chunk c's column e of lane l lies in a wave's part of sm: widened, two
+  // columns side by side in 16 bytes and the lanes next to each other.
+  auto slot = [](int c, int e, int l) {
+    return kWiden ? ((c * VEC + e) / 2 * kWave + l) * 2 + e % 2 : (c * kWave + l) * VEC + e;
+  };
+  if constexpr (kWiden) {
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) sm[wave * W + slot(k / VEC, k % VEC, lane)] = (S)0;
+  }
+
   P* __restrict__ rowpart = static_cast<P*>(a.rowpart);
 
   // One row block; the policy says whether its accesses are nontemporal.
@@ -762,9 +787,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
         if (is_iter(MODE)) rowv = static_cast<const T*>(a.phiT)[i] + shift;
         if (is_final(MODE)) rowv = a.phi64[i] + (double)shift;
         if (MODE == kInitPQ) rowv = static_cast<const T*>(a.p)[i];
-        L rsum;
+        L rsum, rsum0;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
+          if (kTwoSums && c == 1) {
+            rsum0 = rsum;
+            rsum = L{};
+          }
           if (ok[c]) {
             T outv[VEC];
 #pragma unroll
@@ -824,8 +853,28 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
           }
         }
         const P tot = wave_sum(rsum.get());
-        if (lane == 0) rowpart[(int64_t)ct * m + i] = tot;
+        if constexpr (kTwoSums) {
+          const P tot0 = wave_sum(rsum0.get());
+          if (lane < 2) rowpart[(2 * (int64_t)ct + lane) * m + i] = lane == 0 ? tot0 : tot;
+        } else {
+          if (lane == 0) rowpart[(int64_t)ct * m + i] = tot;
+        }
       }
+    }
+    if constexpr (kWiden) {
+      // nothing of the next rows in here: it would cost a wave per SIMD
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          sm[wave * W + slot(c, e, lane)] += (S)colacc[c][e].get();
+          colacc[c][e] = L{};
+        }
+      s0d += (double)s0.get();
+      s1d += (double)s1.get();
+      s0 = s1 = L{};
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   };
@@ -843,28 +892,32 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
   }
 
   // ---- tile partials: combine the four waves in LDS, fixed order -----------
-  __shared__ P sm[kWaves * W];
   __shared__ double ssc[2][kWaves];
+  if constexpr (kWiden) {
+    s0d = wave_sum(s0d);
+    s1d = wave_sum(s1d);
+  } else {
 #pragma unroll
-  for (int c = 0; c < CH; ++c)
+    for (int c = 0; c < CH; ++c)
 #pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      sm[wave * W + c * kWave * VEC + lane * VEC + e] = colacc[c][e].get();
-  const P w0 = wave_sum(s0.get());
-  const P w1 = wave_sum(s1.get());
+      for (int e = 0; e < VEC; ++e) sm[wave * W + slot(c, e, lane)] = colacc[c][e].get();
+    s0d = (double)wave_sum(s0.get());
+    s1d = (double)wave_sum(s1.get());
+  }
   if (lane == 0) {
-    ssc[0][wave] = (double)w0;
-    ssc[1][wave] = (double)w1;
+    ssc[0][wave] = s0d;
+    ssc[1][wave] = s1d;
   }
   __syncthreads();
   P* __restrict__ colpart = static_cast<P*>(a.colpart);
   for (int k = threadIdx.x; k < W; k += kBlock) {
     const int64_t j = col0 + k;
     if (j < n) {
-      P v = sm[k];
+      const int at = slot(k / (kWave * VEC), k % VEC, k / VEC % kWave);
+      S v = sm[at];
 #pragma unroll
-      for (int w = 1; w < kWaves; ++w) v += sm[w * W + k];
-      colpart[(int64_t)rg * a.g.ldcp + j] = v;
+      for (int w = 1; w < kWaves; ++w) v += sm[w * W + at];
+      colpart[(int64_t)rg * a.g.ldcp + j] = (P)v;
     }
   }
   if (threadIdx.x == 0) {
