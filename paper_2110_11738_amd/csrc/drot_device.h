@@ -130,9 +130,6 @@ __device__ __forceinline__ double div_by(double x, double d, double r) {
 __device__ __forceinline__ float relu_of(float v) { return __builtin_fmaxf(v, 0.f); }
 __device__ __forceinline__ double relu_of(double v) { return __builtin_fmax(v, 0.0); }
 
-__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
 // ---------------------------------------------------------------------------
 // Types and memory helpers.
 // ---------------------------------------------------------------------------

@@ -2,8 +2,8 @@
 // the cost held on the chip.
 //
 // A problem is cut into R x S tiles, one workgroup (one compute unit) each.
-// A workgroup of eight waves loads its tile of X and of C once, keeps
-// both in registers (the largest tiles keep half of C in LDS) for up to
+// A workgroup of eight waves loads its tile of X and of rho C once, keeps
+// both in registers (the largest tiles keep half of rho C in LDS) for up to
 // thousands of iterations, and writes X back at the end.  What crosses
 // workgroups in an iteration is O(rows + columns) per tile: the tile's row
 // and column partials and a few scalars, exchanged through memory.  256
@@ -77,7 +77,7 @@ typedef unsigned long long u64;
 constexpr u64 kSent = ~0ull;
 constexpr int kResSpins = 1 << 22;  // polls of one word before giving up (seconds)
 constexpr int kResScal = 16;        // scalar words of a message
-// Scalar words: total of the tile, <C, X>, sum [t]_+^2, stop iteration
+// Scalar words: total of the tile, <rho C, X>, sum [t]_+^2, stop iteration
 // (workgroup 0), and of the previous iteration sum r^2, sum p phi~ (tile
 // column 0), sum s^2, sum q psi~ (tile row 0).
 enum ResWord : int { kRwTot = 0, kRwS0, kRwS1, kRwCtl, kRwR2, kRwPphi, kRwS2, kRwQpsi, kRwCount };
@@ -233,15 +233,15 @@ __device__ __forceinline__ bool res_leave(ResSync* g, int blocks) {
 
 // Shared state of a workgroup outside the sums.
 struct ResShared {
-  double wsum[3][kResWaves];  // total, <C,X>, sum [t]_+^2 per wave
+  double wsum[3][kResWaves];  // total, <rho C,X>, sum [t]_+^2 per wave
   double esum[2][kResWaves];  // sum r^2 (or s^2), sum p phi~ (or q psi~) per wave
   double bc[4][3];            // cphi, cpsi, alpha after iteration k, at k mod 4
   double inv[3];              // 1 / n, 1 / m, 1 / (m + n)
   double mon[2][6][kWave];    // workgroup 0: a step's test sums per lane, by step parity
-  double prev[2];             // workgroup 0: <C,X> and sum [t]_+^2 one iteration back
+  double prev[2];             // workgroup 0: <rho C,X> and sum [t]_+^2 one iteration back
   double rec[6];              // workgroup 0: the latest tested iteration
   StateIn sv;
-  double wall_rate;
+  double rhoT, wall_rate;
   double* trace;
   double ctl;                 // workgroup 0: stop iteration to announce
   int trace_mask;
@@ -329,7 +329,7 @@ __device__ __forceinline__ void res_keep(double (&mon)[6][kWave], int wave, int 
 
 // Workgroup 0, one wave: the test of iteration kt (of this launch; none if
 // kt < 1) with the sums that the step of iteration kt + 1 (or the closing
-// step) brought into sh.mon: <C,X> and sum [t]_+^2 of that step's own
+// step) brought into sh.mon: <rho C,X> and sum [t]_+^2 of that step's own
 // iteration, kept for the next call, and the other four of iteration kt.
 __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][kWave], int kt,
                                          int lane) {
@@ -353,7 +353,7 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
     f.cpsi = sh.bc[kt & 3][1];
     f.alpha = sh.bc[kt & 3][2];
     f.k = sh.sv.iter + kt;
-    const double ws[8] = {0.0, w[2], w[3], 0.0, w[4], w[5], sh.prev[0], sh.prev[1]};
+    const double ws[8] = {0.0, w[2], w[3], 0.0, w[4], w[5], sh.prev[0] / sh.rhoT, sh.prev[1]};
     scalar_tests(f, sh.sv, ws, false);
     double* const tr = sh.trace + (((int)f.k - 1) & sh.trace_mask) * kTraceWidth;
     trace_record(tr, f, sh.sv.t_start, wall_clock64(), sh.wall_rate);
@@ -372,7 +372,7 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
   sh.prev[1] = w[1];
 }
 
-// RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep C in
+// RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep rho C in
 // LDS.  `map`: the (team, workgroup) of each block, or null for the one team
 // teams[0].
 //
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   constexpr int GC = kResBlock / WC;         // peers read side by side, columns
   constexpr int GR = kResBlock / WR;         // and rows
   constexpr int G = RPW < 8 ? RPW : 8;       // rows whose sums are folded together
-  constexpr int kHeld = RPW - CL;            // rows with C in registers
+  constexpr int kHeld = RPW - CL;            // rows with rho C in registers
   constexpr int kBuf = kResWaves * W > GC * W + GR * WR * PW ? kResWaves * W : GC * W + GR * WR * PW;
   // Row words in flight per thread: all of them for the usual team shapes.
   constexpr int NR = sizeof(T) == 4 ? (kRows64 ? 2 : RPW == 4 ? 1 : RPW <= 16 ? 2 : 4)
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   using Wd = WordOf<T>;
 
   __shared__ double buf[kBuf];  // column sums of the waves, then the peers' sums
-  // C of the last CL rows; before that (and where CL = 0) the staging area
+  // rho C of the last CL rows; before that (and where CL = 0) the staging area
   // of rows on their way between memory and registers, SR rows per wave.
   constexpr int SR = CL > 0 ? CL : RPW < 8 ? RPW : 8;
   static_assert(RPW % SR == 0 && (CL == 0 || SR == CL), "staging");
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   // Scalar words that a wave reads, up to four per lane: word ox + (lane mod
   // (1 << xsh)) of every xstep-th byte from lane >> xsh on, xcnt of them.
   // Every workgroup: wave 7 the totals, wave 2 the stop word.  Workgroup 0:
-  // waves 5 and 6 <C,X> and the dual sums of all tiles, wave 3 the row sums
+  // waves 5 and 6 <rho C,X> and the dual sums of all tiles, wave 3 the row sums
   // (first tile column), wave 4 the column sums (first tile row), two words
   // of a workgroup by two lanes.
   int xcnt = R * S, xstep = 8 * MSG, xsh = 0, xw = kRwTot;
@@ -496,6 +496,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     sh.inv[0] = 1.0 / (double)n;
     sh.inv[1] = 1.0 / (double)m;
     sh.inv[2] = 1.0 / ((double)m + (double)n);
+    sh.rhoT = (double)rhoT;
     sh.wall_rate = tm->a.wall_rate;
     sh.trace = tm->a.trace;
     sh.trace_mask = (int)tm->a.trace_cap - 1;
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   }
 
   // The state is saved between segments of the launch (kResSaves says when),
-  // except where X's way to memory leads through LDS that holds C.
+  // except where X's way to memory leads through LDS that holds rho C.
   const bool saves = CL == 0 || (uni(tm->vec_x) && n % VEC == 0);
   const int seg0 = R > 32 ? kResSaves[0] : kResSaves[1];
   bool replay = false;
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     const ResTeam* const t2 = fresh(tm);
     const int wl0 = fresh(wr0), nvl = fresh_lane(nv);
     {
-      // X, then C.  Chunks of 16 bytes straight to registers where the
+      // X, then rho C.  Chunks of 16 bytes straight to registers where the
       // layout allows (a chunk that straddles column n stays inside the row's
       // leading dimension); else element by element through the staging area.
       const T* const X = uni(static_cast<const T*>(t2->a.X));
@@ -615,6 +616,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     }
     __builtin_amdgcn_sched_barrier(0);
     {
+      // rho c outside the matrix: such entries stay 0
+      const T kFar = std::is_same<T, float>::value ? (T)3e38f : (T)1e300;
       const int64_t ldc = uni(t2->a.g.ldc);
       const int wc0 = fresh(wr0), nvc = fresh_lane(nv);
       if (uni(t2->vec_c)) {
@@ -625,7 +628,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           T c[VEC];
           load_chunk<T, VEC, false>(C + (int64_t)(wc0 + r < m ? wc0 + r : m - 1) * ldc + jc, c);
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) c[e] = wc0 + r < m && e < nvc ? c[e] : (T)0;
+          for (int e = 0; e < VEC; ++e)
+            c[e] = wc0 + r < m && e < nvc ? mul_rounded<T>(rhoT, c[e]) : kFar;
           if (r < kHeld) {
 #pragma unroll
             for (int e = 0; e < VEC; ++e) pc[r < kHeld ? r : 0][e] = c[e];
@@ -666,7 +670,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
             for (int u = 0; u < 4; ++u)
 #pragma unroll
               for (int e = 0; e < VEC; ++e)
-                stage[(u0 + u) * W + e] = wc0 + g * SR + u0 + u < m && e < nvc ? c[u][e] : (T)0;
+                stage[(u0 + u) * W + e] = wc0 + g * SR + u0 + u < m && e < nvc
+                                              ? mul_rounded<T>(rhoT, c[u][e]) : kFar;
           }
           if (g * SR < kHeld) {
 #pragma unroll
@@ -678,10 +683,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     }
     if (base == 0) {
       accs[tid] = own_r ? t2->a.a[gid] : own_c ? t2->a.b[gid] : 0.0;
-      // outside the matrix a dual so low that such entries stay 0
-      const T kFar = std::is_same<T, float>::value ? (T)-3e38f : (T)-1e300;
-      if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : kFar;
-      if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : kFar;
+      if (is_row) rowsh[tid] = own_r ? static_cast<const T*>(t2->a.phiT)[gid] : (T)0;
+      if (is_col) colsh[cc0] = own_c ? static_cast<const T*>(t2->a.psiT)[gid] : (T)0;
       if (tid == 0) {
         sh.base[0] = st->cphi;
         sh.base[1] = st->cpsi;
@@ -743,7 +746,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
             T rsum = (T)0;
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-              const T t = fma_of(-rhoT, c[e], rowv + colv[e]);
+              const T t = rowv + colv[e] - c[e];
               const T tp = relu_of(t);
               s1 += tp * tp;
               const T x = relu_of(xr[r][e] + t);

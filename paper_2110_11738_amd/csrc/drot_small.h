@@ -1,5 +1,5 @@
 // Small problems: the whole iteration in one workgroup, thousands of
-// iterations per launch, with the plan and C in registers.
+// iterations per launch, with the plan and rho C in registers.
 //
 // Eleven sweep waves hold the plan: wave w the rows w, w + 11, ..., lane l the
 // columns l, l + 64, ... (NCOL of them).  The twelfth wave, the service wave,
@@ -55,13 +55,11 @@ __device__ __forceinline__ int small_fresh(int v) {
 template <typename T, int NCOL>
 struct SmallShared {
   static constexpr int NW = kSmallWaves;
-  // A dual outside the matrix: such entries stay 0.
-  static constexpr T kFar = std::is_same<T, float>::value ? (T)-3e38f : (T)-1e300;
   static constexpr int RT = small_wave_rows(std::is_same<T, float>::value ? 0 : 1, NCOL);
   T rowp[NW][RT][kWave];         // each lane's partial of each row
   T rowsh[NW][RT];               // row shifts without the scalar part
   double colp[NW][kWave * NCOL];  // column sums of each wave
-  double mon0[2][NW][kWave];     // <C,X> (lanes < 32), sum [t]_+^2; by parity
+  double mon0[2][NW][kWave];     // <rho C,X> (lanes < 32), sum [t]_+^2; by parity
   double mon1[NW][kWave];        // sum r^2 (lanes < 32), sum p phi~
   T colsh[kWave * NCOL];         // column shifts without the scalar part
   T shift;                       // the scalar part, of rows and columns together
@@ -88,15 +86,16 @@ __device__ __forceinline__ void small_sweep(SmallShared<T, NCOL>& sh, const Swee
   double ra[NP], rph[NP];  // a, phi~ of row 16 p + lane / 4 of the wave
   T marg[NP];
 
-  // C once, and outside the matrix (whose duals are kFar there) nothing.
+  // rho C once; outside the matrix a cost so large that such entries stay 0.
   {
     const T* C = static_cast<const T*>(a.C) + lane;
+    const T kFar = std::is_same<T, float>::value ? (T)3e38f : (T)1e300;
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const T* const row = C + (int64_t)(wave + NW * t) * a.g.ldc;
 #pragma unroll
       for (int c = 0; c < NCOL; ++c)
-        pc[t][c] = t < nrows && lane + kWave * c < n ? row[kWave * c] : (T)0;
+        pc[t][c] = t < nrows && lane + kWave * c < n ? mul_rounded<T>(rhoT, row[kWave * c]) : kFar;
     }
   }
 #pragma unroll
@@ -127,7 +126,7 @@ __device__ __forceinline__ void small_sweep(SmallShared<T, NCOL>& sh, const Swee
         rph[p] = r < nr ? a.phi64[w + NW * r] : 0.0;
       }
       for (int r = lane; r < RT; r += kWave)
-        sh.rowsh[w][r] = r < nr ? static_cast<const T*>(a.phiT)[w + NW * r] : sh.kFar;
+        sh.rowsh[w][r] = r < nr ? static_cast<const T*>(a.phiT)[w + NW * r] : (T)0;
     }
     small_barrier();
 
@@ -156,7 +155,7 @@ __device__ __forceinline__ void small_sweep(SmallShared<T, NCOL>& sh, const Swee
     bool stopped = false;
     while (k < limit) {
       const int nr = small_fresh(nrows);
-      // Step 4 on the held entries; <C,X> and sum [t]_+^2 at the incoming
+      // Step 4 on the held entries; <rho C,X> and sum [t]_+^2 at the incoming
       // shifts.
       {
         const T shift = sh.shift;
@@ -178,7 +177,7 @@ __device__ __forceinline__ void small_sweep(SmallShared<T, NCOL>& sh, const Swee
               T rs = (T)0;
 #pragma unroll
               for (int c = 0; c < NCOL; ++c) {
-                const T tt = fma_of(-rhoT, pc[t][c], rowv + colv[c]);
+                const T tt = rowv + colv[c] - pc[t][c];
                 const T tp = relu_of(tt);
                 s1 += tp * tp;
                 const T xn = relu_of(xr[t][c] + tt);
@@ -255,12 +254,12 @@ __device__ __forceinline__ void small_sweep(SmallShared<T, NCOL>& sh, const Swee
 // Wave 11.
 template <typename T, int NCOL>
 __device__ __forceinline__ void small_service(SmallShared<T, NCOL>& sh, const SweepArgs& a,
-                                              const StateIn& sv, int limit) {
+                                              const StateIn& sv, const T rhoT, int limit) {
   constexpr int NW = kSmallWaves;
   const int lane = threadIdx.x & (kWave - 1);
   const int n = (int)a.g.n;
   const double dm = (double)a.g.m, dn = (double)n, dmn = (double)a.g.m + (double)n;
-  const double im = 1.0 / dm, in = 1.0 / dn, imn = 1.0 / dmn;
+  const double im = 1.0 / dm, in = 1.0 / dn, imn = 1.0 / dmn, irho = 1.0 / (double)rhoT;
   double cb[NCOL], cps[NCOL], marg[NCOL];  // b, psi~, q
   double cphi = sv.cphi, cpsi = sv.cpsi, alpha = sv.alpha;
   double base[3] = {cphi, cpsi, alpha};  // of the state in memory
@@ -303,7 +302,7 @@ __device__ __forceinline__ void small_service(SmallShared<T, NCOL>& sh, const Sw
       const int j = lane + kWave * c;
       cb[c] = j < n ? a.b[j] : 0.0;
       cps[c] = j < n ? a.psi64[j] : 0.0;
-      sh.colsh[j] = j < n ? static_cast<const T*>(a.psiT)[j] : sh.kFar;
+      sh.colsh[j] = j < n ? static_cast<const T*>(a.psiT)[j] : (T)0;
     }
     if (lane == 0) sh.shift = (T)(cphi + cpsi);
     small_barrier();
@@ -341,7 +340,7 @@ __device__ __forceinline__ void small_service(SmallShared<T, NCOL>& sh, const Sw
         const double ps = div_by(cb[c] - 2.0 * s[c], dm, im);
         cb[c] -= s[c];
         cps[c] = ps;
-        sh.colsh[lane + kWave * c] = lane + kWave * c < n ? (T)ps : sh.kFar;
+        sh.colsh[lane + kWave * c] = (T)ps;
         s2 += s[c] * s[c];
         qpsi += marg[c] * ps;
       }
@@ -364,6 +363,7 @@ __device__ __forceinline__ void small_service(SmallShared<T, NCOL>& sh, const Sw
           v[0] += sh.mon0[(k - 1) & 1][w][lane];
           v[1] += sh.mon1[w][lane];
         }
+        v[0] *= lane < 32 ? irho : 1.0;  // <rho C,X> to <C,X>
 #pragma unroll
         for (int q = 0; q < 3; ++q) v[q] += dpp<0xB1>(v[q]);
 #pragma unroll
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kSmallBlock) void small_kernel(SweepArgs a, int64_t
   if (limit <= 0) return;
   const T rhoT = (T)sv.rho;
   if (__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) == kSmallWaves)
-    small_service<T, NCOL>(sh, a, sv, limit);
+    small_service<T, NCOL>(sh, a, sv, rhoT, limit);
   else
     small_sweep<T, NCOL>(sh, a, rhoT, limit);
 }

@@ -79,27 +79,3 @@ def test_rounding_of_one_iteration(ctx, kind, m, n, rows, per, cols):
         print(f"[sums] rms {float(err):.3e}, plain {float(ref):.3e}, ratio {float(err / ref):.3f}",
               flush=True)
         assert err <= 1.02 * ref
-
-
-@pytest.mark.parametrize("dtype,m,n", [("float32", 100, 90), ("float64", 90, 70), ("float32", 300, 700),
-                                       ("float32", 1500, 2300), ("float64", 300, 700)])
-@pytest.mark.parametrize("rho", ["small", "below the type"])
-def test_objective_of_the_trace_is_of_the_cost_as_given(ctx, dtype, m, n, rho):
-    """On-chip iterations: X = 1, so small a rho that X stays 1, and a constant cost
-    of few bits make <C, X> an exact sum; rho times that cost is not exact, and
-    zero where rho is below what the type can hold."""
-    import torch
-    from paper_2110_11738_amd import drot
-    dt = getattr(torch, dtype)
-    rho = {"float32": 1.1e-9, "float64": 1.1e-18}[dtype] if rho == "small" else \
-        {"float32": 1e-50, "float64": 1e-307}[dtype]
-    p, q = torch.full((m,), 1.0 / 4096, dtype=dt, device="cuda"), torch.full((n,), 1.0 / 4096, dtype=dt, device="cuda")
-    p[0] += 1 - p.double().sum().item()
-    q[0] += 1 - q.double().sum().item()
-    X = torch.ones(m, n, dtype=dt, device="cuda")
-    print(f"[objective] {dtype} {m}x{n} rho {rho}", flush=True)
-    ctx.bind(torch.full_like(X, 1.25), p, q, X, drot.make_params(rho, 0.0, 8, x0_mode=drot.X0_GIVEN))
-    ctx.iterate(1)
-    assert ctx.poll() == (1, False)
-    assert torch.equal(X, torch.ones_like(X))
-    assert ctx.trace(1, 1)[0, 0] == 1.25 * m * n
