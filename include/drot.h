@@ -122,8 +122,9 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * registers of one workgroup -- in float32 n <= 64 and m <= 512,
  * n <= 128 and m <= 256, n <= 256 and m <= 128, or n <= 512 and m <= 64; in
  * float64 half those rows -- with all sweep-schedule fields 0, cache_mode
- * AUTO, neither DROT_FLAG_SKIP_C nor DROT_FLAG_TIME_SWEEP, and in float32 not
- * DROT_FLAG_COMPENSATED.  There a single workgroup runs many whole
+ * AUTO, neither DROT_FLAG_SKIP_C nor DROT_FLAG_TIME_SWEEP, in float32 not
+ * DROT_FLAG_COMPENSATED, and rho and rho times the costs well inside the type's
+ * range (float32: 1e-30 to 1e30).  There a single workgroup runs many whole
  * iterations per launch (the same steps, state and stopping test; a lane's
  * partial sums of a row, at most 8 entries, are in the problem's type and
  * everything after them in float64; the test trails by one iteration, and a
@@ -137,8 +138,8 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
  * path: one cooperative launch runs many iterations with the plan and the cost
  * on the chip, tile by tile, and the tiles exchange their row and column sums.
  * It needs all sweep-schedule fields 0, cache_mode AUTO, no flags (float64
- * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32 and max_iter at
- * least 8; anything else, and a call on a stream that is being captured or has
+ * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32, max_iter at
+ * least 8 and rho and rho times the costs in the same range; anything else, and a call on a stream that is being captured or has
  * fewer compute units, runs sweep + aux launches from the same state.  Steps,
  * state and stopping test are the same; sums are formed in another order, so
  * results agree with sweep + aux to rounding.  How iterations are split into

@@ -398,6 +398,7 @@ struct BatchRun {
       if (h.init_neg > 0 || !(h.sum_p > 0) ||
           std::fabs(h.sum_p - h.sum_q) > 8.0 * eps * std::max(h.sum_p, h.sum_q))
         return bfail(DROT_EMASS, "problem %d: negative marginals or unequal mass", b);
+      if (!on_chip_range(dtype, h.rho, h.norm_c, h.m, h.n)) fits[b] = 0;
     }
     return DROT_OK;
   }

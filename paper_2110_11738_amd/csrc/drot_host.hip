@@ -951,6 +951,10 @@ int drot_bind_cost(drot_ctx* c, int64_t m, int64_t n, int dtype, const drot_cost
   const double sp = h->sum_p, sq = h->sum_q;
   if (!(sp > 0) || std::fabs(sp - sq) > 8.0 * eps * std::max(sp, sq))
     return fail(DROT_EMASS, "sum(p) = %.17g and sum(q) = %.17g differ (or are not positive)", sp, sq);
+  if (!on_chip_range(dtype, prm->rho, h->norm_c, m, n)) {
+    c->small = c->res = false;
+    c->pend = aux_workgroups(m, n) < kAuxSplitMin;
+  }
   c->bound = true;
   return DROT_OK;
 }

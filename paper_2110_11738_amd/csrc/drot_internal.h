@@ -214,6 +214,16 @@ inline int row_partials(int dtype, const TileCfg& t, int n_ct) {
   return dtype == 0 && t.vec == 4 && t.chunks == 2 && t.stream && !t.comp ? 2 * n_ct : n_ct;
 }
 
+// The on-chip iterations hold rho C in the element type and take <C,X> from it,
+// so rho, rho times the costs' root mean square and their largest value have to
+// be well inside the type's range; the sweeps, which hold C, have no such bound.
+// `norm_c`: |C|_F, from the initialisation pass.
+inline bool on_chip_range(int dtype, double rho, double norm_c, int64_t m, int64_t n) {
+  const double low = dtype == 0 ? 1e-30 : 1e-290, high = dtype == 0 ? 1e30 : 1e290;
+  const double rms = norm_c / __builtin_sqrt((double)m * (double)n);
+  return rho >= low && rho <= high && rho * norm_c <= high && (norm_c == 0.0 || rho * rms >= low);
+}
+
 // Launchers (drot_kernels.hip).
 // With e0 / e1 given, the sweep goes through hipExtLaunchKernel, which
 // records the dispatch's own start and end times in those events.

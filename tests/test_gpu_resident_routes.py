@@ -191,3 +191,24 @@ def test_a_stream_with_fewer_units_replays_graphs(ctx):
     assert tuple(_counts(ctx) - c0) == (0, (at + 31) // 32, 0)
     torch.cuda.synchronize()
     drop()
+
+
+@pytest.mark.parametrize("m,n", [(100, 90), (300, 700)])
+@pytest.mark.parametrize("rho,cost", [(1e-50, 1.0), (1e-12, 1e-30), (1e25, 1e20)])
+def test_products_beyond_the_element_type_take_sweeps(ctx, m, n, rho, cost):
+    """rho times the cost is below float32's normal numbers, or beyond its range:
+    alone, and in a batch beside an ordinary problem."""
+    from paper_2110_11738_amd import drot
+    C, p, q, _ = _problem(m, n, "float32")
+    C = C * cost
+    X, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=20, ctx=ctx)
+    tr = ctx.trace(1, 20)
+    assert res["iters"] == 20 and np.isfinite(tr).all()
+    # <C, X> of the last iteration: float32 sums of at most 512 entries
+    assert abs(tr[19, 0] - res["objective"]) <= 1e-6 * abs(res["objective"])
+    c0 = _counts(ctx)
+    rc, outs = drot.solve_batched([dict(C=C, p=p, q=q, rho=rho, tol=0.0),
+                                   dict(C=_problem(m, n, "float32")[0], p=p, q=q, rho=1e-3, tol=0.0)],
+                                  max_iter=20, ctx=ctx)
+    assert rc == drot.MAXITER and all(r["iters"] == 20 for _, r, _, _ in outs)
+    assert _counts(ctx)[0] - c0[0] == 1
