@@ -47,7 +47,8 @@ void* drot_internal_staging(drot_ctx* c, size_t bytes);
 int drot_internal_resident_cap(const drot_ctx* c);
 size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles);
 bool drot_internal_resident_stream(hipStream_t s, int blocks);
-bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, const ResTeam* teams,
+bool drot_internal_resident_fine(int64_t m, int64_t n);
+bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, bool fine, const ResTeam* teams,
                                    const uint2* map, int blocks, int64_t iters, hipStream_t s);
 
 namespace {
@@ -157,6 +158,7 @@ struct BatchRun {
   struct Launch {
     int rpw, blocks;
     int64_t first;  // in the map
+    bool fine;
   };
   std::vector<Launch> launches;
   std::vector<char> active;
@@ -477,7 +479,7 @@ struct BatchRun {
     const size_t es = dtype == DROT_F32 ? 4 : 8;
     const int V = (int)(16 / es);
     for (const auto& bin : bins) {
-      Launch L0{32, 0, at};
+      Launch L0{32, 0, at, false};
       for (int rpw : kResRpw) {
         int sum = 0;
         bool ok = true;
@@ -503,6 +505,7 @@ struct BatchRun {
         t.vec_x = (uintptr_t)P.X % 16 == 0 && P.ldx % V == 0;
         t.xch = reinterpret_cast<unsigned long long*>(base + off_msg) + words;
         t.sync = reinterpret_cast<ResSync*>(base + off_sync) + b;
+        L0.fine = L0.fine || L0.rpw == kResRpw[0] || drot_internal_resident_fine(P.m, P.n);
         words += drot_internal_resident_bytes(dtype, L0.rpw, R * S) / sizeof(unsigned long long);
         for (int w = 0; w < R * S; ++w) h_map[at++] = uint2{(unsigned)b, (unsigned)w};
       }
@@ -530,7 +533,8 @@ struct BatchRun {
         BHIP(hipMemsetAsync(base + off_sync, 0, sizeof(ResSync) * count, s));
         BHIP(hipMemsetAsync(base + off_msg, 0xff,
                             drot_internal_resident_bytes(dtype, l.rpw, l.blocks), s));
-        if (!drot_internal_resident_launch(c, dtype, l.rpw, d_team, d_map + l.first, l.blocks, G, s))
+        if (!drot_internal_resident_launch(c, dtype, l.rpw, l.fine, d_team, d_map + l.first, l.blocks, G,
+                                           s))
           return 1;
       }
       BHIP(hipMemcpyAsync(h_st, base, SS * count, hipMemcpyDeviceToHost, s));

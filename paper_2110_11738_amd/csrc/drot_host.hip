@@ -140,8 +140,8 @@ void drop_graph(drot_ctx* c) {
 constexpr size_t kResTeamOff = 256, kResMsgOff = 4096;
 static_assert(kResTeamOff + sizeof(ResTeam) <= kResMsgOff, "team record");
 size_t res_msg_bytes(int dtype, int rpw, int tiles) {
-  // The smallest float32 tiles may have a word for each row instead of for two.
-  const int more = dtype == DROT_F32 && rpw == kResRpw[0] ? kResWaves * rpw / 2 : 0;
+  // Float32 tiles may have a word for each row instead of for two.
+  const int more = dtype == DROT_F32 ? kResWaves * rpw / 2 : 0;
   return sizeof(unsigned long long) * (size_t)tiles *
          (kResPhases * (size_t)(res_msg_words(dtype, rpw) + more) + res_saved_words());
 }
@@ -676,9 +676,10 @@ size_t drot_internal_resident_bytes(int dtype, int rpw, int tiles) {
   return res_msg_bytes(dtype, rpw, tiles);
 }
 bool drot_internal_resident_stream(hipStream_t s, int blocks) { return resident_stream(s, blocks); }
-bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, const ResTeam* teams,
+bool drot_internal_resident_fine(int64_t m, int64_t n) { return resident_fine(m, n); }
+bool drot_internal_resident_launch(drot_ctx* c, int dtype, int rpw, bool fine, const ResTeam* teams,
                                    const uint2* map, int blocks, int64_t iters, hipStream_t s) {
-  return go_resident(c, dtype, rpw, true, teams, map, blocks, iters, s);
+  return go_resident(c, dtype, rpw, fine, teams, map, blocks, iters, s);
 }
 
 extern "C" void drot_internal_counts(const drot_ctx* c, int64_t* out) {

@@ -376,16 +376,17 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
 // LDS.  `map`: the (team, workgroup) of each block, or null for the one team
 // teams[0].
 //
-// FINE: column sums cross tiles unrounded where a plan has few columns or few
-// rows.  Such a side sums many entries into few duals, and a float rounding of
-// every tile's sum shows in them: nu of a float32 plan of 583 x 26 is 6.4e-7
-// off after 1000 iterations, 4.4e-7 with sweeps over blocks of four rows and
+// FINE (float32): column sums cross tiles unrounded where a plan has few columns
+// or few rows.  Such a side sums many entries into few duals, and a float rounding
+// of every tile's sum shows in them: nu of a plan of 4096 x 26 is 1.4 times as far
+// off after 500 iterations as with sweeps over blocks of eight rows, 0.96 times
 // here.  With at most half a tile's columns (`slim`) each has a whole word, for
 // the sum as a float and what that leaves out; with one tile row (`lone`) the
-// tile's sums are the totals and are taken as they are.  A float32 row's sum is
-// formed in float64 across the lanes and has a whole word too: a flat plan's
-// few rows sum as many entries.  In the other plans all this would cost 0.1 us
-// of 4.1 per iteration.
+// tile's sums are the totals and are taken as they are.  A lane's column sum is
+// float32 over four rows, not eight, and a row's sum is formed in float64 across
+// the lanes and has a whole word too: a flat plan's few rows sum as many entries.
+// It costs 0.6 us of 5.8 per iteration there, 0.9 of 9.7 at 16384 x 64, and would
+// cost the other plans 0.1 of 4.1.
 template <typename T, int RPW, int CL, bool FINE>
 __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* teams,
                                                                 const uint2* map, int64_t iters,
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   constexpr int MSG = WR + WC + kResScal;
   constexpr int GC = kResBlock / WC;         // peers read side by side, columns
   constexpr int GR = kResBlock / WR;         // and rows
-  constexpr int G = RPW < 8 ? RPW : 8;       // rows whose sums are folded together
+  constexpr int G = FINE || RPW < 8 ? 4 : 8;  // rows whose sums are folded together
   constexpr int kHeld = RPW - CL;            // rows with rho C in registers
   constexpr int kBuf = kResWaves * W > GC * W + GR * WR * PW ? kResWaves * W : GC * W + GR * WR * PW;
   // Row words in flight per thread: all of them for the usual team shapes.
@@ -1047,30 +1048,31 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   }
 }
 
-// Plans with few rows or columns, which have the smallest tiles.
+// Plans with few rows (one row of the smallest tiles) or columns (half a tile's).
 inline bool resident_fine(int64_t m, int64_t n) {
   return m <= kResWaves * kResRpw[0] || n <= kResBlock / 4;
 }
 
-template <typename T>
-const void* resident_entry(int rpw, bool fine) {
+template <typename T, bool FINE>
+const void* resident_entry(int rpw) {
   switch (rpw) {
-    case 4: return fine ? reinterpret_cast<const void*>(&resident_kernel<T, 4, 0, true>)
-                        : reinterpret_cast<const void*>(&resident_kernel<T, 4, 0, false>);
-    case 8: return reinterpret_cast<const void*>(&resident_kernel<T, 8, 0, false>);
-    case 16: return reinterpret_cast<const void*>(&resident_kernel<T, 16, 0, false>);
-    case 24: return reinterpret_cast<const void*>(&resident_kernel<T, 24, 0, false>);
-    case 32: return reinterpret_cast<const void*>(&resident_kernel<T, 32, 16, false>);
+    case 4: return reinterpret_cast<const void*>(&resident_kernel<T, 4, 0, FINE>);
+    case 8: return reinterpret_cast<const void*>(&resident_kernel<T, 8, 0, FINE>);
+    case 16: return reinterpret_cast<const void*>(&resident_kernel<T, 16, 0, FINE>);
+    case 24: return reinterpret_cast<const void*>(&resident_kernel<T, 24, 0, FINE>);
+    case 32: return reinterpret_cast<const void*>(&resident_kernel<T, 32, 16, FINE>);
   }
   return nullptr;
 }
 
 // Launch `blocks` workgroups of teams with `rpw` rows per wave.  Cooperative:
 // the workgroups wait for each other, so they have to be on the chip together.
-// `fine`: for teams with a plan that resident_fine() names, at the smallest rpw.
+// `fine`: one of them has a plan that resident_fine() names.
 hipError_t launch_resident(int dtype, int rpw, bool fine, const ResTeam* teams, const uint2* map,
                            int blocks, int64_t iters, int gate_polls, hipStream_t s) {
-  const void* f = dtype == 0 ? resident_entry<float>(rpw, fine) : resident_entry<double>(rpw, fine);
+  const void* f = dtype != 0 ? resident_entry<double, false>(rpw)
+                  : fine     ? resident_entry<float, true>(rpw)
+                             : resident_entry<float, false>(rpw);
   if (!f || blocks < 1) return hipErrorInvalidValue;
   void* args[] = {(void*)&teams, (void*)&map, (void*)&iters, (void*)&gate_polls};
   return hipLaunchCooperativeKernel(f, dim3((unsigned)blocks), dim3(kResBlock), args, 0, s);

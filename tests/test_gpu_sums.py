@@ -1,8 +1,9 @@
-"""Float32 sums of the streamed and of the coordinate and bfloat16 sweeps.  With
-zero cost and duals the first iteration leaves X as it is, so the duals after it
+"""Float32 sums of the streamed and of the coordinate and bfloat16 sweeps, and of
+plans with few columns on the chip.  With zero cost and duals the first iteration leaves X as it is, so the duals after it
 show what rounding did to the row and column sums.  That may not be more than in
 a plain schedule: strips of 256 columns (512 where the plan is cached), two row
-blocks of 16 per workgroup (one of 32 where cached), a lane's sum over its rows
+blocks of 16 per workgroup (one of 32 where cached, of 8 to 32 for few columns),
+a lane's sum over its rows
 or columns, the lanes' and waves' sums, all in float32, and float64 between
 workgroups -- worked out here with float32 tensors.  The margin of 2% is that of
 a root mean square over 5000 values and more (1%, one standard deviation)."""
@@ -79,3 +80,35 @@ def test_rounding_of_one_iteration(ctx, kind, m, n, rows, per, cols):
         print(f"[sums] rms {float(err):.3e}, plain {float(ref):.3e}, ratio {float(err / ref):.3f}",
               flush=True)
         assert err <= 1.02 * ref
+
+
+@pytest.mark.parametrize("m,n,rows", [(4096, 26, 8), (9216, 60, 16), (16384, 128, 32)])
+def test_rounding_of_few_columns_on_the_chip(ctx, m, n, rows):
+    """Of the column sums; every tile height from 16 rows per wave on.  Enough
+    plans for 2000 columns (their root mean square within 1.6%)."""
+    import torch
+    from paper_2110_11738_amd import drot
+    p, q = torch.full((m,), 1.0 / 32768, device="cuda"), torch.full((n,), 1.0 / 32768, device="cuda")
+    p[0] += 1 - p.double().sum().item()
+    q[0] += 1 - q.double().sum().item()
+    C = torch.zeros(m, n, device="cuda")
+    nu, errs, refs = torch.empty(n, dtype=torch.float64, device="cuda"), [], []
+    mu = torch.empty(m, dtype=torch.float64, device="cuda")
+    print(f"[sums] few columns {m}x{n}", flush=True)
+    for seed in range(2000 // n + 1):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        X0 = torch.rand(m, n, generator=g, device="cuda") * 0.5 + 0.5
+        X = X0.clone()
+        ctx.bind(C, p, q, X, drot.make_params(1.0, 0.0, 100, x0_mode=drot.X0_GIVEN))
+        ctx.iterate(1)
+        ctx.finish(mu, nu)
+        assert torch.equal(X, X0)
+        col = X0.double().sum(0)
+        err = (nu * m + col - q.double()) / 2
+        errs.append(err - err.mean())
+        ref = _plain_sums(torch.nn.functional.pad(X0, (0, 512 - n)), rows, 1, 512)[1][:n] - col
+        refs.append(ref - ref.mean())
+    err, ref = (torch.cat(v).square().mean().sqrt() for v in (errs, refs))
+    print(f"[sums] rms {float(err):.3e}, plain {float(ref):.3e}, ratio {float(err / ref):.3f}", flush=True)
+    assert err <= 1.02 * ref
