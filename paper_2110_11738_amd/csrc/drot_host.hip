@@ -686,6 +686,7 @@ extern "C" void drot_internal_counts(const drot_ctx* c, int64_t* out) {
   out[0] = c->n_res;
   out[1] = c->n_graph;
   out[2] = c->n_single;
+  out[3] = c->st_host->repeated;
 }
 
 extern "C" void drot_internal_rare(drot_ctx* c, int gate_polls, int64_t refuse_after) {

@@ -109,7 +109,8 @@ struct DevState {
   // --- final evaluation ---
   double f_pobj, f_dobj, f_rp, f_rd, f_gap, f_eps_p, f_eps_d, f_eps_g;
   // --- completion counter of the finishers (the last one does the scalars) ---
-  uint32_t counter, pad1;
+  uint32_t counter;
+  uint32_t repeated;        // iterations that resident launches repeated after a stop
 };
 
 // Geometry of one sweep launch.
@@ -254,7 +255,8 @@ hipError_t launch_prep_batch(const SweepArgs* args, int count, hipStream_t s);
 
 // For tests, which look them up in the library.  What a context has run since
 // it was created: out[0] resident launches, [1] graph replays, [2] iterations
-// launched singly.
+// launched singly; out[3] iterations of the bound problem repeated after a stop, as
+// of its state read last.
 extern "C" void drot_internal_counts(const struct drot_ctx* c, int64_t* out);
 // Conditions that are rare in use, from now on: how often a workgroup of a
 // resident launch polls for the others before giving up (0: it never waits),

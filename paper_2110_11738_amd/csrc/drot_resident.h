@@ -506,9 +506,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     sh.rec_k = sh.rec_done = sh.rec_status = 0;
   }
 
-  // The state is saved between segments of the launch (kResSaves says when),
-  // except where X's way to memory leads through LDS that holds rho C.
-  const bool saves = CL == 0 || (uni(tm->vec_x) && n % VEC == 0);
+  // The state is saved between segments of the launch (kResSaves says when).
   const int seg0 = R > 32 ? kResSaves[0] : kResSaves[1];
   bool replay = false;
   int base = 0, k = 0;  // iterations of this launch in the saved state, and done
@@ -530,16 +528,26 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     }
     if (!vec || n % VEC != 0) {  // the other chunks, element by element
       const int ne = vec && nvs == VEC ? 0 : nvs;
+      if constexpr (CL > 0) {  // the staging area holds rho C
+        T* const Xl = X + jl;
 #pragma unroll
-      for (int g = 0; g < RPW / SR; ++g) {
+        for (int r = 0; r < RPW; ++r)
+          if (ws0 + r < m)
 #pragma unroll
-        for (int u = 0; u < SR; ++u) store_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
+            for (int e = 0; e < VEC; ++e)
+              if (e < ne) Xl[(int64_t)(ws0 + r) * ldx + e] = xr[r][e];
+      } else {
+#pragma unroll
+        for (int g = 0; g < RPW / SR; ++g) {
+#pragma unroll
+          for (int u = 0; u < SR; ++u) store_chunk<T, VEC, false>(stage + u * W, xr[g * SR + u]);
 #pragma unroll 1
-        for (int u = 0; u < SR; ++u) {
-          const int i = ws0 + g * SR + u;
+          for (int u = 0; u < SR; ++u) {
+            const int i = ws0 + g * SR + u;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e)
-            if (i < m && e < ne) X[i * ldx + jl + e] = stage[u * W + e];
+            for (int e = 0; e < VEC; ++e)
+              if (i < m && e < ne) X[i * ldx + jl + e] = stage[u * W + e];
+          }
         }
       }
     }
@@ -709,7 +717,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     for (;;) {  // segments
     const int start = k;
     int end = limit;
-    if (saves && !replay) {
+    if (!replay) {
       const int64_t total = uni(sh.sv.iter) + k;
       const int len = total < seg0 ? seg0 : total < kResSaves[2] ? (int)total : kResSaves[2];
       if (limit - k > len) end = k + len;
@@ -1032,6 +1040,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     st->cpsi = sh.bc[k & 3][1];
     st->alpha = sh.bc[k & 3][2];
     st->iter = sh.sv.iter + k;
+    if (replay) st->repeated += (uint32_t)(k - base);
     st->t_last = now;
     st->pobj = sh.rec[0];
     st->dobj = sh.rec[1];

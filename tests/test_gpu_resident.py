@@ -199,3 +199,11 @@ def test_stop_after_saved_states(ctx, dtype, m, n):
         assert (a["iters"], a["status"], a["path"]) == (k, 0, 0) and b["iters"] == k
         for u, v in zip(x, y):
             assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("dtype,m,n", [("float32", 4000, 4000), ("float32", 4001, 4001),
+                                       ("float32", 4000, 4003), ("float64", 4000, 2047)])
+def test_stop_after_saved_states_in_the_tallest_tiles(ctx, dtype, m, n):
+    """32 rows per wave: half of rho C in LDS, which a save may not touch and a
+    repeat loads again."""
+    test_stop_after_saved_states(ctx, dtype, m, n)

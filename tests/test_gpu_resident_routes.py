@@ -23,8 +23,13 @@ def ctx():
 
 def _counts(ctx):
     """Resident launches, graph replays, iterations launched singly."""
+    return _all_counts(ctx)[:3]
+
+
+def _all_counts(ctx):
+    """The same, and iterations of the bound problem repeated after a stop."""
     from paper_2110_11738_amd import drot
-    out = (ctypes.c_int64 * 3)()
+    out = (ctypes.c_int64 * 4)()
     drot.lib().drot_internal_counts(ctx.handle, out)
     return np.array(out)
 
@@ -212,3 +217,26 @@ def test_products_beyond_the_element_type_take_sweeps(ctx, m, n, rho, cost):
                                   max_iter=20, ctx=ctx)
     assert rc == drot.MAXITER and all(r["iters"] == 20 for _, r, _, _ in outs)
     assert _counts(ctx)[0] - c0[0] == 1
+
+
+@pytest.mark.parametrize("dtype,m,n", [("float32", 4000, 4000), ("float32", 4001, 4001),
+                                       ("float32", 3999, 4003), ("float64", 4000, 2047),
+                                       ("float32", 3300, 3203)])
+def test_a_stop_repeats_no_more_than_since_a_saved_state(ctx, dtype, m, n):
+    """Whole and ragged widths, aligned rows and not, up to the tallest tiles: a
+    stop beyond 300 iterations repeats at most 256 and the two the test trails by."""
+    from paper_2110_11738_amd import drot
+    C, p, q, rho = _problem(m, n, dtype)
+    K = 700
+    X, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=K, ctx=ctx)
+    test = ctx.trace(1, K)[:, 5]
+    at = max(k for k in range(K) if k == 0 or test[k] < test[:k].min())
+    assert at > 300
+    c0 = _counts(ctx)
+    Y, res, mu2, nu2 = drot.solve(C, p, q, rho, tol=float(test[at]), max_iter=2000, ctx=ctx)
+    assert (res["iters"], res["status"]) == (at + 1, 0)
+    assert tuple(_counts(ctx) - c0) == (1, 0, 0)
+    print(f"[saved] {dtype} {m}x{n} stop at {at + 1}, {_all_counts(ctx)[3]} repeated", flush=True)
+    assert _all_counts(ctx)[3] <= 258
+    Z, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=at + 1, ctx=ctx)
+    _same((Y, mu2, nu2), (Z, mu, nu))
