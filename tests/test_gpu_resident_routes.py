@@ -240,3 +240,122 @@ def test_a_stop_repeats_no_more_than_since_a_saved_state(ctx, dtype, m, n):
     assert _all_counts(ctx)[3] <= 258
     Z, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=at + 1, ctx=ctx)
     _same((Y, mu2, nu2), (Z, mu, nu))
+
+
+@pytest.mark.parametrize("dtype,m,n", [
+    ("float32", 129, 129), ("float32", 32, 1025), ("float32", 1024, 255), ("float32", 1025, 257),
+    ("float32", 2080, 3840), ("float32", 4095, 4096), ("float32", 16500, 9), ("float32", 4096, 5),
+    ("float32", 12, 16640), ("float64", 65, 257), ("float64", 1100, 1030), ("float64", 2100, 2561),
+    ("float64", 4000, 2047), ("float64", 600, 26)])
+def test_shapes_that_run_on_the_chip(ctx, dtype, m, n):
+    """The shapes whose results tests/test_gpu_resident.py compares with the oracle."""
+    import torch
+    from paper_2110_11738_amd import drot
+    dt = getattr(torch, dtype)
+    p, q = (torch.full((k,), 1.0 / 32768, dtype=dt, device="cuda") for k in (m, n))
+    p[0] += 1 - p.double().sum().item()
+    q[0] += 1 - q.double().sum().item()
+    drot.solve(torch.rand(m, n, dtype=dt, device="cuda"), p, q, 1.0 / (m + n), tol=0.0, max_iter=12,
+               ctx=ctx)
+    assert tuple(_counts(ctx)) == (1, 0, 0)
+
+
+def test_a_captured_call_is_sweeps(ctx):
+    """iterate() into a capture, replayed between other work, then on-chip calls."""
+    import torch
+    from paper_2110_11738_amd import drot
+    C, p, q, rho = _problem(300, 700, "float64")
+
+    def run(capture):
+        X = torch.empty_like(C)
+        ctx.bind(C, p, q, X, drot.make_params(rho, 0.0, 1000))
+        states = []
+        if capture:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                ctx.iterate(40, stream=torch.cuda.current_stream())
+        for _ in range(3):
+            if capture:
+                g.replay()
+            else:
+                ctx.iterate(40)
+            torch.cuda.synchronize()
+            states.append(X.clone())
+            _ = torch.rand(1000, 1000, device="cuda") @ torch.rand(1000, 1000, device="cuda")
+        c0 = _counts(ctx)
+        if capture:
+            assert ctx.poll()[0] == 120
+            ctx.iterate(20)
+            assert tuple(_counts(ctx) - c0) == (1, 0, 0)
+            assert ctx.finish()["iters"] == 140
+        return states
+
+    _rare(ctx, refuse_after=0)
+    sweeps = run(False)
+    _rare(ctx)
+    c0 = _counts(ctx)
+    replayed = run(True)
+    assert tuple(_counts(ctx) - c0) == (1, 0, 40)  # recorded once
+    _same(replayed, sweeps)
+
+
+def test_two_threads_with_a_context_and_a_stream_each():
+    import threading
+    import torch
+    from paper_2110_11738_amd import drot
+    probs = [_problem(700, 300, "float32", 61), _problem(1300, 900, "float32", 62)]
+    want, got, errors = [None, None], [[], []], []
+    ctxs = [drot.Context(0), drot.Context(0)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+
+    def solve(k):
+        C, p, q, rho = probs[k]
+        X, res, mu, nu = drot.solve(C, p, q, rho, tol=0.0, max_iter=300, ctx=ctxs[k])
+        assert res["iters"] == 300
+        torch.cuda.current_stream().synchronize()
+        return X, mu, nu
+
+    for k in range(2):
+        want[k] = solve(k)
+    torch.cuda.synchronize()
+
+    def work(k):
+        try:
+            with torch.cuda.stream(streams[k]):
+                for _ in range(5):
+                    got[k].append(solve(k))
+        except Exception as e:
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for k in range(2):
+        assert _counts(ctxs[k])[0] == 6
+        for out in got[k]:
+            _same(out, want[k])
+        ctxs[k].close()
+
+
+def test_a_batch_whose_second_launch_is_refused(ctx):
+    """The launches before it have run; the sweeps take every problem on from
+    where it stands."""
+    from paper_2110_11738_amd import drot
+    probs = []
+    for k in range(12):
+        C, p, q, rho = _problem(1500, 1400, "float64", 70 + k)
+        probs.append(dict(C=C, p=p, q=q, rho=rho, tol=0.0))
+    rc, want = drot.solve_batched(probs, max_iter=50, ctx=ctx)
+    launches = _counts(ctx)[0]
+    assert launches > 1
+    _rare(ctx, refuse_after=1)
+    rc, outs = drot.solve_batched(probs, max_iter=50, ctx=ctx)
+    assert rc == drot.MAXITER and _counts(ctx)[0] == launches + 1
+    for (X, res, mu, nu), (X0, _, mu0, nu0) in zip(outs, want):
+        assert res["iters"] == 50
+        for a, b in ((X, X0), (mu, mu0), (nu, nu0)):  # float64: sums in another order
+            assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
