@@ -787,7 +787,8 @@ int drot_ctx_create(drot_ctx** out, int device) {
   memset(c->st_host, 0, sizeof(DevState));
   int coop = 0, cus = 0;
   if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) == hipSuccess && coop &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess)
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
+      resident_warm(std::min(cus, kResMaxTiles), c->cap_stream))
     c->cus = cus;
   (void)hipGetLastError();
   *out = c;

@@ -424,6 +424,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   __shared__ double accs[kResBlock];  // a_i, b_j of the thread's row or column
   __shared__ ResShared sh;
 
+  if (iters <= 0) return;  // see resident_warm(): nothing is there to be read
   const uint2 who = map ? map[blockIdx.x] : uint2{0u, blockIdx.x};
   const ResTeam* const tm = teams + uni((int)who.x);
   const int b = uni((int)who.y);
@@ -1085,6 +1086,16 @@ hipError_t launch_resident(int dtype, int rpw, bool fine, const ResTeam* teams, 
   if (!f || blocks < 1) return hipErrorInvalidValue;
   void* args[] = {(void*)&teams, (void*)&map, (void*)&iters, (void*)&gate_polls};
   return hipLaunchCooperativeKernel(f, dim3((unsigned)blocks), dim3(kResBlock), args, 0, s);
+}
+
+// A process's first cooperative launch sets up a queue, loads these kernels and
+// takes their scratch memory, 17 ms in all: an empty launch pays for it when a
+// context is made, not the first solve.  False where there are none.
+bool resident_warm(int blocks, hipStream_t s) {
+  for (int dtype = 0; dtype < 2; ++dtype)
+    if (launch_resident(dtype, kResRpw[4], false, nullptr, nullptr, blocks, 0, 0, s) != hipSuccess)
+      return false;
+  return hipStreamSynchronize(s) == hipSuccess;
 }
 
 }  // namespace

@@ -359,3 +359,36 @@ def test_a_batch_whose_second_launch_is_refused(ctx):
         assert res["iters"] == 50
         for a, b in ((X, X0), (mu, mu0), (nu, nu0)):  # float64: sums in another order
             assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
+
+
+FIRST = """
+import time, torch
+from paper_2110_11738_amd import drot
+ctx = drot.Context(0)
+C = torch.rand(517, 483, device="cuda")
+p, q = (torch.full((k,), 1.0 / 8192, device="cuda") for k in C.shape)
+p[0] += 1 - p.double().sum().item()
+q[0] += 1 - q.double().sum().item()
+ctx.bind(C, p, q, torch.empty_like(C), drot.make_params(1e-3, 0.0, 1000))
+torch.cuda.synchronize()
+for _ in range(3):
+    t = time.perf_counter()
+    ctx.iterate(20)
+    torch.cuda.synchronize()
+    print("took", time.perf_counter() - t, flush=True)
+"""
+
+
+def test_the_first_iterations_of_a_process_take_no_longer():
+    """What a process's first cooperative launch sets up (17 ms) is there with the
+    context."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", FIRST], cwd=root, capture_output=True, text=True,
+                         timeout=90)
+    assert out.returncode == 0, out.stderr
+    first, second, third = (float(l.split()[1]) for l in out.stdout.splitlines() if l.startswith("took"))
+    print(f"[first] {1e6 * first:.0f} us, then {1e6 * second:.0f} and {1e6 * third:.0f}", flush=True)
+    assert first < third + 5e-3
