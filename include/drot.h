@@ -350,8 +350,10 @@ typedef struct {
   const double *mu0, *nu0;  /* warm start (nullable, both or neither), as in drot_solve */
 } drot_problem;
 
-/* Solve `count` independent problems of any shapes together: every iteration
- * is one batched sweep launch, one batched aux launch over the (problem, work
+/* Solve `count` independent problems of any shapes together.  Problems that fit
+ * the chip take the resident path (drot_params) under the same conditions as
+ * alone, as many side by side in a launch as the compute units hold; then, for
+ * the others, every iteration is one batched sweep launch, one batched aux launch over the (problem, work
  * item) pairs of the problems still running and one finishing launch (one
  * wave per problem), replayed as hipGraphs of
  * params->check_every iterations.  Each problem runs Algorithm 1 with its own
@@ -360,8 +362,8 @@ typedef struct {
  * check_every, cache_mode, tile_rows, tile_chunks, tile_groups and
  * DROT_FLAG_NO_GRAPH; each problem's sweep schedule (rows per block, blocks
  * per work item) comes from the context's tuner cache for its size class
- * (drot_tune_batched) unless tile_rows / tile_groups set it.  outs[count] receives one result per
- * problem.  Returns DROT_OK when every problem met its test, DROT_MAXITER if
+ * (drot_tune_batched) unless tile_rows / tile_groups set it.  outs[count]
+ * receives one result per problem.  Returns DROT_OK when every problem met its test, DROT_MAXITER if
  * some hit max_iter, or an error (the message names the problem).  The call
  * uses the context's workspace and releases a problem bound by drot_bind. */
 int drot_solve_batched(drot_ctx *ctx, int32_t count, int dtype, const drot_problem *probs,
@@ -383,7 +385,9 @@ int drot_solve_batched(drot_ctx *ctx, int32_t count, int dtype, const drot_probl
  * graph, under the batch's cache policy.  The choices go to the context's
  * tuner cache, which drot_solve_batched consults (untuned: 2 chunks, 16-row
  * blocks, one per item; params->tile_chunks, tile_rows and tile_groups, when
- * set, override).  `table` (host, table_cap entries, may be NULL if
+ * set, override).  Problems that drot_solve_batched would run on the resident
+ * path with these params have no schedule: the stages leave them out, and where
+ * there are no others the cache stays as it is.  `table` (host, table_cap entries, may be NULL if
  * table_cap is 0) receives one entry per class present and *n_entries their
  * number.  The problems' X arrays are overwritten by the trials.  Blocks
  * until done. */
@@ -393,7 +397,8 @@ typedef struct {
   int32_t blocks_per_item;    /* chosen row blocks per sweep work item */
   int32_t problems;           /* problems of the class in the batch */
   int32_t chunks;             /* chosen 16-byte chunks per lane (whole batch) */
-  double us_per_iter;         /* the whole batch per iteration with the final choices */
+  double us_per_iter;         /* the whole batch per iteration with the final choices,
+                                 each problem on the path that the solver takes */
 } drot_batch_tile;
 
 int drot_tune_batched(drot_ctx *ctx, int32_t count, int dtype, const drot_problem *probs,

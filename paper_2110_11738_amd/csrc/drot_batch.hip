@@ -94,6 +94,15 @@ int tile_key(int dtype, bool stream, int64_t m, int64_t n) {
   return ((dtype * 2 + (stream ? 1 : 0)) * 6 + side_bucket(m)) * 6 + side_bucket(n);
 }
 
+// Whether a batch's problems that fit the chip take the resident iteration: the same
+// rules as for a single problem, the default schedule, graphs allowed, polls no
+// more often than every 32 iterations.
+bool chip_options(const drot_params& p) {
+  return !(p.flags & DROT_FLAG_NO_GRAPH) && p.tile_rows == 0 && p.tile_chunks == 0 &&
+         p.tile_groups == 0 && p.cache_mode == DROT_CACHE_AUTO &&
+         (p.check_every == 0 || p.check_every >= 32) && p.max_iter >= kResMinIters;
+}
+
 // Validation of a batch's arguments (before any device work).
 int validate_batch(int32_t count, int dtype, const drot_problem* probs, const drot_params* prm) {
   if (count < 1) return bfail(DROT_EINVAL, "count must be >= 1");
@@ -261,13 +270,9 @@ struct BatchRun {
     o += up(sizeof(uint2) * (size_t)max_sweep);
     off_aw = o;
     o += up(sizeof(uint2) * (size_t)max_aux);
-    // The same rules as for a single problem: default schedule, graphs
-    // allowed, polls no more often than every 32 iterations.
     fits.assign(count, 0);
     max_map = 0;
-    if (resident && !(prm.flags & DROT_FLAG_NO_GRAPH) && prm.tile_rows == 0 &&
-        prm.tile_chunks == 0 && prm.tile_groups == 0 && prm.cache_mode == DROT_CACHE_AUTO &&
-        (prm.check_every == 0 || prm.check_every >= 32) && prm.max_iter >= kResMinIters) {
+    if (resident && chip_options(prm)) {
       for (int b = 0; b < count; ++b) {
         int R = 0, S = 0;
         if (!drot_internal_resident_tiles(c, dtype, probs[b].m, probs[b].n, 32, &R, &S)) continue;
@@ -514,29 +519,40 @@ struct BatchRun {
     }
   }
 
+  // Plan the resident launches of the problems still running, for launch_all().
+  int plan_resident(hipStream_t s) {
+    plan_launches();
+    if (launches.empty()) return DROT_OK;
+    const int64_t n_map = launches.back().first + launches.back().blocks;
+    BHIP(hipMemcpyAsync(base + off_team, h_team, sizeof(ResTeam) * count, hipMemcpyHostToDevice, s));
+    BHIP(hipMemcpyAsync(base + off_map, h_map, sizeof(uint2) * n_map, hipMemcpyHostToDevice, s));
+    return DROT_OK;
+  }
+
+  // G iterations of those problems, without waiting.  1 when a launch is refused.
+  int launch_all(hipStream_t s, int G) {
+    const ResTeam* d_team = reinterpret_cast<const ResTeam*>(base + off_team);
+    const uint2* d_map = reinterpret_cast<const uint2*>(base + off_map);
+    for (const Launch& l : launches) {
+      if (!drot_internal_resident_stream(s, l.blocks)) return 1;
+      BHIP(hipMemsetAsync(base + off_sync, 0, sizeof(ResSync) * count, s));
+      BHIP(hipMemsetAsync(base + off_msg, 0xff,
+                          drot_internal_resident_bytes(dtype, l.rpw, l.blocks), s));
+      if (!drot_internal_resident_launch(c, dtype, l.rpw, l.fine, d_team, d_map + l.first, l.blocks, G,
+                                         s))
+        return 1;
+    }
+    return DROT_OK;
+  }
+
   // Resident launches of up to G iterations until every problem that fits has
   // stopped.  Returns 1 when a launch is refused (the rest goes to the sweeps).
   int run_resident(hipStream_t s, int G) {
-    const ResTeam* d_team = reinterpret_cast<const ResTeam*>(base + off_team);
-    const uint2* d_map = reinterpret_cast<const uint2*>(base + off_map);
     bool changed = true;
     for (;;) {
-      if (changed) {
-        plan_launches();
-        if (launches.empty()) return DROT_OK;
-        const int64_t n_map = launches.back().first + launches.back().blocks;
-        BHIP(hipMemcpyAsync(base + off_team, h_team, sizeof(ResTeam) * count, hipMemcpyHostToDevice, s));
-        BHIP(hipMemcpyAsync(base + off_map, h_map, sizeof(uint2) * n_map, hipMemcpyHostToDevice, s));
-      }
-      for (const Launch& l : launches) {
-        if (!drot_internal_resident_stream(s, l.blocks)) return 1;
-        BHIP(hipMemsetAsync(base + off_sync, 0, sizeof(ResSync) * count, s));
-        BHIP(hipMemsetAsync(base + off_msg, 0xff,
-                            drot_internal_resident_bytes(dtype, l.rpw, l.blocks), s));
-        if (!drot_internal_resident_launch(c, dtype, l.rpw, l.fine, d_team, d_map + l.first, l.blocks, G,
-                                           s))
-          return 1;
-      }
+      int rc = changed ? plan_resident(s) : DROT_OK;
+      if (rc || launches.empty()) return rc;
+      if ((rc = launch_all(s, G))) return rc;
       BHIP(hipMemcpyAsync(h_st, base, SS * count, hipMemcpyDeviceToHost, s));
       BHIP(hipStreamSynchronize(s));
       changed = false;
@@ -642,6 +658,31 @@ extern "C" int drot_solve_batched(drot_ctx* c, int32_t count, int dtype, const d
 
 namespace {
 
+// Time `iters` iterations of problems that take the resident iteration (after as
+// many to warm up).  `us_per_iter` stays 0 where none does or a launch is refused.
+int time_resident(drot_ctx* c, int32_t count, int dtype, const drot_problem* probs,
+                  const drot_params* trial, int64_t iters, hipStream_t s, hipEvent_t e0,
+                  hipEvent_t e1, double* us_per_iter) {
+  *us_per_iter = 0.0;
+  if (count < 1) return DROT_OK;
+  BatchRun r;
+  int rc = r.setup(c, count, dtype, probs, trial, -1, 0, 0, 0, true);
+  if (!rc) rc = r.init(s);
+  if (!rc && r.res) rc = r.plan_resident(s);
+  if (rc || r.launches.empty()) return rc;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1) BHIP(hipEventRecord(e0, s));
+    for (int64_t k = 0; k < iters; k += 1024)
+      if ((rc = r.launch_all(s, (int)std::min<int64_t>(1024, iters - k)))) return rc < 0 ? rc : DROT_OK;
+  }
+  float ms = 0.f;
+  BHIP(hipEventRecord(e1, s));
+  BHIP(hipEventSynchronize(e1));
+  BHIP(hipEventElapsedTime(&ms, e0, e1));
+  *us_per_iter = ms * 1e3 / (double)iters;
+  return DROT_OK;
+}
+
 // Time `groups` graph replays of G iterations of the batch (after one warm
 // replay) with the schedules the context's cache holds.
 int time_batch(drot_ctx* c, int32_t count, int dtype, const drot_problem* probs,
@@ -681,20 +722,29 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
   // The cache policy of the whole batch (the schedules are tuned under it).
   const size_t es = dtype == DROT_F32 ? 4 : 8;
   double total_bytes = 0;
-  std::vector<double> class_entries(36, 0.0);
+  std::vector<double> class_entries(36, 0.0);  // of the problems that are swept
   std::vector<int> class_count(36, 0);
+  auto class_of = [](const drot_problem& P) { return side_bucket(P.m) * 6 + side_bucket(P.n); };
   for (int b = 0; b < count; ++b) {
     total_bytes += 2.0 * (double)probs[b].m * (double)probs[b].n * (double)es;
-    const int k = side_bucket(probs[b].m) * 6 + side_bucket(probs[b].n);
-    class_entries[k] += (double)probs[b].m * (double)probs[b].n;
-    class_count[k] += 1;
+    class_count[class_of(probs[b])] += 1;
   }
   const bool stream_mode = prm->cache_mode == DROT_CACHE_STREAM ||
                            (prm->cache_mode == DROT_CACHE_AUTO && total_bytes > 192.0 * 1024 * 1024);
   const int base_key = (dtype * 2 + (stream_mode ? 1 : 0)) * 36;
-  // Fixed iteration counts: every problem's tolerance 0.
-  std::vector<drot_problem> ps(probs, probs + count);
-  for (auto& P : ps) P.tol = 0.0;
+  // Fixed iteration counts: every problem's tolerance 0.  `ps`: the problems that
+  // the solver sweeps under these parameters, `on_chip` those that it does not.
+  std::vector<drot_problem> ps, on_chip;
+  const bool chip = chip_options(*prm) &&
+                    drot_internal_resident_stream(s, drot_internal_resident_cap(c));
+  for (int b = 0; b < count; ++b) {
+    int R = 0, S = 0;
+    auto& to = chip && drot_internal_resident_tiles(c, dtype, probs[b].m, probs[b].n, 32, &R, &S)
+                   ? on_chip : ps;
+    to.push_back(probs[b]);
+    to.back().tol = 0.0;
+  }
+  for (const auto& P : ps) class_entries[class_of(P)] += (double)P.m * (double)P.n;
   drot_params trial = *prm;
   trial.tol_mode = DROT_TOL_ABSOLUTE;
   trial.max_iter = (int64_t)(groups + 2) * G + 1;
@@ -702,6 +752,12 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
   trial.tile_rows = 0;
   trial.tile_groups = 0;
   trial.tile_chunks = 0;
+  if (!on_chip.empty() && !ps.empty()) {  // the data checks, by the problems' own numbers
+    BatchRun r;
+    rc = r.setup(c, count, dtype, probs, &trial, stream_mode ? 1 : 0, 0, 0);
+    if (!rc) rc = r.init(s);
+    if (rc) return rc;
+  }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   BHIP(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -716,15 +772,16 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
   static const int kRows[] = {8, 16, 32};
   static const int kPer1[] = {1, 2};
   double best = -1.0;
-  int best_ch = 2, best_rows = 16, best_per = 1;
+  const int had_ch = drot_internal_batch_chunks(c, dtype * 2 + (stream_mode ? 1 : 0));
+  int best_ch = had_ch > 0 ? had_ch : 2, best_rows = 16, best_per = 1;
   for (int ch : kChunks)
     for (int rows : kRows)
       for (int per : kPer1) {
-        if (rc) break;
+        if (rc || ps.empty()) break;
         set_all(rows, per);
         drot_internal_set_batch_chunks(c, dtype * 2 + (stream_mode ? 1 : 0), ch);
         double us = 0.0;
-        rc = time_batch(c, count, dtype, ps.data(), &trial, stream_mode ? 1 : 0, G, groups, s, e0,
+        rc = time_batch(c, (int32_t)ps.size(), dtype, ps.data(), &trial, stream_mode ? 1 : 0, G, groups, s, e0,
                         e1, &us);
         if (!rc && (best < 0 || us < best)) {
           best = us;
@@ -733,15 +790,17 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
           best_per = per;
         }
       }
-  set_all(best_rows, best_per);
-  drot_internal_set_batch_chunks(c, dtype * 2 + (stream_mode ? 1 : 0), best_ch);
+  if (!ps.empty()) {
+    set_all(best_rows, best_per);
+    drot_internal_set_batch_chunks(c, dtype * 2 + (stream_mode ? 1 : 0), best_ch);
+  }
   // Stage 2: each class holding at least 5% of the entries, largest first,
   // with the others fixed; a change is kept when it is 1% faster.
   std::vector<int> order;
   double all_entries = 0;
   for (int k = 0; k < 36; ++k) all_entries += class_entries[k];
   for (int k = 0; k < 36; ++k)
-    if (class_entries[k] >= 0.05 * all_entries) order.push_back(k);
+    if (class_entries[k] > 0 && class_entries[k] >= 0.05 * all_entries) order.push_back(k);
   std::sort(order.begin(), order.end(),
             [&](int x, int y) { return class_entries[x] > class_entries[y]; });
   static const int kPer2[] = {1, 2, 4};
@@ -753,7 +812,7 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
         if (rc || (rows == cur_rows && per == cur_per)) continue;
         drot_internal_set_batch_tile(c, base_key + k, rows, per);
         double us = 0.0;
-        rc = time_batch(c, count, dtype, ps.data(), &trial, stream_mode ? 1 : 0, G, groups, s, e0,
+        rc = time_batch(c, (int32_t)ps.size(), dtype, ps.data(), &trial, stream_mode ? 1 : 0, G, groups, s, e0,
                         e1, &us);
         if (!rc && us < 0.99 * best) {
           best = us;
@@ -763,14 +822,22 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
         drot_internal_set_batch_tile(c, base_key + k, cur_rows, cur_per);
       }
   }
+  double chip_us = 0.0;
+  if (!rc) {
+    drot_params t = trial;
+    t.max_iter = 2 * iters + 1;
+    rc = time_resident(c, (int32_t)on_chip.size(), dtype, on_chip.data(), &t, iters, s, e0, e1,
+                       &chip_us);
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
+  best = std::max(best, 0.0) + chip_us;
   int32_t entries = 0;
   for (int k = 0; k < 36; ++k) {
     if (!class_count[k]) continue;
     if (entries < table_cap) {
-      int rows = 0, per = 0;
+      int rows = 16, per = 1;  // untuned
       drot_internal_batch_tile(c, base_key + k, &rows, &per);
       drot_batch_tile& t = table[entries];
       t.m_class = k / 6;

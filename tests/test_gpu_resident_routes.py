@@ -361,6 +361,34 @@ def test_a_batch_whose_second_launch_is_refused(ctx):
             assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
 
 
+def test_batch_tuner_times_what_the_solver_runs(ctx):
+    """Problems on the chip have no schedule to choose: the tuner times their
+    launches, leaves the cache alone and tunes the others."""
+    from paper_2110_11738_amd import drot
+    fit = [dict(zip("Cpq", _problem(k, 700, "float32", 80)[:3]), rho=1e-3, tol=0.0)
+           for k in (300, 600, 900)]
+    table = drot.tune_batched(fit, iters=64, ctx=ctx)
+    launches, _, _ = _counts(ctx)
+    assert launches == 2  # one to warm up, one timed
+    assert sum(t["problems"] for t in table) == 3
+    for t in table:  # untuned
+        assert (t["tile_rows"], t["blocks_per_item"], t["chunks"]) == (16, 1, 2)
+        assert t["us_per_iter"] > 0
+    drot.tune_batched(fit, iters=64, check_every=16, ctx=ctx)  # swept
+    assert _counts(ctx)[0] == launches
+    big = dict(zip("Cpq", _problem(4500, 4400, "float32", 81)[:3]), rho=1e-4, tol=0.0)
+    table = drot.tune_batched(fit + [big], iters=32, ctx=ctx)
+    assert _counts(ctx)[0] == launches + 2
+    assert sum(t["problems"] for t in table) == 4
+    t = [t for t in table if (t["m_class"], t["n_class"]) == (5, 5)][0]
+    assert t["tile_rows"] in (8, 16, 32) and t["blocks_per_item"] in (1, 2, 4) and t["chunks"] in (1, 2)
+    rc, outs = drot.solve_batched(fit + [big], max_iter=40, ctx=ctx)
+    assert rc == drot.MAXITER and all(r["iters"] == 40 for _, r, _, _ in outs)
+    bad = dict(fit[2], p=fit[2]["p"] * 2)
+    with pytest.raises(drot.DrotError, match="problem 2:"):
+        drot.tune_batched([big, fit[0], bad], iters=32, ctx=ctx)
+
+
 FIRST = """
 import time, torch
 from paper_2110_11738_amd import drot
