@@ -738,145 +738,145 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, const int ct, con
 
   // One row block; the policy says whether its accesses are nontemporal.
   auto block = [&](int64_t rb, auto policy) {
-  constexpr bool STREAM = decltype(policy)::value;
-  const int64_t row0 = rb * a.g.rows;
-  const int64_t rowE = row0 + a.g.rows < m ? row0 + a.g.rows : m;
-  const int64_t rw0 = row0 + (int64_t)wave * rpw;
-  const int64_t rw1 = rw0 + rpw < rowE ? rw0 + rpw : rowE;
-  for (int64_t i0 = rw0; i0 < rw1; i0 += U) {
-    T xv[U][CH][VEC], cv[U][CH][VEC];
-    float xsr[U][DD];
+    constexpr bool STREAM = decltype(policy)::value;
+    const int64_t row0 = rb * a.g.rows;
+    const int64_t rowE = row0 + a.g.rows < m ? row0 + a.g.rows : m;
+    const int64_t rw0 = row0 + (int64_t)wave * rpw;
+    const int64_t rw1 = rw0 + rpw < rowE ? rw0 + rpw : rowE;
+    for (int64_t i0 = rw0; i0 < rw1; i0 += U) {
+      T xv[U][CH][VEC], cv[U][CH][VEC];
+      float xsr[U][DD];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + u;
-      if (i < rw1) {
-        if constexpr (CM == kCostCoords)
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + u;
+        if (i < rw1) {
+          if constexpr (CM == kCostCoords)
 #pragma unroll
-          for (int d = 0; d < D; ++d) xsr[u][d] = a.xs[i * D + d];
+            for (int d = 0; d < D; ++d) xsr[u][d] = a.xs[i * D + d];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          if (ok[c]) {
-            if constexpr (kReadC && CM == kCostDense)
-              load_chunk<T, VEC, STREAM>(C + i * a.g.ldc + jc[c], cv[u][c]);
-            if constexpr (kReadC && CM == kCostBF16)
-              load_bf16<VEC, STREAM>(Cb + i * a.g.ldc + jc[c], cv[u][c]);
-            if (kReadX) load_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], xv[u][c]);
-          }
-        }
-      }
-    }
-    // c_ij as the storage type sees it.
-    auto cost = [&](int u, int c, int e) -> T {
-      if constexpr (CM == kCostCoords) {
-        float s = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          const float df = xsr[u][d] - xtl[c][e][d];
-          s += df * df;
-        }
-        return (T)(s * cscale);
-      } else {
-        return cv[u][c][e];
-      }
-    };
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + u;
-      if (i < rw1) {
-        A rowv = 0;
-        if (is_iter(MODE)) rowv = static_cast<const T*>(a.phiT)[i] + shift;
-        if (is_final(MODE)) rowv = a.phi64[i] + (double)shift;
-        if (MODE == kInitPQ) rowv = static_cast<const T*>(a.p)[i];
-        L rsum, rsum0;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          if (kTwoSums && c == 1) {
-            rsum0 = rsum;
-            rsum = L{};
-          }
-          if (ok[c]) {
-            T outv[VEC];
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-              A x = 0;
-              if (RAGGED && e >= nv[c]) {
-                // beyond column n (padding): contributes nothing, never stored
-                outv[e] = (T)0;
-              } else if constexpr (MODE == kIterB) {
-                // X_{k+2} = [W + phi_i + psi_j]_+ with W = X_{k+1} - rho C.
-                const A y = (A)xv[u][c][e] + (rowv + colv[c][e]);
-                x = y > (A)0 ? y : (A)0;
-                outv[e] = (T)x;
-              } else if constexpr (is_iter(MODE) || is_final(MODE)) {
-                const A cij = (A)cost(u, c, e);
-                const A pc = is_final(MODE) ? rho * cij : mul_rounded<A>(rho, cij);
-                const A t = rowv + colv[c][e] - pc;
-                const A tp = t > (A)0 ? t : (A)0;
-                s1.add(tp * tp);
-                if constexpr (MODE == kFinalW) {
-                  // Restore X from W in the stored type, with the product the
-                  // C-reading iteration subtracted.
-                  const T pcT = mul_rounded<T>(rhoT, cv[u][c][e]);
-                  const T xr = xv[u][c][e] + pcT;
-                  outv[e] = xr;
-                  x = (A)xr;
-                } else if constexpr (MODE == kFinal) {
-                  x = (A)xv[u][c][e];
-                } else {
-                  const A y = (A)xv[u][c][e] + t;
-                  x = y > (A)0 ? y : (A)0;
-                  outv[e] = MODE == kIterA ? (T)(x - pc) : (T)x;
-                }
-                s0.add(cij * x);
-              } else {
-                const A cij = (A)cost(u, c, e);
-                if (MODE == kInitPQ) x = rowv * colv[c][e];
-                else x = (A)xv[u][c][e];
-                s0.add((double)cij * (double)cij);
-                const bool bad = !finite_d((double)cij) || !finite_d((double)x) ||
-                                 (MODE == kInitX && x < (A)0);
-                s1.add(bad ? (P)1 : (P)0);
-                outv[e] = (T)x;
-              }
-              rsum.add(x);
-              colacc[c][e].add(x);
-            }
-            if (kWriteX) {
-              if (!RAGGED || nv[c] == VEC) {
-                store_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], outv);
-              } else {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                  if (e < nv[c]) X[i * a.g.ldx + jc[c] + e] = outv[e];
-              }
+          for (int c = 0; c < CH; ++c) {
+            if (ok[c]) {
+              if constexpr (kReadC && CM == kCostDense)
+                load_chunk<T, VEC, STREAM>(C + i * a.g.ldc + jc[c], cv[u][c]);
+              if constexpr (kReadC && CM == kCostBF16)
+                load_bf16<VEC, STREAM>(Cb + i * a.g.ldc + jc[c], cv[u][c]);
+              if (kReadX) load_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], xv[u][c]);
             }
           }
         }
-        const P tot = wave_sum(rsum.get());
-        if constexpr (kTwoSums) {
-          const P tot0 = wave_sum(rsum0.get());
-          if (lane < 2) rowpart[(2 * (int64_t)ct + lane) * m + i] = lane == 0 ? tot0 : tot;
+      }
+      // c_ij as the storage type sees it.
+      auto cost = [&](int u, int c, int e) -> T {
+        if constexpr (CM == kCostCoords) {
+          float s = 0.f;
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            const float df = xsr[u][d] - xtl[c][e][d];
+            s += df * df;
+          }
+          return (T)(s * cscale);
         } else {
-          if (lane == 0) rowpart[(int64_t)ct * m + i] = tot;
+          return cv[u][c][e];
+        }
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + u;
+        if (i < rw1) {
+          A rowv = 0;
+          if (is_iter(MODE)) rowv = static_cast<const T*>(a.phiT)[i] + shift;
+          if (is_final(MODE)) rowv = a.phi64[i] + (double)shift;
+          if (MODE == kInitPQ) rowv = static_cast<const T*>(a.p)[i];
+          L rsum, rsum0;
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            if (kTwoSums && c == 1) {
+              rsum0 = rsum;
+              rsum = L{};
+            }
+            if (ok[c]) {
+              T outv[VEC];
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                A x = 0;
+                if (RAGGED && e >= nv[c]) {
+                  // beyond column n (padding): contributes nothing, never stored
+                  outv[e] = (T)0;
+                } else if constexpr (MODE == kIterB) {
+                  // X_{k+2} = [W + phi_i + psi_j]_+ with W = X_{k+1} - rho C.
+                  const A y = (A)xv[u][c][e] + (rowv + colv[c][e]);
+                  x = y > (A)0 ? y : (A)0;
+                  outv[e] = (T)x;
+                } else if constexpr (is_iter(MODE) || is_final(MODE)) {
+                  const A cij = (A)cost(u, c, e);
+                  const A pc = is_final(MODE) ? rho * cij : mul_rounded<A>(rho, cij);
+                  const A t = rowv + colv[c][e] - pc;
+                  const A tp = t > (A)0 ? t : (A)0;
+                  s1.add(tp * tp);
+                  if constexpr (MODE == kFinalW) {
+                    // Restore X from W in the stored type, with the product the
+                    // C-reading iteration subtracted.
+                    const T pcT = mul_rounded<T>(rhoT, cv[u][c][e]);
+                    const T xr = xv[u][c][e] + pcT;
+                    outv[e] = xr;
+                    x = (A)xr;
+                  } else if constexpr (MODE == kFinal) {
+                    x = (A)xv[u][c][e];
+                  } else {
+                    const A y = (A)xv[u][c][e] + t;
+                    x = y > (A)0 ? y : (A)0;
+                    outv[e] = MODE == kIterA ? (T)(x - pc) : (T)x;
+                  }
+                  s0.add(cij * x);
+                } else {
+                  const A cij = (A)cost(u, c, e);
+                  if (MODE == kInitPQ) x = rowv * colv[c][e];
+                  else x = (A)xv[u][c][e];
+                  s0.add((double)cij * (double)cij);
+                  const bool bad = !finite_d((double)cij) || !finite_d((double)x) ||
+                                   (MODE == kInitX && x < (A)0);
+                  s1.add(bad ? (P)1 : (P)0);
+                  outv[e] = (T)x;
+                }
+                rsum.add(x);
+                colacc[c][e].add(x);
+              }
+              if (kWriteX) {
+                if (!RAGGED || nv[c] == VEC) {
+                  store_chunk<T, VEC, STREAM>(X + i * a.g.ldx + jc[c], outv);
+                } else {
+#pragma unroll
+                  for (int e = 0; e < VEC; ++e)
+                    if (e < nv[c]) X[i * a.g.ldx + jc[c] + e] = outv[e];
+                }
+              }
+            }
+          }
+          const P tot = wave_sum(rsum.get());
+          if constexpr (kTwoSums) {
+            const P tot0 = wave_sum(rsum0.get());
+            if (lane < 2) rowpart[(2 * (int64_t)ct + lane) * m + i] = lane == 0 ? tot0 : tot;
+          } else {
+            if (lane == 0) rowpart[(int64_t)ct * m + i] = tot;
+          }
         }
       }
-    }
-    if constexpr (kWiden) {
-      // nothing of the next rows in here: it would cost a wave per SIMD
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (kWiden) {
+        // nothing of the next rows in here: it would cost a wave per SIMD
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          sm[wave * W + slot(c, e, lane)] += (S)colacc[c][e].get();
-          colacc[c][e] = L{};
-        }
-      s0d += (double)s0.get();
-      s1d += (double)s1.get();
-      s0 = s1 = L{};
-      __builtin_amdgcn_sched_barrier(0);
+          for (int e = 0; e < VEC; ++e) {
+            sm[wave * W + slot(c, e, lane)] += (S)colacc[c][e].get();
+            colacc[c][e] = L{};
+          }
+        s0d += (double)s0.get();
+        s1d += (double)s1.get();
+        s0 = s1 = L{};
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-  }
   };
   for (int64_t rb = rg; rb < a.g.n_rb; rb += a.g.n_rg) {
     if constexpr (NT && !KC) {

@@ -84,7 +84,6 @@ __host__ __device__ inline bf16 to_bf16(float f) {
 // Requires M % 32 == N % 64 == ks % 32 == 0, leading dimensions multiples of 8
 // and 16-byte aligned operands (checked on the host).
 // ---------------------------------------------------------------------------
-typedef short v8s __attribute__((ext_vector_type(8)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -96,15 +95,15 @@ constexpr int kColSlices = 16;       // row classes of a bias gradient
 // What happens to a product.
 enum Epi : int {
   kEpiStore = 0,  // C
-  kEpiLayer = 1,  // + bias, ReLU if `relu`: C, its bfloat16 copy and (CbT) that transposed
+  kEpiLayer = 1,  // + bias, ReLU if `relu`: C, its bfloat16 copy (Cb) and (CbT) that transposed
   kEpiGate = 2,   // kept where gate > 0, zero elsewhere: the same three
   kEpiError = 3   // + bias: y in C; d = 2 (y - t) / count in D, Cb and CbT; sum (y - t)^2 in `part`
 };
 
 struct Job {
-  const void* A;  // M x K bfloat16 (float32 in the first step), leading dimension lda
-  const bf16* B;  // N x K (or K x N), leading dimension ldb
-  float* C;       // M x N, leading dimension N
+  const void* A;  // M x K bfloat16 (float32 in the first step)
+  const bf16* B;  // N x K (or K x N)
+  float* C;       // M x N; every matrix is contiguous
   bf16 *Cb, *CbT;
   const float *bias, *gate, *t;
   float* D;
@@ -313,8 +312,10 @@ __device__ __forceinline__ double finish(const Job& j, int row, int col, float v
   }
   if constexpr (EPI != kEpiStore) {
     const uint32_t both = round2(v[0], v[1]);
-    j.Cb[o] = (bf16)both;
-    j.Cb[o + j.N] = (bf16)(both >> 16);
+    if (j.Cb) {
+      j.Cb[o] = (bf16)both;
+      j.Cb[o + j.N] = (bf16)(both >> 16);
+    }
     if (j.CbT) *reinterpret_cast<uint32_t*>(j.CbT + (size_t)col * j.M + row) = both;
   }
   return err;
@@ -544,8 +545,8 @@ struct drot_mlp {
   float* m1 = nullptr;
   float* m2 = nullptr;
   float* a[3] = {};  // activations (layer outputs)
-  bf16 *ab[3] = {}, *xb = nullptr;    // bfloat16 copies
-  bf16 *abt[3] = {}, *xbt = nullptr;  // and their transposes (of the last layer: none)
+  bf16 *ab[3] = {}, *xb = nullptr;    // bfloat16 copies (of the last layer: none)
+  bf16 *abt[3] = {}, *xbt = nullptr;  // and their transposes
   float* d[3] = {};  // gradients with respect to the pre-activations
   bf16 *db[3] = {}, *dbt[3] = {};
   double* part = nullptr;  // the loss's partial sums
@@ -620,7 +621,7 @@ int forward(drot_mlp* n, int B, const float* x, float* y, const float* t, hipStr
       j.CbT = n->dbt[2];
       j.part = n->part;
     } else {
-      j.Cb = n->ab[l];
+      j.Cb = l < 2 ? n->ab[l] : nullptr;
       j.CbT = t ? n->abt[l] : nullptr;
     }
     const dim3 grid(j.wgs + (l == 0 && t ? (B / 64) * (K / 64) : 0)), block(64 * waves);
@@ -732,7 +733,7 @@ int drot_mlp_create(drot_mlp** out, int device, int in, int hidden, int outd, in
     for (int l = 0; l < 3; ++l) {
       const size_t c = (size_t)max_batch * layer_out(n, l);
       place(&n->a[l], c);
-      place(&n->ab[l], c);
+      place(&n->ab[l], l == 2 ? 0 : c);
       place(&n->abt[l], l == 2 ? 0 : c);
       place(&n->d[l], c);
       place(&n->db[l], c);

@@ -716,297 +716,297 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
 
     k = base;
     for (;;) {  // segments
-    const int start = k;
-    int end = limit;
-    if (!replay) {
-      const int64_t total = uni(sh.sv.iter) + k;
-      const int len = total < seg0 ? seg0 : total < kResSaves[2] ? (int)total : kResSaves[2];
-      if (limit - k > len) end = k + len;
-    }
-    while (k < end) {  // sweep iteration k + 1, exchange, steps 5-8
-      const Msg cur = xch + (seq & 3) * phase;
-      // Step 4 on the held entries, with the row and column sums of step 5
-      // and the stopping-test sums.  A lane's float32 sums run over at most
-      // 8 rows; from there on everything is float64.
-      {
-        const int lane = fresh_lane(tid) & (kWave - 1);
-        const T shift = (T)(sh.bc[k & 3][0] + sh.bc[k & 3][1]);
-        T* const held = cl + (wave * SR * kWave + lane) * VEC;
-        T colv[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) colv[e] = colsh[lane * VEC + e];
-        double cd[VEC], s0d = 0.0, s1d = 0.0, rtot = 0.0;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) cd[e] = 0.0;
-#pragma unroll
-        for (int g = 0; g < RPW / G; ++g) {
-          T ca[VEC], s0 = (T)0, s1 = (T)0;
-          RowSum rs[G];
-#pragma unroll
-          for (int u = 0; u < G; ++u) {
-            const int r = g * G + u;
-            const T rowv = rowsh[wave * RPW + r] + shift;
-            T c[VEC];
-            if (r < kHeld) {
-#pragma unroll
-              for (int e = 0; e < VEC; ++e) c[e] = pc[r < kHeld ? r : 0][e];
-            } else {
-              load_chunk<T, VEC, false>(held + (r - kHeld) * W, c);
-            }
-            T rsum = (T)0;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-              const T t = rowv + colv[e] - c[e];
-              const T tp = relu_of(t);
-              s1 += tp * tp;
-              const T x = relu_of(xr[r][e] + t);
-              xr[r][e] = x;
-              rsum = e == 0 ? x : rsum + x;
-              ca[e] = u == 0 ? x : ca[e] + x;
-              s0 += c[e] * x;
-            }
-            rs[u] = (RowSum)rsum;
-          }
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) cd[e] += (double)ca[e];
-          s0d += (double)s0;
-          s1d += (double)s1;
-          const RowSum v = wave_fold(rs, lane);
-          rowp[wave * RPW + g * G + lane / (kWave / G)] = v;  // its 64 / G lanes agree
-          rtot += (double)v;
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) buf[wave * W + lane * VEC + e] = cd[e];
-        // rtot holds G distinct values, each in 64 / G neighbouring lanes
-        if (G == 8) rtot += dpp<0x128>(rtot);
-        rtot += dpp<0x142, 0xA>(rtot);
-        rtot += dpp<0x143, 0xC>(rtot);
-        double sx = fold32(s0d, s1d);  // lanes < 32: s0, others: s1
-        sx += dpp<0xB1>(sx);
-        sx += dpp<0x4E>(sx);
-        sx += dpp<0x141>(sx);
-        sx += dpp<0x140>(sx);
-        sx += dpp<0x142, 0xA>(sx);
-        if (lane == 63) {
-          sh.wsum[0][wave] = rtot;
-          sh.wsum[2][wave] = sx;
-        }
-        if (lane == 31) sh.wsum[1][wave] = sx;
+      const int start = k;
+      int end = limit;
+      if (!replay) {
+        const int64_t total = uni(sh.sv.iter) + k;
+        const int len = total < seg0 ? seg0 : total < kResSaves[2] ? (int)total : kResSaves[2];
+        if (limit - k > len) end = k + len;
       }
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-
-      // Publish, then clear the words for the step after the next.
-      double own[PW];
+      while (k < end) {  // sweep iteration k + 1, exchange, steps 5-8
+        const Msg cur = xch + (seq & 3) * phase;
+        // Step 4 on the held entries, with the row and column sums of step 5
+        // and the stopping-test sums.  A lane's float32 sums run over at most
+        // 8 rows; from there on everything is float64.
+        {
+          const int lane = fresh_lane(tid) & (kWave - 1);
+          const T shift = (T)(sh.bc[k & 3][0] + sh.bc[k & 3][1]);
+          T* const held = cl + (wave * SR * kWave + lane) * VEC;
+          T colv[VEC];
 #pragma unroll
-      for (int e = 0; e < PW; ++e) own[e] = 0.0;
-      {
-        const int t = fresh_lane(tid);
-        const Msg dst = word_at(cur, 8 * b * MSG);
-        const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
-        if (wave < WC / kWave) {
-          double v[PW];
-          const double* const src = buf + (slim ? t : t * PW);
+          for (int e = 0; e < VEC; ++e) colv[e] = colsh[lane * VEC + e];
+          double cd[VEC], s0d = 0.0, s1d = 0.0, rtot = 0.0;
 #pragma unroll
-          for (int e = 0; e < PW; ++e) v[e] = src[e];
+          for (int e = 0; e < VEC; ++e) cd[e] = 0.0;
 #pragma unroll
-          for (int q = 1; q < kResWaves; ++q)
+          for (int g = 0; g < RPW / G; ++g) {
+            T ca[VEC], s0 = (T)0, s1 = (T)0;
+            RowSum rs[G];
 #pragma unroll
-            for (int e = 0; e < PW; ++e) v[e] += src[q * W + e];
-          if (lone)
+            for (int u = 0; u < G; ++u) {
+              const int r = g * G + u;
+              const T rowv = rowsh[wave * RPW + r] + shift;
+              T c[VEC];
+              if (r < kHeld) {
 #pragma unroll
-            for (int e = 0; e < PW; ++e) own[e] = v[e];
-          if (slim) {  // the column's sum as a float and what that leaves out
-            const double rest = v[0] - (double)(float)v[0];
-            v[PW - 1] = rest - rest == 0.0 ? rest : 0.0;
-          }
-          if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack((float)v[0], (float)v[PW - 1]));
-          else st_word(dst, 8 * t, pack_double(v[0]));
-          st_word(clr, 8 * t, kSent);
-        } else if (wave == kResWaves - 1) {
-          // the sum of eight (or four) LDS values from `src` on
-          const int q = t & (kWave - 1);
-          if (q < kRwCount) {
-            const double* src = q <= kRwS1 ? sh.wsum[q] : &sh.esum[q & 1][q >= kRwS2 ? 4 : 0];
-            double v = (src[0] + src[1]) + (src[2] + src[3]);
-            if (q <= kRwS1) v += (src[4] + src[5]) + (src[6] + src[7]);
-            if (q == kRwCtl) v = sh.ctl;
-            st_word(dst, 8 * (WC + WR + q), pack_double(v));
-            st_word(clr, 8 * (WC + WR + q), kSent);
-          }
-        } else if (t < WC + WR) {
-          const int w = t - WC;
-          if constexpr (kRows64) {
-            const double v = rowp[w], rest = v - (double)(float)v;
-            st_word(dst, 8 * t, Wd::pack((float)v, rest - rest == 0.0 ? (float)rest : 0.f));
-          } else if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack(rowp[2 * w], rowp[2 * w + 1]));
-          else st_word(dst, 8 * t, pack_double((double)rowp[w]));
-          st_word(clr, 8 * t, kSent);
-        }
-      }
-      __syncthreads();  // `buf` changes its use
-
-      // While the peers' words are on their way: the test of iteration k - 1.
-      // (A segment begins with both iterations before it tested.)
-      if (b == 0 && wave == 6 && !replay && k > start)
-        res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
-
-      // Read the peers' words.  All loads of a batch are in flight together,
-      // and so are the repeats of those that came too early.
-      bool fine = true;
-      {
-        const int t = fresh_lane(tid), nc = fresh(nc0);
-        const int rsub = t / WR;
-        const int nr = rsub < GR && rsub < S ? (S - rsub + GR - 1) / GR : 0;
-        const uint32_t orow = 8 * ((nr > 0 ? rsub : 0) * MSG + t % WR);
-        const int sc = 8 * GC * S * MSG, sr = 8 * GR * MSG;
-        const Msg pcol = word_at(cur, ocol), prow = word_at(cur, 8 * (ti * S * MSG + WC));
-        const uint32_t vcol = 8 * (t & (WC - 1));
-        const int xl = (t & (kWave - 1)) >> xsh;  // which workgroup's word
-        const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
-        const uint32_t ox = 8 * (WC + WR + xw + (t & xsh)) + (nx > 0 ? xl * xstep : 0);
-        const int sx = xstep << (6 - xsh);
-        double cs[PW], rsu[PW];
-        u64 wx[4];
-#pragma unroll
-        for (int e = 0; e < PW; ++e) cs[e] = rsu[e] = 0.0;
-        // wave 7's scalar step: everything but the total, ready beforehand
-        double sum_p = 0.0, alpha = 0.0, dn = 0.0, dm = 0.0, inv[3] = {0.0, 0.0, 0.0};
-        auto scalars = [&]() {
-          sum_p = sh.sv.sum_p;
-          alpha = sh.bc[k & 3][2];
-          dn = (double)fresh_lane(n);
-          dm = (double)fresh_lane(m);
-#pragma unroll
-          for (int q = 0; q < 3; ++q) inv[q] = sh.inv[q];
-        };
-        if (RPW <= 16 && wave == 7) scalars();
-        if (extra) res_load4(wx, cur, ox, sx, nx);
-        auto rounds = [&](int rc) { return rc > nqr ? rc : nqr; };
-        if (RPW >= 24 || (R > 2 * GC && R <= 4 * GC))
-          fine = res_read<T, 4, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 4 * GC - 1) / (4 * GC)), cs, rsu);
-        else if (R <= 2 * GC)
-          fine = res_read<T, 2, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds(1), cs, rsu);
-        else
-          fine = res_read<T, 8, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 8 * GC - 1) / (8 * GC)), cs, rsu);
-#pragma unroll
-        for (int e = 0; e < PW; ++e) buf[t * PW + e] = lone ? own[e] : cs[e];  // [csub][column]
-        if (t < GR * WR)
-#pragma unroll
-          for (int e = 0; e < PW; ++e) buf[GC * W + t * PW + e] = rsu[e];  // [rsub][row]
-        if (extra) {
-          double v = 0.0;
-          if (fine) fine = res_sum4(wx, cur, ox, sx, nx, v);
-          if (wave == 7) {
-            // beta from the total of X, and the scalar parts of the shifts
-            v = wave_sum(v);
-            if (RPW > 16) scalars();
-            const double beta = div_by(v - sum_p, dm + dn, inv[2]);
-            const double cc = 2.0 * beta - alpha;
-            const double nphi = div_by(cc, dn, inv[0]), npsi = div_by(cc, dm, inv[1]);
-            if (lane == 0) {
-              sh.bc[(k + 1) & 3][0] = nphi;
-              sh.bc[(k + 1) & 3][1] = npsi;
-              sh.bc[(k + 1) & 3][2] = alpha - beta;
-            }
-          } else if (wave == 2) {
-            if (lane == 0 && !replay) sh.stop_at = (int)v;
-          } else if (wave >= 5) {
-            sh.mon[seq & 1][wave - 5][lane] = v;
-          } else {
-            res_keep(sh.mon[seq & 1], wave, lane, v);
-          }
-        }
-      }
-      if (!fine) sh.dead = 1;
-      __syncthreads();
-      if (uni(sh.dead)) break;
-
-      // Steps 5-8 of this tile's rows and columns.
-      {
-        const int tid = fresh_lane((int)threadIdx.x), cc0 = tid - 256;
-        const bool is_row = tid < TR, is_col = cc0 >= 0 && cc0 < W;
-        const int gid = is_row ? row0 + tid : col0 + cc0;
-        const bool own_r = is_row && gid < m, own_c = is_col && gid < n;
-        double tot = 0.0;
-        if (is_row) {
-          for (int q = 0; q < GR && q < S; q += 4) {
-            // the peers' sums in order, zeros where there is no peer
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (q + u < GR) {
-                if constexpr (kRows64) {
-                  const double* const v = buf + GC * W + ((q + u) * WR + tid) * 2;
-                  tot += v[0] + v[1];
-                } else {
-                  tot += buf[GC * W + (q + u) * TR + tid];
-                }
+                for (int e = 0; e < VEC; ++e) c[e] = pc[r < kHeld ? r : 0][e];
+              } else {
+                load_chunk<T, VEC, false>(held + (r - kHeld) * W, c);
               }
-          }
-        } else if (is_col) {
+              T rsum = (T)0;
 #pragma unroll
-          for (int q = 0; q < GC; ++q)
-            tot += slim ? buf[q * W + 2 * (cc0 & (WC - 1))] + buf[q * W + 2 * (cc0 & (WC - 1)) + 1]
-                        : buf[q * W + cc0];
-        }
-        double e[2] = {0.0, 0.0};
-        if (own_r || own_c) {
-          const double mg = (double)fresh_lane(marg), acc = accs[tid];
-          const double res = tot - mg;
-          const int len = is_row ? n : m;
-          const double dual = div_by(acc - 2.0 * res, (double)fresh_lane(len), sh.inv[is_row ? 0 : 1]);
-          accs[tid] = acc - res;
-          if (is_row) rowsh[tid] = (T)dual;
-          else colsh[cc0] = (T)dual;
-          e[0] = res * res;
-          e[1] = mg * dual;
-          // phi~ and psi~ in full, of what may be the last iteration
-          if (k + 1 == end) {
-            const ResTeam* const t4 = fresh(tm);
-            if (is_row && tj == 0) t4->a.phi64[gid] = dual;
-            if (!is_row && ti == 0) t4->a.psi64[gid] = dual;
+              for (int e = 0; e < VEC; ++e) {
+                const T t = rowv + colv[e] - c[e];
+                const T tp = relu_of(t);
+                s1 += tp * tp;
+                const T x = relu_of(xr[r][e] + t);
+                xr[r][e] = x;
+                rsum = e == 0 ? x : rsum + x;
+                ca[e] = u == 0 ? x : ca[e] + x;
+                s0 += c[e] * x;
+              }
+              rs[u] = (RowSum)rsum;
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) cd[e] += (double)ca[e];
+            s0d += (double)s0;
+            s1d += (double)s1;
+            const RowSum v = wave_fold(rs, lane);
+            rowp[wave * RPW + g * G + lane / (kWave / G)] = v;  // its 64 / G lanes agree
+            rtot += (double)v;
+            __builtin_amdgcn_sched_barrier(0);
           }
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) buf[wave * W + lane * VEC + e] = cd[e];
+          // rtot holds G distinct values, each in 64 / G neighbouring lanes
+          if (G == 8) rtot += dpp<0x128>(rtot);
+          rtot += dpp<0x142, 0xA>(rtot);
+          rtot += dpp<0x143, 0xC>(rtot);
+          double sx = fold32(s0d, s1d);  // lanes < 32: s0, others: s1
+          sx += dpp<0xB1>(sx);
+          sx += dpp<0x4E>(sx);
+          sx += dpp<0x141>(sx);
+          sx += dpp<0x140>(sx);
+          sx += dpp<0x142, 0xA>(sx);
+          if (lane == 63) {
+            sh.wsum[0][wave] = rtot;
+            sh.wsum[2][wave] = sx;
+          }
+          if (lane == 31) sh.wsum[1][wave] = sx;
         }
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        // The sums that the test needs, from the first tile column and row
-        // (waves 0-3 hold rows, 4-7 columns).
-        if (!replay && ((wave < 4 && tj == 0) || (wave >= 4 && ti == 0))) {
-          double v = fold32(e[0], e[1]);  // lanes < 32: e[0], others: e[1]
-          v += dpp<0xB1>(v);
-          v += dpp<0x4E>(v);
-          v += dpp<0x141>(v);
-          v += dpp<0x140>(v);
-          v += dpp<0x142, 0xA>(v);
-          if (lane == 31) sh.esum[0][wave] = v;
-          if (lane == 63) sh.esum[1][wave] = v;
-        }
-      }
-      ++seq;
-      ++k;
-      if (uni(sh.stop_at) > 0) break;
-    }
-    if (uni(sh.dead) || replay || uni(sh.stop_at) > 0) break;
-    // The end of a segment: an exchange for the last two tests.
-    if (b == 0 && wave == 6)
-      res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
-    exchange();
-    if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
-    if (b == 0 && wave == 6)
-      res_test(sh, sh.mon[(seq - 1) & 1], k, lane);
-    if (k == limit) break;
-    // Another one for the word that the launch goes on, and the state is saved.
-    __syncthreads();  // every thread has read stop_at
-    exchange();
-    if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
-    store_x();
-    double* const v = saved();
-    v[0] = accs[tid];
-    v[1] = is_row ? (double)rowsh[tid] : is_col ? (double)colsh[cc0] : 0.0;
-    if (tid == 0)
+
+        // Publish, then clear the words for the step after the next.
+        double own[PW];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) sh.base[q] = sh.bc[k & 3][q];
-    base = k;
+        for (int e = 0; e < PW; ++e) own[e] = 0.0;
+        {
+          const int t = fresh_lane(tid);
+          const Msg dst = word_at(cur, 8 * b * MSG);
+          const Msg clr = word_at(xch + ((seq + 2) & 3) * phase, 8 * b * MSG);
+          if (wave < WC / kWave) {
+            double v[PW];
+            const double* const src = buf + (slim ? t : t * PW);
+#pragma unroll
+            for (int e = 0; e < PW; ++e) v[e] = src[e];
+#pragma unroll
+            for (int q = 1; q < kResWaves; ++q)
+#pragma unroll
+              for (int e = 0; e < PW; ++e) v[e] += src[q * W + e];
+            if (lone)
+#pragma unroll
+              for (int e = 0; e < PW; ++e) own[e] = v[e];
+            if (slim) {  // the column's sum as a float and what that leaves out
+              const double rest = v[0] - (double)(float)v[0];
+              v[PW - 1] = rest - rest == 0.0 ? rest : 0.0;
+            }
+            if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack((float)v[0], (float)v[PW - 1]));
+            else st_word(dst, 8 * t, pack_double(v[0]));
+            st_word(clr, 8 * t, kSent);
+          } else if (wave == kResWaves - 1) {
+            // the sum of eight (or four) LDS values from `src` on
+            const int q = t & (kWave - 1);
+            if (q < kRwCount) {
+              const double* src = q <= kRwS1 ? sh.wsum[q] : &sh.esum[q & 1][q >= kRwS2 ? 4 : 0];
+              double v = (src[0] + src[1]) + (src[2] + src[3]);
+              if (q <= kRwS1) v += (src[4] + src[5]) + (src[6] + src[7]);
+              if (q == kRwCtl) v = sh.ctl;
+              st_word(dst, 8 * (WC + WR + q), pack_double(v));
+              st_word(clr, 8 * (WC + WR + q), kSent);
+            }
+          } else if (t < WC + WR) {
+            const int w = t - WC;
+            if constexpr (kRows64) {
+              const double v = rowp[w], rest = v - (double)(float)v;
+              st_word(dst, 8 * t, Wd::pack((float)v, rest - rest == 0.0 ? (float)rest : 0.f));
+            } else if constexpr (PW == 2) st_word(dst, 8 * t, Wd::pack(rowp[2 * w], rowp[2 * w + 1]));
+            else st_word(dst, 8 * t, pack_double((double)rowp[w]));
+            st_word(clr, 8 * t, kSent);
+          }
+        }
+        __syncthreads();  // `buf` changes its use
+
+        // While the peers' words are on their way: the test of iteration k - 1.
+        // (A segment begins with both iterations before it tested.)
+        if (b == 0 && wave == 6 && !replay && k > start)
+          res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
+
+        // Read the peers' words.  All loads of a batch are in flight together,
+        // and so are the repeats of those that came too early.
+        bool fine = true;
+        {
+          const int t = fresh_lane(tid), nc = fresh(nc0);
+          const int rsub = t / WR;
+          const int nr = rsub < GR && rsub < S ? (S - rsub + GR - 1) / GR : 0;
+          const uint32_t orow = 8 * ((nr > 0 ? rsub : 0) * MSG + t % WR);
+          const int sc = 8 * GC * S * MSG, sr = 8 * GR * MSG;
+          const Msg pcol = word_at(cur, ocol), prow = word_at(cur, 8 * (ti * S * MSG + WC));
+          const uint32_t vcol = 8 * (t & (WC - 1));
+          const int xl = (t & (kWave - 1)) >> xsh;  // which workgroup's word
+          const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
+          const uint32_t ox = 8 * (WC + WR + xw + (t & xsh)) + (nx > 0 ? xl * xstep : 0);
+          const int sx = xstep << (6 - xsh);
+          double cs[PW], rsu[PW];
+          u64 wx[4];
+#pragma unroll
+          for (int e = 0; e < PW; ++e) cs[e] = rsu[e] = 0.0;
+          // wave 7's scalar step: everything but the total, ready beforehand
+          double sum_p = 0.0, alpha = 0.0, dn = 0.0, dm = 0.0, inv[3] = {0.0, 0.0, 0.0};
+          auto scalars = [&]() {
+            sum_p = sh.sv.sum_p;
+            alpha = sh.bc[k & 3][2];
+            dn = (double)fresh_lane(n);
+            dm = (double)fresh_lane(m);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) inv[q] = sh.inv[q];
+          };
+          if (RPW <= 16 && wave == 7) scalars();
+          if (extra) res_load4(wx, cur, ox, sx, nx);
+          auto rounds = [&](int rc) { return rc > nqr ? rc : nqr; };
+          if (RPW >= 24 || (R > 2 * GC && R <= 4 * GC))
+            fine = res_read<T, 4, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 4 * GC - 1) / (4 * GC)), cs, rsu);
+          else if (R <= 2 * GC)
+            fine = res_read<T, 2, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds(1), cs, rsu);
+          else
+            fine = res_read<T, 8, NR>(pcol, vcol, sc, nc, prow, orow, sr, nr, rounds((R + 8 * GC - 1) / (8 * GC)), cs, rsu);
+#pragma unroll
+          for (int e = 0; e < PW; ++e) buf[t * PW + e] = lone ? own[e] : cs[e];  // [csub][column]
+          if (t < GR * WR)
+#pragma unroll
+            for (int e = 0; e < PW; ++e) buf[GC * W + t * PW + e] = rsu[e];  // [rsub][row]
+          if (extra) {
+            double v = 0.0;
+            if (fine) fine = res_sum4(wx, cur, ox, sx, nx, v);
+            if (wave == 7) {
+              // beta from the total of X, and the scalar parts of the shifts
+              v = wave_sum(v);
+              if (RPW > 16) scalars();
+              const double beta = div_by(v - sum_p, dm + dn, inv[2]);
+              const double cc = 2.0 * beta - alpha;
+              const double nphi = div_by(cc, dn, inv[0]), npsi = div_by(cc, dm, inv[1]);
+              if (lane == 0) {
+                sh.bc[(k + 1) & 3][0] = nphi;
+                sh.bc[(k + 1) & 3][1] = npsi;
+                sh.bc[(k + 1) & 3][2] = alpha - beta;
+              }
+            } else if (wave == 2) {
+              if (lane == 0 && !replay) sh.stop_at = (int)v;
+            } else if (wave >= 5) {
+              sh.mon[seq & 1][wave - 5][lane] = v;
+            } else {
+              res_keep(sh.mon[seq & 1], wave, lane, v);
+            }
+          }
+        }
+        if (!fine) sh.dead = 1;
+        __syncthreads();
+        if (uni(sh.dead)) break;
+
+        // Steps 5-8 of this tile's rows and columns.
+        {
+          const int tid = fresh_lane((int)threadIdx.x), cc0 = tid - 256;
+          const bool is_row = tid < TR, is_col = cc0 >= 0 && cc0 < W;
+          const int gid = is_row ? row0 + tid : col0 + cc0;
+          const bool own_r = is_row && gid < m, own_c = is_col && gid < n;
+          double tot = 0.0;
+          if (is_row) {
+            for (int q = 0; q < GR && q < S; q += 4) {
+              // the peers' sums in order, zeros where there is no peer
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (q + u < GR) {
+                  if constexpr (kRows64) {
+                    const double* const v = buf + GC * W + ((q + u) * WR + tid) * 2;
+                    tot += v[0] + v[1];
+                  } else {
+                    tot += buf[GC * W + (q + u) * TR + tid];
+                  }
+                }
+            }
+          } else if (is_col) {
+#pragma unroll
+            for (int q = 0; q < GC; ++q)
+              tot += slim ? buf[q * W + 2 * (cc0 & (WC - 1))] + buf[q * W + 2 * (cc0 & (WC - 1)) + 1]
+                          : buf[q * W + cc0];
+          }
+          double e[2] = {0.0, 0.0};
+          if (own_r || own_c) {
+            const double mg = (double)fresh_lane(marg), acc = accs[tid];
+            const double res = tot - mg;
+            const int len = is_row ? n : m;
+            const double dual = div_by(acc - 2.0 * res, (double)fresh_lane(len), sh.inv[is_row ? 0 : 1]);
+            accs[tid] = acc - res;
+            if (is_row) rowsh[tid] = (T)dual;
+            else colsh[cc0] = (T)dual;
+            e[0] = res * res;
+            e[1] = mg * dual;
+            // phi~ and psi~ in full, of what may be the last iteration
+            if (k + 1 == end) {
+              const ResTeam* const t4 = fresh(tm);
+              if (is_row && tj == 0) t4->a.phi64[gid] = dual;
+              if (!is_row && ti == 0) t4->a.psi64[gid] = dual;
+            }
+          }
+          __syncthreads();
+          // The sums that the test needs, from the first tile column and row
+          // (waves 0-3 hold rows, 4-7 columns).
+          if (!replay && ((wave < 4 && tj == 0) || (wave >= 4 && ti == 0))) {
+            double v = fold32(e[0], e[1]);  // lanes < 32: e[0], others: e[1]
+            v += dpp<0xB1>(v);
+            v += dpp<0x4E>(v);
+            v += dpp<0x141>(v);
+            v += dpp<0x140>(v);
+            v += dpp<0x142, 0xA>(v);
+            if (lane == 31) sh.esum[0][wave] = v;
+            if (lane == 63) sh.esum[1][wave] = v;
+          }
+        }
+        ++seq;
+        ++k;
+        if (uni(sh.stop_at) > 0) break;
+      }
+      if (uni(sh.dead) || replay || uni(sh.stop_at) > 0) break;
+      // The end of a segment: an exchange for the last two tests.
+      if (b == 0 && wave == 6)
+        res_test(sh, sh.mon[(seq - 1) & 1], k - 1 > start ? k - 1 : 0, lane);
+      exchange();
+      if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
+      if (b == 0 && wave == 6)
+        res_test(sh, sh.mon[(seq - 1) & 1], k, lane);
+      if (k == limit) break;
+      // Another one for the word that the launch goes on, and the state is saved.
+      __syncthreads();  // every thread has read stop_at
+      exchange();
+      if (uni(sh.dead) || uni(sh.stop_at) > 0) break;
+      store_x();
+      double* const v = saved();
+      v[0] = accs[tid];
+      v[1] = is_row ? (double)rowsh[tid] : is_col ? (double)colsh[cc0] : 0.0;
+      if (tid == 0)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sh.base[q] = sh.bc[k & 3][q];
+      base = k;
     }
     const int stop = uni(sh.stop_at);
     if (uni(sh.dead) || replay || stop == 0 || stop == k) break;
