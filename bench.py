@@ -8,8 +8,8 @@ m x n plan plus the O(m+n) dual update and the stopping test.  The timed
 workload is the 4096 x 4096 float32 problem (2-D five-Gaussian point clouds,
 squared-Euclidean cost normalised to max 1, Dirichlet(1) marginals,
 rho = (1/ln m)/(m+n)), resident in HBM before timing starts.  One JSON line
-is printed with iterations/s at 4096^2 (`value`: whole graph replays, no
-events), the roofline of the sweep kernel on the 20000 x 20000 instance
+is printed with iterations/s at 4096^2 (`value`: no events; at this size whole
+iterations run in resident launches), the roofline of the sweep kernel on the 20000 x 20000 instance
 (3.2 GB, the HBM-bound size; a timed region of eager launches, every sweep
 carrying hipExtLaunchKernel start/stop events), the times to the 1e-4
 relative stopping test at 4096^2 and 20000^2, the precision forms, the
@@ -111,12 +111,13 @@ def graph_size(steps, check_every):
 
 
 def timed_run(ctx, bind, steps, warmup, flags):
-    """Bind with `flags` (bind(flags, max_iter)), capture the graph, run
-    `warmup` iterations, then time exactly `steps`.  Returns (seconds,
+    """Bind with `flags` (bind(flags, max_iter)), capture the graph where
+    iterations are replayed from one, run `warmup` iterations on the path that
+    is timed, then time exactly `steps`.  Returns (seconds,
     average sweep ms or None, sweeps timed)."""
     import torch
     bind(flags, warmup + steps + 1)
-    ctx.iterate(0)  # graph capture, outside the timed region
+    ctx.iterate(0)  # graph capture, where there is one, outside the timed region
     if warmup:
         ctx.iterate(warmup)
     torch.cuda.synchronize()
@@ -134,8 +135,8 @@ def timed_run(ctx, bind, steps, warmup, flags):
 
 
 def measure(ctx, bind, steps, warmup, flags=0):
-    """Two timed regions of the same workload: graph replays without events
-    (the throughput), then eager launches in which every sweep carries
+    """Two timed regions of the same workload: resident launches or graph
+    replays without events (the throughput), then eager launches in which every sweep carries
     hipExtLaunchKernel start/stop events (the sweep kernel's own average
     duration, the figure the roofline uses)."""
     from paper_2110_11738_amd import drot
@@ -353,15 +354,15 @@ def batch_section(ctx, count=512, iters=100, tol_rho0=2.0, tol=1e-4, n_seq=32, d
 
 def protocol_runs(ctx, bind, runs=10, iters=100):
     """The paper's per-iteration runtime protocol (runtime experiment): `runs`
-    independent runs of `iters` iterations (graph replays), each from a fresh
-    bind; median iterations/s and a 95% interval of the median (order
+    independent runs of `iters` iterations (one resident launch at this size),
+    each from a fresh bind; median iterations/s and a 95% interval of the median (order
     statistics of the runs)."""
     import statistics
     import torch
     rates = []
     for _ in range(runs):
         bind(0, iters + 1)
-        ctx.iterate(0)  # captures the graph: the protocol times its replay
+        ctx.iterate(0)  # captures the graph, where there is one: the protocol times its replay
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         ctx.iterate(iters)
@@ -405,7 +406,7 @@ def paper_sizes_section(ctx, sizes=(100, 200, 500, 1000, 2000, 5000, 10000, 2000
         rates = []
         for _ in range(runs):
             ctx.bind(C, p, q, X, drot.make_params(rho, 0.0, iters + 1, check_every=iters))
-            ctx.iterate(0)  # captures the graph: the protocol times its replay
+            ctx.iterate(0)  # captures the graph, where there is one: the protocol times its replay
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             ctx.iterate(iters)
@@ -794,13 +795,9 @@ def main():
         inst = make_instance(args.m, args.n)
         C, p, q = upload(inst)
         m, n = args.m, args.n
-        G = graph_size(args.steps, args.check_every)
-        log(f"timing {args.steps} iterations ({args.steps // G} replays of a {G}-iteration graph) "
-            f"after {args.warmup} warm-up iterations")
+        log(f"timing {args.steps} iterations after {args.warmup} warm-up iterations")
         bind = dense_binder(ctx, C, p, q, inst.rho, args)
-        bind.check_every = G
         r = measure(ctx, bind, args.steps, args.warmup)
-        bind.check_every = args.check_every
         secs, sweep_ms, cnt = r["seconds"], r["sweep_ms"], r["sweeps_timed"]
         value = args.steps / secs
         alg_bytes = BYTES_PER_ENTRY_F32 * m * n
@@ -832,10 +829,10 @@ def main():
             "data": "synthetic",
             "config": {"workload": f"DROT mixture2d {m}x{n} float32 (two 2-D 5-Gaussian clouds, "
                                    f"sigma 0.1, sq-Euclidean C / max, Dirichlet(1) marginals, "
-                                   f"rho0 = 1/ln m); value = iterations/s at {m}x{n} (graph "
-                                   f"replays of {G} iterations); roofline = the sweep at "
+                                   f"rho0 = 1/ln m); value = iterations/s at {m}x{n}; "
+                                   f"roofline = the sweep at "
                                    f"{args.large}x{args.large} (the HBM instance)",
-                       "m": m, "n": n, "rho": inst.rho, "graph_iterations": G,
+                       "m": m, "n": n, "rho": inst.rho,
                        "tile_rows": args.tile_rows, "tile_chunks": args.tile_chunks,
                        "tile_unroll": args.tile_unroll, "cache_mode": args.cache_mode,
                        "tile_groups": args.tile_groups,
