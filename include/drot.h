@@ -119,38 +119,46 @@ typedef enum { DROT_CACHE_AUTO = 0, DROT_CACHE_CACHED = 1, DROT_CACHE_STREAM = 2
 #define DROT_FLAG_COMPENSATED 0x8
 
 /* Small problems take a one-workgroup path: a dense cost whose plan fits the
- * registers of one workgroup -- in float32 n <= 64 and m <= 512,
- * n <= 128 and m <= 256, n <= 256 and m <= 128, or n <= 512 and m <= 64; in
- * float64 half those rows -- with all sweep-schedule fields 0, cache_mode
- * AUTO, neither DROT_FLAG_SKIP_C nor DROT_FLAG_TIME_SWEEP, in float32 not
- * DROT_FLAG_COMPENSATED, and rho and rho times the costs well inside the type's
- * range (float32: 1e-30 to 1e30).  There a single workgroup runs many whole
- * iterations per launch (the same steps, state and stopping test; a lane's
- * partial sums of a row, at most 8 entries, are in the problem's type and
- * everything after them in float64; the test trails by one iteration, and a
- * stop repeats at most 64), since at these sizes two
- * launches per iteration would cost more than the memory traffic;
- * DROT_FLAG_NO_GRAPH has no effect on it.  Setting any tile field keeps a
- * small problem on the sweep + aux path.  drot_result.path reports which
- * path ran. */
+ * registers of one workgroup -- in float32 n <= 64 and m <= 512, n <= 128 and
+ * m <= 256, n <= 256 and m <= 128, or n <= 512 and m <= 64; in float64 half
+ * those rows -- with all sweep-schedule fields 0, cache_mode AUTO, neither
+ * DROT_FLAG_SKIP_C nor DROT_FLAG_TIME_SWEEP, in float32 not
+ * DROT_FLAG_COMPENSATED, and rho and rho times the costs well inside the
+ * type's range (float32: 1e-30 to 1e30).  There a single workgroup runs many
+ * whole iterations per launch (the same steps, state and stopping test; a
+ * lane's partial sums of a row, at most 8 entries, and of <C,X> and the dual
+ * residual, at most 24, are in the problem's type and everything after them in
+ * float64; the test trails by one iteration, and a stop repeats at most 64),
+ * since at these sizes two launches per iteration would cost more than the
+ * memory traffic; DROT_FLAG_NO_GRAPH has no effect on it.  Setting any tile
+ * field keeps a small problem on the sweep + aux path.  drot_result.path
+ * reports which path ran. */
 /* Larger problems up to what the compute units' registers hold (float32 up to
  * 4096 x 4096, float64 up to 2048 x 4096, any cost kind) take the resident
  * path: one cooperative launch runs many iterations with the plan and the cost
- * on the chip, tile by tile, and the tiles exchange their row and column sums.
- * It needs all sweep-schedule fields 0, cache_mode AUTO, no flags (float64
- * ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32, max_iter at
- * least 8 and rho and rho times the costs in the same range; anything else, and a call on a stream that is being captured or has
- * fewer compute units, runs sweep + aux launches from the same state.  Steps,
- * state and stopping test are the same; sums are formed in another order, so
- * results agree with sweep + aux to rounding.  How iterations are split into
- * calls, and a checkpoint between them, changes no bit on either path.  A
- * launch whose workgroups do not all reach the chip (other processes' kernels
- * keep some away for 0.2 s) does nothing; its iterations are run as sweep + aux
- * before drot_poll, drot_finish, drot_checkpoint or drot_get_trace reports, and
- * the bound problem then stays there.  A
- * run that stops inside a launch repeats the iterations since its last saved
+ * on the chip, tile by tile, and the tiles exchange their row and column
+ * sums.  It needs all sweep-schedule fields 0, cache_mode AUTO, no flags
+ * (float64 ignores DROT_FLAG_COMPENSATED), check_every 0 or at least 32,
+ * max_iter at least 8, and rho and rho times the costs in the same range.
+ * Anything else, and a call on a stream that is being captured or has fewer
+ * compute units, runs sweep + aux launches from the same state.
+ *
+ * Steps, state and stopping test are the same; sums are formed in another
+ * order, so results agree with sweep + aux to rounding.  On either path, how
+ * iterations are split into calls, and a checkpoint between them, changes no
+ * bit.  In float32 problems a lane's column sums run over 8 rows, a row's sum
+ * over a tile's 256 columns, and <C,X> and the dual residual over 32 entries
+ * in float32; a tile's row and column sums go to the other tiles as floats,
+ * except where a plan has at most 128 columns or 32 rows, whose few duals
+ * would show it.
+ *
+ * A run that stops inside a launch repeats the iterations since its last saved
  * state up to the stopping one (the test trails by two; a state is saved after
- * 32 or 128 iterations, then at each doubling and every 256).  path reports 0. */
+ * 32 or 128 iterations, then at each doubling and every 256).  A launch whose
+ * workgroups do not all reach the chip (another process's kernels keep some
+ * away for 0.2 s) does nothing; its iterations are run as sweep + aux before
+ * drot_poll, drot_finish, drot_checkpoint or drot_get_trace reports, and the
+ * bound problem then stays there.  drot_result.path is 0. */
 typedef struct {
   double rho;          /* penalty parameter rho > 0 (the paper uses rho0/(m+n)) */
   double tol;          /* stopping tolerance >= 0; 0 runs exactly max_iter iterations */
@@ -168,7 +176,8 @@ typedef struct {
   int32_t tile_unroll; /* rows whose loads a wave keeps in flight (4 or 8) */
   int32_t cache_mode;  /* drot_cache_mode for the plan and cost streams */
   int32_t tile_groups; /* row groups (workgroups per strip); 0 = one row block per
-                          workgroup when cached, two when streaming */
+                          workgroup when cached (two for costs that are not
+                          dense), two or four when streaming */
   int32_t reserved;    /* must be 0 */
 } drot_params;
 
@@ -184,7 +193,9 @@ typedef struct {
   double r_primal, r_dual, gap;          /* exact, at the returned (X, mu, nu) */
   double eps_primal, eps_dual, eps_gap;  /* the relative forms of the three */
   double seconds_to_tol;  /* device clock, start of initialisation to the end of
-                             the iteration that met the test (or the last one) */
+                             the iteration that met the test (or the last one); on
+                             the one-workgroup and resident paths to the end of its
+                             launch, repeated iterations included */
   double seconds_total;   /* host wall clock of the call */
   double sweep_ms_total;  /* with DROT_FLAG_TIME_SWEEP: summed hipEvent time of
                              the timed sweep launches, else 0 */
@@ -227,7 +238,8 @@ const char *drot_last_error(void);
 
 /* Create a context on HIP device `device` (0-based).  The context owns the
  * workspace (grown on demand, kept between solves), the pinned host mirror of
- * the device state and the captured graphs.  Returns DROT_EDEVICE when no GPU
+ * the device state and the captured graphs.  A process's first context also sets
+ * up what cooperative launches need (17 ms).  Returns DROT_EDEVICE when no GPU
  * is usable, DROT_ENOMEM on allocation failure. */
 int drot_ctx_create(drot_ctx **ctx, int device);
 

@@ -62,9 +62,10 @@
 // flight together (a branch and a wait per word: 5.1 us instead of 4.3 at
 // 517 x 483).
 // Measured per iteration against sweep + aux launches, float32: 4.1 us (10.6)
-// at 517 x 483, 4.15 (13.5) at 1000^2, 4.75 (17) at 2000^2, 7.0 at 3000^2, 7.65
-// (36.5) at 4096^2, 9.6 (17.3) at 16384 x 64; float64: 4.15 (14) at 700 x 901,
-// 5.0 at 2000^2, 8.9 at 2800^2.
+// at 517 x 483, 4.2 (13.5) at 1000^2, 4.85 (17) at 2000^2, 7.0 at 3000^2, 7.65
+// (36.5) at 4096^2, 10.6 (17.3) at 16384 x 64; float64: 4.2 (14) at 700 x 901,
+// 5.1 at 2000^2, 8.8 at 2800^2; and per launch 35 to 85 us more, of which the
+// gate takes 3 to 5.
 #pragma once
 
 #include "drot_device.h"
@@ -726,8 +727,12 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       while (k < end) {  // sweep iteration k + 1, exchange, steps 5-8
         const Msg cur = xch + (seq & 3) * phase;
         // Step 4 on the held entries, with the row and column sums of step 5
-        // and the stopping-test sums.  A lane's float32 sums run over at most
-        // 8 rows; from there on everything is float64.
+        // and the stopping-test sums.  Of a float32 problem a lane's column sums
+        // are float32 over 8 rows (FINE: 4), its <rho C,X> and sum [t]_+^2 over
+        // their 32 (16) entries, a row's sum over 4 entries and then, but for
+        // FINE, over the wave; a tile's row and column sums are rounded once more
+        // for their way to the other tiles (FINE: see there).  Every other sum
+        // is float64.
         {
           const int lane = fresh_lane(tid) & (kWave - 1);
           const T shift = (T)(sh.bc[k & 3][0] + sh.bc[k & 3][1]);

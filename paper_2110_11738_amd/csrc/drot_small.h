@@ -19,6 +19,10 @@
 // memory; after a stop the workgroup loads it and repeats the few iterations
 // up to the stopping one (everything is deterministic).
 //
+// Of a float32 problem a lane's sum of a row (at most 8 entries) and its <rho C,X>
+// and sum [t]_+^2 of a group of rows (at most 24 entries) are float32, every other
+// sum float64.
+//
 // What bounds it: for the largest shapes the vector units of one compute unit
 // (some 12 operations per entry, 64 lanes per clock: 2.6 us of a 256 x 128
 // iteration), for the smallest the chain of two barriers, the column sums, the
