@@ -174,7 +174,7 @@ constexpr int kResMinIters = 8;  // max_iter below it: sweep + aux
 constexpr int kResRpw[] = {4, 8, 16, 24, 32};
 constexpr int kResSaves[] = {32, 128, 256};  // iterations between saved states
 constexpr int kResMaxTiles = 256, kResMaxSide = 128;  // workgroups of a team, tiles of a side
-constexpr int kResGatePolls = 1 << 18;  // of a launch's verdict before giving up (0.2 s)
+constexpr int kResGatePolls = 1 << 20;  // of a launch's verdict before giving up (0.2 s)
 // Words that a team's workgroups share beside the messages (all cleared with them).
 struct ResSync {
   uint32_t seq;      // steps taken since the buffers were cleared

@@ -34,7 +34,7 @@ def _all_counts(ctx):
     return np.array(out)
 
 
-def _rare(ctx, gate_polls=1 << 18, refuse_after=-1):
+def _rare(ctx, gate_polls=1 << 20, refuse_after=-1):
     from paper_2110_11738_amd import drot
     drot.lib().drot_internal_rare(ctx.handle, ctypes.c_int(gate_polls),
                                   ctypes.c_int64(refuse_after))
