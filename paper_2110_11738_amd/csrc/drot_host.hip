@@ -1096,7 +1096,7 @@ extern "C" int drot_tune(drot_ctx* c, int64_t iters, drot_params* best, double* 
     }
     drot_params t = user;
     t.tol = 0.0;
-    t.max_iter = 2 * (iters > 0 ? iters : 256) + 1;
+    t.max_iter = 2 * (iters > 0 ? iters : 256) + kResMinIters;  // the same path as bound
     float ms = 0.f;
     rc = drot_bind_cost(c, A.m, A.n, c->dtype, &A.cost, A.p, A.q, &t, A.X, A.ldx, A.mu0, A.nu0,
                         stream);

@@ -389,6 +389,17 @@ def test_batch_tuner_times_what_the_solver_runs(ctx):
         drot.tune_batched([big, fit[0], bad], iters=32, ctx=ctx)
 
 
+def test_tuning_over_few_iterations_times_the_bound_path(ctx):
+    import torch
+    from paper_2110_11738_amd import drot
+    C, p, q, rho = _problem(300, 700, "float32")
+    ctx.bind(C, p, q, torch.empty_like(C), drot.make_params(rho, 0.0, 1000))
+    for iters in (1, 3, 20):
+        c0 = _counts(ctx)
+        best, us = ctx.tune(iters)
+        assert tuple(_counts(ctx) - c0) == (2, 0, 0) and us > 0
+
+
 FIRST = """
 import time, torch
 from paper_2110_11738_amd import drot
