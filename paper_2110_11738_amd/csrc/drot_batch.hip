@@ -825,7 +825,7 @@ extern "C" int drot_tune_batched(drot_ctx* c, int32_t count, int dtype, const dr
   double chip_us = 0.0;
   if (!rc) {
     drot_params t = trial;
-    t.max_iter = 2 * iters + 1;
+    t.max_iter = 2 * iters + kResMinIters;  // the same path as under *prm
     rc = time_resident(c, (int32_t)on_chip.size(), dtype, on_chip.data(), &t, iters, s, e0, e1,
                        &chip_us);
   }

@@ -398,6 +398,10 @@ def test_tuning_over_few_iterations_times_the_bound_path(ctx):
         c0 = _counts(ctx)
         best, us = ctx.tune(iters)
         assert tuple(_counts(ctx) - c0) == (2, 0, 0) and us > 0
+        c0 = _counts(ctx)
+        table = drot.tune_batched([dict(C=C, p=p, q=q, rho=rho, tol=0.0)], iters=iters, ctx=ctx)
+        assert tuple(_counts(ctx) - c0) == (2, 0, 0) and table[0]["us_per_iter"] > 0
+        ctx.bind(C, p, q, torch.empty_like(C), drot.make_params(rho, 0.0, 1000))
 
 
 FIRST = """
