@@ -78,10 +78,12 @@ typedef unsigned long long u64;
 constexpr u64 kSent = ~0ull;
 constexpr int kResSpins = 1 << 22;  // polls of one word before giving up (seconds)
 constexpr int kResScal = 16;        // scalar words of a message
-// Scalar words: total of the tile, <rho C, X>, sum [t]_+^2, stop iteration
+// Scalar words: <rho C, X>, sum [t]_+^2, total of the tile, stop iteration
 // (workgroup 0), and of the previous iteration sum r^2, sum p phi~ (tile
-// column 0), sum s^2, sum q psi~ (tile row 0).
-enum ResWord : int { kRwTot = 0, kRwS0, kRwS1, kRwCtl, kRwR2, kRwPphi, kRwS2, kRwQpsi, kRwCount };
+// column 0), sum s^2, sum q psi~ (tile row 0).  Float64 problems have the total
+// in two words (see split_sum), in one line of memory, and the stop iteration
+// in the last word.
+enum ResWord : int { kRwS0 = 0, kRwS1, kRwTot, kRwLow, kRwR2, kRwPphi, kRwS2, kRwQpsi, kRwLast };
 // A message: column words, row words, scalar words.
 
 // Messages are global memory (the address space is spelled out because the
@@ -166,6 +168,25 @@ __device__ __forceinline__ V wave_fold(V (&r)[4], int) {
   return v;
 }
 
+// beta is the small difference of two sums of about sum p, so a float64 problem
+// takes it from sums without rounding errors of their size: every row sum and every
+// p_i is split into a multiple of 2^-24 sum p, whose sums are exact, and the rest,
+// whose sums' errors are 2^-24 times smaller.  (With beta from the rounded total
+// less sum p, alpha gathers its errors: nu of 8000 x 40 was 2.8 times as far from
+// the exact iterate after 1000 iterations as with the sweeps, which add residuals.
+// It costs 0.13 us of 4.2 per iteration at 700 x 901, 0.3 of 5.05 at 2000 x 2000,
+// 0.4 of 8.8 at 2800 x 2800; with the second words read by a wave of their own,
+// from lines of their own, 0.25, 0.65 and 0.45.)
+__device__ __forceinline__ double split_magic(double sum_p) {
+  const uint64_t e = ((__builtin_bit_cast(uint64_t, sum_p) >> 52) & 0x7ffu) + 28;
+  return __builtin_bit_cast(double, (e < 2046 ? e : 2046) << 52 | (uint64_t)1 << 51);  // 1.5 2^52 multiples
+}
+__device__ __forceinline__ void split_sum(double v, double magic, double (&sum)[2]) {
+  const double big = (v + magic) - magic;
+  sum[0] += big;
+  sum[1] += v - big;
+}
+
 // Keeps the compiler from carrying `p` (and addresses made from it) in
 // registers from an earlier use: the plan takes most of them.
 template <typename P>
@@ -234,7 +255,10 @@ __device__ __forceinline__ bool res_leave(ResSync* g, int blocks) {
 
 // Shared state of a workgroup outside the sums.
 struct ResShared {
-  double wsum[3][kResWaves];  // total, <rho C,X>, sum [t]_+^2 per wave
+  double wsum[4][kResWaves];  // <rho C,X>, sum [t]_+^2, total (float64: in two) per wave
+  double psum[2][4];          // float64, first tile column: sum of p_i in two, per wave
+  double total[2][2];         // float64: the total less sum p in two, by waves 7 and 2
+  double magic;
   double esum[2][kResWaves];  // sum r^2 (or s^2), sum p phi~ (or q psi~) per wave
   double bc[4][3];            // cphi, cpsi, alpha after iteration k, at k mod 4
   double inv[3];              // 1 / n, 1 / m, 1 / (m + n)
@@ -373,6 +397,19 @@ __device__ __forceinline__ void res_test(ResShared& sh, const double (&mon)[6][k
   sh.prev[1] = w[1];
 }
 
+// The scalar step of iteration k + 1 from the total of X less sum p (one wave).
+__device__ __forceinline__ void res_scalars(ResShared& sh, int k, int lane, double excess, double alpha,
+                                            double dn, double dm, const double (&inv)[3]) {
+  const double beta = div_by(excess, dm + dn, inv[2]);
+  const double cc = 2.0 * beta - alpha;
+  const double nphi = div_by(cc, dn, inv[0]), npsi = div_by(cc, dm, inv[1]);
+  if (lane == 0) {
+    sh.bc[(k + 1) & 3][0] = nphi;
+    sh.bc[(k + 1) & 3][1] = npsi;
+    sh.bc[(k + 1) & 3][2] = alpha - beta;
+  }
+}
+
 // RPW rows per wave (tiles of 8 RPW rows), of which the last CL keep rho C in
 // LDS.  `map`: the (team, workgroup) of each block, or null for the one team
 // teams[0].
@@ -472,17 +509,26 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
   const int nqr = (S + GR * NR - 1) / (GR * NR);  // rounds for the row words
   // Scalar words that a wave reads, up to four per lane: word ox + (lane mod
   // (1 << xsh)) of every xstep-th byte from lane >> xsh on, xcnt of them.
-  // Every workgroup: wave 7 the totals, wave 2 the stop word.  Workgroup 0:
+  // Every workgroup: wave 7 the totals, wave 2 the stop word; float64: wave 7
+  // the totals' two words by two lanes, of the first kHalf workgroups, wave 2 of
+  // the others, wave 1 the stop word.  Workgroup 0:
   // waves 5 and 6 <rho C,X> and the dual sums of all tiles, wave 3 the row sums
   // (first tile column), wave 4 the column sums (first tile row), two words
   // of a workgroup by two lanes.
   int xcnt = R * S, xstep = 8 * MSG, xsh = 0, xw = kRwTot;
-  if (wave == 2) xcnt = 1, xstep = 0, xw = kRwCtl;
+  constexpr bool kSplit = sizeof(T) == 8;
+  constexpr int kCtlWave = kSplit ? 1 : 2, kRwCtl = kSplit ? kRwLast : kRwLow;
+  constexpr int kRwCount = kRwLast + kSplit, kHalf = 2 * kWave;
+  static_assert(kRwCount <= kResScal, "scalar words");
+  if (kSplit && wave == 7) xsh = 1, xcnt = xcnt < kHalf ? xcnt : kHalf;
+  if (kSplit && wave == 2) xsh = 1, xcnt -= kHalf, xw += kHalf * MSG;
+  if (wave == kCtlWave) xcnt = 1, xstep = 0, xw = kRwCtl;
   if (wave == 3) xcnt = R, xstep = 8 * MSG * S, xsh = 1, xw = kRwR2;
   if (wave == 4) xcnt = S, xsh = 1, xw = kRwS2;
   if (wave == 5) xw = kRwS0;
   if (wave == 6) xw = kRwS1;
-  const bool extra = wave == 2 || wave == 7 || (b == 0 && wave > 2);
+  const bool totals = wave == 7 || (kSplit && wave == 2 && xcnt > 0);
+  const bool extra = wave == kCtlWave || totals || (b == 0 && wave > 2);
   // Words of its own message that a thread writes: column and row words by
   // number, the scalar words in the last wave, which has no others.
   static_assert(WC + WR <= kResBlock - kWave, "the last wave writes the scalar words");
@@ -504,6 +550,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     sh.trace = tm->a.trace;
     sh.trace_mask = (int)tm->a.trace_cap - 1;
     sh.ctl = 0.0;
+    sh.magic = split_magic(sh.sv.sum_p);
+    sh.total[1][0] = sh.total[1][1] = 0.0;
     sh.dead = 0;
     sh.rec_k = sh.rec_done = sh.rec_status = 0;
   }
@@ -565,7 +613,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     if (wave == kResWaves - 1) {
       if (lane < kRwCount) {
         const double* src = &sh.esum[lane & 1][lane >= kRwS2 ? 4 : 0];
-        double v = lane >= kRwR2 ? (src[0] + src[1]) + (src[2] + src[3]) : 0.0;
+        double v = lane >= kRwR2 && lane <= kRwQpsi ? (src[0] + src[1]) + (src[2] + src[3]) : 0.0;
         if (lane == kRwCtl) v = sh.ctl;
         st_word(dst, 8 * (WC + WR + lane), pack_double(v));
         st_word(clr, 8 * (WC + WR + lane), kSent);
@@ -573,9 +621,9 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
     } else if (tid < WC + WR) {
       st_word(clr, 8 * tid, kSent);
     }
-    // Wave 7 waits for everybody's word, as in an iteration: whoever has it
-    // is done with the message before, which the next step clears.
-    if (wave == 2 || wave == 7 || (b == 0 && (wave == 3 || wave == 4))) {
+    // Wave 7 (and 2) waits for everybody's word, as in an iteration: whoever has
+    // it is done with the message before, which the next step clears.
+    if (wave == kCtlWave || totals || (b == 0 && (wave == 3 || wave == 4))) {
       const int xl = lane >> xsh;
       const int nx = xcnt > xl ? (xcnt - xl + (kWave >> xsh) - 1) >> (6 - xsh) : 0;
       const uint32_t ox = 8 * (WC + WR + xw + (lane & xsh)) + (nx > 0 ? xl * xstep : 0);
@@ -585,7 +633,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       res_load4(wx, cur, ox, sx, nx);
       if (!res_sum4(wx, cur, ox, sx, nx, v)) sh.dead = 1;
       if (wave == 3 || wave == 4) res_keep(sh.mon[seq & 1], wave, lane, v);
-      else if (wave == 2 && lane == 0) sh.stop_at = (int)v;
+      else if (wave == kCtlWave && lane == 0) sh.stop_at = (int)v;
     }
     __syncthreads();
     ++seq;
@@ -713,6 +761,14 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
       sh.stop_at = 0;
     }
     if (tid < 2 * kResWaves) sh.esum[tid & 1][tid >> 1] = 0.0;
+    if constexpr (kSplit) {
+      if (wave < 4) {
+        double ps[2] = {0.0, 0.0};
+        if (own_r && tj == 0) split_sum((double)marg, split_magic(st->sum_p), ps);
+        wave_sum_n(ps);
+        if (lane == 0) sh.psum[0][wave] = ps[0], sh.psum[1][wave] = ps[1];
+      }
+    }
     __syncthreads();
 
     k = base;
@@ -740,7 +796,8 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           T colv[VEC];
 #pragma unroll
           for (int e = 0; e < VEC; ++e) colv[e] = colsh[lane * VEC + e];
-          double cd[VEC], s0d = 0.0, s1d = 0.0, rtot = 0.0;
+          double cd[VEC], s0d = 0.0, s1d = 0.0, rtot[2] = {0.0, 0.0};
+          const double magic = kSplit ? sh.magic : 0.0;
 #pragma unroll
           for (int e = 0; e < VEC; ++e) cd[e] = 0.0;
 #pragma unroll
@@ -778,15 +835,19 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
             s1d += (double)s1;
             const RowSum v = wave_fold(rs, lane);
             rowp[wave * RPW + g * G + lane / (kWave / G)] = v;  // its 64 / G lanes agree
-            rtot += (double)v;
+            if constexpr (kSplit) split_sum((double)v, magic, rtot);
+            else rtot[0] += (double)v;
             __builtin_amdgcn_sched_barrier(0);
           }
 #pragma unroll
           for (int e = 0; e < VEC; ++e) buf[wave * W + lane * VEC + e] = cd[e];
           // rtot holds G distinct values, each in 64 / G neighbouring lanes
-          if (G == 8) rtot += dpp<0x128>(rtot);
-          rtot += dpp<0x142, 0xA>(rtot);
-          rtot += dpp<0x143, 0xC>(rtot);
+#pragma unroll
+          for (int h = 0; h < (kSplit ? 2 : 1); ++h) {
+            if (G == 8) rtot[h] += dpp<0x128>(rtot[h]);
+            rtot[h] += dpp<0x142, 0xA>(rtot[h]);
+            rtot[h] += dpp<0x143, 0xC>(rtot[h]);
+          }
           double sx = fold32(s0d, s1d);  // lanes < 32: s0, others: s1
           sx += dpp<0xB1>(sx);
           sx += dpp<0x4E>(sx);
@@ -794,10 +855,11 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           sx += dpp<0x140>(sx);
           sx += dpp<0x142, 0xA>(sx);
           if (lane == 63) {
-            sh.wsum[0][wave] = rtot;
-            sh.wsum[2][wave] = sx;
+            sh.wsum[kRwTot][wave] = rtot[0];
+            sh.wsum[kRwS1][wave] = sx;
+            if (kSplit) sh.wsum[kRwLow][wave] = rtot[1];
           }
-          if (lane == 31) sh.wsum[1][wave] = sx;
+          if (lane == 31) sh.wsum[kRwS0][wave] = sx;
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -833,9 +895,14 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
             // the sum of eight (or four) LDS values from `src` on
             const int q = t & (kWave - 1);
             if (q < kRwCount) {
-              const double* src = q <= kRwS1 ? sh.wsum[q] : &sh.esum[q & 1][q >= kRwS2 ? 4 : 0];
+              const bool sums = q <= kRwLow;  // of the eight waves
+              const double* src = sums ? sh.wsum[q] : &sh.esum[q & 1][q >= kRwS2 ? 4 : 0];
               double v = (src[0] + src[1]) + (src[2] + src[3]);
-              if (q <= kRwS1) v += (src[4] + src[5]) + (src[6] + src[7]);
+              if (sums) v += (src[4] + src[5]) + (src[6] + src[7]);
+              if (kSplit && (q == kRwTot || q == kRwLow)) {
+                const double* const ps = sh.psum[q == kRwLow];
+                v -= (ps[0] + ps[1]) + (ps[2] + ps[3]);
+              }
               if (q == kRwCtl) v = sh.ctl;
               st_word(dst, 8 * (WC + WR + q), pack_double(v));
               st_word(clr, 8 * (WC + WR + q), kSent);
@@ -886,7 +953,7 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
 #pragma unroll
             for (int q = 0; q < 3; ++q) inv[q] = sh.inv[q];
           };
-          if (RPW <= 16 && wave == 7) scalars();
+          if (!kSplit && RPW <= 16 && wave == 7) scalars();
           if (extra) res_load4(wx, cur, ox, sx, nx);
           auto rounds = [&](int rc) { return rc > nqr ? rc : nqr; };
           if (RPW >= 24 || (R > 2 * GC && R <= 4 * GC))
@@ -903,19 +970,18 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
           if (extra) {
             double v = 0.0;
             if (fine) fine = res_sum4(wx, cur, ox, sx, nx, v);
-            if (wave == 7) {
-              // beta from the total of X, and the scalar parts of the shifts
+            if (kSplit && totals) {
+              v += dpp<0x4E>(v);   // even lanes the first words, odd lanes the second
+              v += dpp<0x124>(v);  // row_ror:4
+              v += dpp<0x128>(v);
+              const double hi = (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+              const double lo = (read_lane(v, 1) + read_lane(v, 17)) + (read_lane(v, 33) + read_lane(v, 49));
+              if (lane == 0) sh.total[wave == 2][0] = hi, sh.total[wave == 2][1] = lo;
+            } else if (wave == 7) {
               v = wave_sum(v);
               if (RPW > 16) scalars();
-              const double beta = div_by(v - sum_p, dm + dn, inv[2]);
-              const double cc = 2.0 * beta - alpha;
-              const double nphi = div_by(cc, dn, inv[0]), npsi = div_by(cc, dm, inv[1]);
-              if (lane == 0) {
-                sh.bc[(k + 1) & 3][0] = nphi;
-                sh.bc[(k + 1) & 3][1] = npsi;
-                sh.bc[(k + 1) & 3][2] = alpha - beta;
-              }
-            } else if (wave == 2) {
+              res_scalars(sh, k, lane, v - sum_p, alpha, dn, dm, inv);
+            } else if (wave == kCtlWave) {
               if (lane == 0 && !replay) sh.stop_at = (int)v;
             } else if (wave >= 5) {
               sh.mon[seq & 1][wave - 5][lane] = v;
@@ -928,6 +994,13 @@ __global__ __launch_bounds__(kResBlock, 2) void resident_kernel(const ResTeam* t
         __syncthreads();
         if (uni(sh.dead)) break;
 
+        if (kSplit && wave == 7) {  // it has no columns; the next sweep is two barriers away
+          double inv[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) inv[q] = sh.inv[q];
+          res_scalars(sh, k, lane, (sh.total[0][0] + sh.total[1][0]) + (sh.total[0][1] + sh.total[1][1]), sh.bc[k & 3][2], (double)fresh_lane(n),
+                      (double)fresh_lane(m), inv);
+        }
         // Steps 5-8 of this tile's rows and columns.
         {
           const int tid = fresh_lane((int)threadIdx.x), cc0 = tid - 256;
