@@ -144,3 +144,55 @@ def test_no_drift_of_the_multipliers_in_float64(ctx, m, n):
     drot.lib().drot_internal_rare(ctx.handle, ctypes.c_int(1 << 20), ctypes.c_int64(-1))
     chip, sweeps = np.sqrt((d ** 2).mean(axis=1))
     assert chip <= 2 * sweeps, (chip, sweeps)
+
+
+@pytest.mark.parametrize("m,n", [(256, 3), (256, 10), (3, 256), (100, 100)])
+def test_no_drift_of_the_multipliers_in_one_workgroup(ctx, m, n):
+    """The same where one workgroup iterates, against the sweeps."""
+    import math
+    import numpy as np
+    import torch
+    from gen import config_mixture_2d
+    from paper_2110_11738_amd import drot
+    d = np.zeros((2, 16))
+    for k in range(16):
+        inst = config_mixture_2d(70 + k, m, n)
+        C, p, q = (torch.tensor(a, device="cuda") for a in (inst.C, inst.p, inst.q))
+        for path, cache in enumerate((drot.CACHE_AUTO, drot.CACHE_STREAM)):
+            _, _, mu, nu = drot.solve(C, p, q, inst.rho, tol=0.0, max_iter=1000,
+                                      cache_mode=cache, ctx=ctx)
+            d[path, k] = math.fsum(mu.tolist() + (-nu).tolist())
+    one, sweeps = np.sqrt((d ** 2).mean(axis=1))
+    assert one <= 2 * sweeps, (one, sweeps)
+
+
+def test_stops_and_calls_of_tall_problems_in_one_workgroup(ctx):
+    """The state that a stop between two saved states repeats from, and that a call
+    leaves to the next, has the corrected alpha: no bit depends on either."""
+    import torch
+    from gen import config_mixture_2d
+    from paper_2110_11738_amd import drot
+    inst = config_mixture_2d(90, 250, 6)
+    C, p, q = (torch.tensor(a, device="cuda") for a in (inst.C, inst.p, inst.q))
+
+    def run(tol, calls):
+        X = torch.empty_like(C)
+        mu, nu = (torch.empty(k, dtype=torch.float64, device="cuda") for k in C.shape)
+        ctx.bind(C, p, q, X, drot.make_params(inst.rho, tol, 10 ** 5))
+        for k in calls:
+            ctx.iterate(k)
+        res = ctx.finish(mu, nu)
+        return res["iters"], ctx.trace(1, res["iters"])[:, 5], X, mu, nu
+
+    stop = None
+    for tol in (1e-2, 3e-3, 1e-3):
+        it, test, *out = run(tol, (4000,))
+        if it == 4000:
+            continue
+        stop = it
+        for calls in ((it,), (64, it - 64) if it > 64 else (it // 2, it - it // 2), (1,) * 3 + (it - 3,)):
+            it2, test2, *out2 = run(0.0, calls)
+            assert it2 == it
+            for a, b in zip(out, out2):
+                assert torch.equal(a, b)
+    assert stop is not None
