@@ -63,8 +63,8 @@
 // 517 x 483).
 // Measured per iteration against sweep + aux launches, float32: 4.1 us (10.6)
 // at 517 x 483, 4.2 (13.5) at 1000^2, 4.85 (17) at 2000^2, 7.0 at 3000^2, 7.65
-// (36.5) at 4096^2, 10.6 (17.3) at 16384 x 64; float64: 4.2 (14) at 700 x 901,
-// 5.1 at 2000^2, 8.8 at 2800^2; and per launch 35 to 85 us more, of which the
+// (36.5) at 4096^2, 10.6 (17.3) at 16384 x 64; float64: 4.3 (14) at 700 x 901,
+// 5.35 at 2000^2, 9.3 at 2800^2; and per launch 35 to 85 us more, of which the
 // gate takes 3 to 5.
 #pragma once
 

@@ -8,7 +8,8 @@
 //    goes to LDS as it is, its column sums (float64) too;
 //  - barrier;
 //  - service wave: column sums over the waves, their total, beta, steps 5-8 of
-//    the columns and the scalar parts of the shifts.  Meanwhile the sweep
+//    the columns and the scalar parts of the shifts (tall float64 problems: alpha
+//    once more at the end, from the rows' residuals).  Meanwhile the sweep
 //    waves add their own rows' partials, four lanes per row, and take steps
 //    5-8 of the rows;
 //  - barrier.
